@@ -476,8 +476,10 @@ const char* lpide_last_error(void);
  * supported transform side >= #in among 64, 128, 256, 512, 640, 896, 1024,
  * 1152, 1280, 1536, 1792, 2048, 2304, 2560, 3072, 3584, 4096, 4608, 5120,
  * 6144, 7168, 8192, 12288, 16384, 24576 (largest prime factor at most 7, as
- * Sec. 4 asks); otherwise one of these or 768, at least #in; sides above 8192
- * run as (3, 4, 6) transforms of length 4096 per sequence) and
+ * Sec. 4 asks), whose correlation runs as overlapping tiles of a smaller side
+ * where that is faster (always above 8192 unless 2 N_z comes near 8192);
+ * otherwise one of these or 768, at least #in, as one transform; sides above
+ * 8192 then run as (3, 4, 6) transforms of length 4096 per sequence) and
  * all_correlations (0: the explicit part of a step after one
  * with theta > 0 from that step's implicit equation, as the log plan does;
  * 1: by the correlation).  precision must be LPIDE_FP64. */
@@ -502,7 +504,7 @@ typedef struct {
     int32_t N_ym, N_yp, N_ystar;      /* N_y^-, N_y^+, N_y^* (Sec. 4) */
     int32_t n_in, n_out;              /* #in and #out per axis */
     int32_t n_nz;                     /* y^in nodes inside [0, x_max] (rows of T^in that are not zero) */
-    int32_t L;                        /* side of the zero-padded correlation transform (>= #in) */
+    int32_t L;                        /* side of the zero-padded correlation transform (>= #in), tiled or not */
     int32_t N_t, n_steps;             /* time steps, entries of the step list */
     double  c, x_int, F;              /* grid constant, end of the uniform part, fraction target */
     double  h_z, z_star, sum_omega;

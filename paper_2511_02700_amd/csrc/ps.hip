@@ -57,6 +57,63 @@ int ps_side_at_least(int need) {
         if (v >= need) return v;
     return 0;
 }
+
+// Tiles per axis for transforms of side M (overlap-save, ps_kernels.hpp): tile
+// outputs advance by vs = M - 2 N_z + 1 - 3.  0: side too short for the weights.
+int tiles_for(int M, int n_out, int N_z) {
+    const int vs = M - 2 * N_z - 2;
+    if (vs < 1) return 0;
+    return std::max(1, (n_out - 3 + vs - 1) / vs);
+}
+
+// Time of the column pass of one tile pair of side M (us, n = 401; the row
+// passes are a tenth of it); 0 below 1024, where nothing is gained by tiles.
+double tile_us(int M) {
+    switch (M) {
+        case 1024: return 10.4;
+        case 1152: return 15.8;
+        case 1280: return 14.2;
+        case 1536: return 15.1;
+        case 1792: return 19.7;
+        case 2048: return 20.0;
+        case 2304: return 40.9;
+        case 2560: return 38.6;
+        case 3072: return 50.4;
+        case 3584: return 64.2;
+        case 4096: return 69.2;
+        case 4608: return 132.0;
+        case 5120: return 151.0;
+        case 6144: return 215.0;
+        case 7168: return 320.0;
+        case 8192: return 361.0;
+        default: return 0.0;
+    }
+}
+
+// Transforms of the correlation when no side is asked for: one of side L, or
+// nb x nb tiles of a side M <= 8192 (one workgroup per sequence) where that is
+// faster: above 4096 a CU holds one workgroup, so that four tiles of 4096 take
+// 277 us where one transform of 8192 takes 361 (NIG0 at N_x = 200, B v whole:
+// 256 us against 350 at 7168).  The two-level transforms take 7e-7 us L^2 log2 L
+// or more (B v whole 1.47 ms at 12288, 3.3 at 16384, 8.0 at 24576; by tiles of 4096
+// and 8192 on the same grids 0.83, 1.32 and 2.82).
+void choose_tiles(const PsHost& hp, int L, int* Lc, int* nb) {
+    *Lc = L;
+    *nb = 1;
+    double best = L > 8192 ? 7.0e-7 * double(L) * L * std::log2(double(L)) : tile_us(L);
+    for (int M : kPsAutoSides) {
+        if (M >= L || tile_us(M) == 0.0) continue;
+        const int t = tiles_for(M, hp.n_out, hp.N_z);
+        if (t < 1) continue;
+        const double c = double(t) * t * tile_us(M);
+        if (c < best) {
+            best = c;
+            *Lc = M;
+            *nb = t;
+        }
+    }
+}
+
 constexpr int BATCH = 16;       // steps enqueued between host checks
 
 struct Kind {
@@ -73,7 +130,9 @@ struct PsPlan {
     double theta = 0.5;
     int N_t = 1;
     hipStream_t stream = nullptr;
-    int L = 0;
+    int L = 0;                      // transform side >= #in (fft_size, or the smallest supported)
+    int Lc = 0;                     // side of the transforms in use: L, or of one tile (choose_tiles)
+    int nb = 1;                     // tiles per axis
     bool jumps = false;
     std::vector<void*> allocs;
     int64_t bytes = 0;
@@ -149,7 +208,7 @@ void destroy(PsPlan* p) {
 
 // Correlation launches for the plan's transform side.
 void bapply(PsPlan* p, const PsConv& c, const double* Y, int k) {
-    switch (p->L) {
+    switch (p->Lc) {
 #define PS_CASE(Lc) \
     case Lc: PsL<Lc>::bapply(c, Y, k); break;
         PS_CASE(64) PS_CASE(128) PS_CASE(256) PS_CASE(512) PS_CASE(640) PS_CASE(768) PS_CASE(896)
@@ -162,7 +221,7 @@ void bapply(PsPlan* p, const PsConv& c, const double* Y, int k) {
 }
 
 void spectrum(PsPlan* p, const double* W, int W2, double2* Xf) {
-    switch (p->L) {
+    switch (p->Lc) {
 #define PS_CASE(Lc) \
     case Lc: PsL<Lc>::spectrum(p->stream, W, W2, Xf, const_cast<double2*>(p->conv.spec), p->conv.tw, p->conv.twM); break;
         PS_CASE(64) PS_CASE(128) PS_CASE(256) PS_CASE(512) PS_CASE(640) PS_CASE(768) PS_CASE(896)
@@ -261,6 +320,8 @@ int create(const lpide_ps_grid* g, const lpide_levy* lv, const lpide_payoff* pay
                 return fail(LPIDE_E_PARAM, msg);
             }
         }
+        p->Lc = p->L;
+        if (o.fft_size == 0) choose_tiles(hp, p->L, &p->Lc, &p->nb);
     }
     {
         hipError_t e = hipSetDevice(o.device);
@@ -324,7 +385,19 @@ int create(const lpide_ps_grid* g, const lpide_levy* lv, const lpide_payoff* pay
     if (p->jumps) {
         op.n_nz = hp.n_nz;
         op.n_out = hp.n_out;
-        op.ldx = std::max(hp.n_nz, hp.n_out);
+        op.ldx = n;
+        op.nb = p->nb;
+        op.vs = p->nb > 1 ? p->Lc - 2 * hp.N_z - 2 : 0;
+        op.v = p->nb > 1 ? op.vs + 3 : hp.n_out;
+        // tile b takes the nodes whose T^out stencil starts in [b vs, b vs + vs)
+        std::vector<int> mlo(p->nb + 1, n);
+        for (int b = 0, m = 0; b < p->nb; ++b) {
+            while (m < n && hp.tout[m].s < b * op.vs) ++m;
+            mlo[b] = m;
+        }
+        int* mlo_d = nullptr;
+        if ((rc = upload(p, &mlo_d, mlo))) return bail(rc);
+        op.mlo = mlo_d;
         int* s = nullptr;
         double* w = nullptr;
         if ((rc = upload_rows(p, hp.tin, &s, &w))) return bail(rc);
@@ -333,7 +406,7 @@ int create(const lpide_ps_grid* g, const lpide_levy* lv, const lpide_payoff* pay
         if ((rc = upload_rows(p, hp.tout, &s, &w))) return bail(rc);
         op.tout_s = s;
         op.tout_w = w;
-        const int L = p->L;
+        const int L = p->Lc;
         auto twiddles = [](int N) {
             std::vector<double2> t(N);
             for (int q = 0; q < N; ++q) {
@@ -343,19 +416,21 @@ int create(const lpide_ps_grid* g, const lpide_levy* lv, const lpide_payoff* pay
             }
             return t;
         };
-        double2 *twd = nullptr, *twM = nullptr, *spec = nullptr, *X = nullptr;
-        double *U = nullptr, *Z = nullptr;
+        double2 *twd = nullptr, *twM = nullptr, *spec = nullptr, *X = nullptr, *Xo = nullptr;
+        double *U = nullptr, *BV = nullptr;
         if ((rc = upload(p, &twd, twiddles(L)))) return bail(rc);
         if (L > 8192 && (rc = upload(p, &twM, twiddles(big_m(L))))) return bail(rc);
-        if ((rc = dalloc(p, &spec, size_t(L / 2 + 1) * L)) || (rc = dalloc(p, &X, size_t(L / 2 + 1) * op.ldx)) ||
-            (rc = dalloc(p, &U, size_t(n) * hp.n_nz)) || (rc = dalloc(p, &Z, size_t(hp.n_out) * n)))
+        const size_t xn = size_t(p->nb) * (L / 2 + 1) * op.ldx;
+        if ((rc = dalloc(p, &spec, size_t(L / 2 + 1) * L)) || (rc = dalloc(p, &X, xn)) || (rc = dalloc(p, &Xo, xn)) ||
+            (L > 8192 && (rc = dalloc(p, &U, size_t(n) * hp.n_nz))) || (rc = dalloc(p, &BV, N)))
             return bail(rc);
         PsConv& c = p->conv;
         c.stream = p->stream;
         c.o = op;
         c.U = U;
         c.X = X;
-        c.Z = Z;
+        c.Xo = Xo;
+        c.BV = BV;
         c.spec = spec;
         c.tw = twd;
         c.twM = twM;
@@ -431,7 +506,7 @@ void iteration(PsPlan* p, const Kind& kd, double* Y, const double* W, int k) {
     auto rows = chr <= 4 ? ps_resid_rows<4> : chr <= 8 ? ps_resid_rows<8> : ps_resid_rows<LINE_MM>;
     auto cols = chc <= 4 ? ps_line_cols<4> : chc <= 8 ? ps_line_cols<8> : ps_line_cols<LINE_MM>;
     hipLaunchKernelGGL(rows, dim3((n + lpb - 1) / lpb), dim3(256), 0, p->stream, (const double*)Y, W,
-                       p->jumps ? (const double*)p->conv.Z : (const double*)nullptr, p->Q, p->ops, kd.sk, p->P_rows,
+                       p->jumps ? (const double*)p->conv.BV : (const double*)nullptr, p->Q, p->ops, kd.sk, p->P_rows,
                        (const PsCtl*)p->ctl, k, tol);
     const bool aa = p->aa_m > 0;
     hipLaunchKernelGGL(cols, dim3((n + 3) / 4), dim3(4 * p->P_cols), 0, p->stream, p->Q, Y, p->ops, kd.sk,
@@ -471,7 +546,7 @@ void enqueue_step(PsPlan* p, int s, int kmax, MState& m) {
         } else {
             if (p->jumps) bapply(p, p->conv, V, 0);
             hipLaunchKernelGGL(ps_expl, eb, dim3(256), 0, p->stream, (const double*)V,
-                               p->jumps ? (const double*)p->conv.Z : (const double*)nullptr, p->E, p->ops,
+                               p->jumps ? (const double*)p->conv.BV : (const double*)nullptr, p->E, p->ops,
                                dt * (1.0 - th), (const PsCtl*)p->ctl);
             a.src = p->E;
         }
@@ -750,8 +825,8 @@ int lpide_ps_apply_B(void* plan, const double* v, double* bv) {
     } else {
         lpide::ps::PsConv c = p->conv;
         c.ctl = nullptr;
+        c.BV = bv;
         lpide::ps::bapply(p, c, v, 0);
-        hipLaunchKernelGGL(lpide::ps::ps_tout1, eb, dim3(256), 0, p->stream, (const double*)c.Z, bv, p->ops);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return fail(LPIDE_E_HIP, std::string("lpide_ps_apply_B: ") + hipGetErrorString(e));

@@ -1,6 +1,7 @@
 // Two-level transforms of the price-space correlation for sides L = R M
-// beyond one workgroup's LDS (M = 4096; R = 3, 4, 6: L = 12288, 16384, 24576;
-// the paper's grids need up to #in = 16807, Sec. 4).
+// beyond one workgroup's LDS (M = 4096; R = 3, 4, 6: L = 12288, 16384, 24576):
+// forced sides (lpide_opts.fft_size), and kernels so long (2 N_z near or above
+// 8192) that tiles of at most 8192 would keep too few outputs each.
 //
 // With w_N = exp(-2 pi i / N), a length-L transform splits by decimation in
 // frequency into R transforms of length M,
@@ -36,15 +37,25 @@ constexpr int big_m(int) { return 4096; }
 
 __device__ __forceinline__ double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 
+// U[row][q] = sum_t T^in_{q, s_q + t} Y[row][s_q + t]; grid (ceil(n_nz / 256), n).
+static __global__ __launch_bounds__(256) void ps_tin2(const double* __restrict__ Y, double* __restrict__ U, PsOps o,
+                                                      const PsCtl* ctl, int k, double tol) {
+    if (ps_halted(ctl, k, tol)) return;
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= o.n_nz) return;
+    const int row = blockIdx.y;
+    const int s = o.tin_s[q];
+    const double* w = o.tin_w + 4 * (size_t)q;
+    const double* y = Y + (size_t)row * o.n + s;
+    U[(size_t)row * o.n_nz + q] = w[0] * y[0] + w[1] * y[1] + w[2] * y[2] + w[3] * y[3];
+}
+
 // Rows forward of a length-L real transform, two rows per workgroup (as one
-// complex sequence), the half spectra into X[k * ldx + row], k = 0..L/2.
-// MODE 0: the rows of v^in = T^in U (U: n x ldu; n_nz rows and columns);
-// MODE 1: rows of a dense real array G (nrows x ncols, row stride ldu).
-template <int M, int R, int MODE>
+// complex sequence), the half spectra into X[k * ldx + row], k = 0..L/2, of the
+// dense real array U (nrows x ncols, row stride ldu).
+template <int M, int R>
 __global__ __launch_bounds__(BIG_T) void ps_big_rows_fwd(const double* __restrict__ U, int ldu, int nrows, int ncols,
                                                          double2* __restrict__ X, int ldx,
-                                                         const int* __restrict__ tin_s,
-                                                         const double* __restrict__ tin_w,
                                                          const double2* __restrict__ twL,
                                                          const double2* __restrict__ twM, const PsCtl* ctl, int k,
                                                          double tol) {
@@ -58,21 +69,9 @@ __global__ __launch_bounds__(BIG_T) void ps_big_rows_fwd(const double* __restric
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < nrows;
     const int tid = threadIdx.x;
-    const double *ua, *ub;
-    double wa[4] = {1.0, 0.0, 0.0, 0.0}, wb[4] = {0.0, 0.0, 0.0, 0.0};
-    if constexpr (MODE == 0) {
-        ua = U + (size_t)tin_s[ra] * ldu;
-        ub = U + (size_t)tin_s[hasb ? rb : ra] * ldu;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            wa[t] = tin_w[4 * ra + t];
-            wb[t] = hasb ? tin_w[4 * rb + t] : 0.0;
-        }
-    } else {
-        ua = U + (size_t)ra * ldu;
-        ub = U + (size_t)(hasb ? rb : ra) * ldu;
-        wb[0] = hasb ? 1.0 : 0.0;
-    }
+    const double* ua = U + (size_t)ra * ldu;
+    const double* ub = U + (size_t)(hasb ? rb : ra) * ldu;
+    const double wb = hasb ? 1.0 : 0.0;
     // y^(r) and y^(r2) for this thread's m from one pass over the inputs (the
     // two sub-sequences of a pair read the same z), then the transform of y^(r)
     auto gather2 = [&](int r, int r2, double2 (&y1)[E], double2 (&y2)[E]) {
@@ -85,17 +84,7 @@ __global__ __launch_bounds__(BIG_T) void ps_big_rows_fwd(const double* __restric
             for (int e = 0; e < E; ++e) {
                 const int j = tid + e * T + s * M;
                 if (j < ncols) {
-                    double a = 0.0, b = 0.0;
-                    if constexpr (MODE == 0) {
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            a += wa[t] * ua[(size_t)t * ldu + j];
-                            b += wb[t] * ub[(size_t)t * ldu + j];
-                        }
-                    } else {
-                        a = ua[j];
-                        b = wb[0] * ub[j];
-                    }
+                    const double a = ua[j], b = wb * ub[j];
                     y1[e].x += a * w1.x - b * w1.y;
                     y1[e].y += a * w1.y + b * w1.x;
                     y2[e].x += a * w2.x - b * w2.y;
@@ -153,12 +142,43 @@ __global__ __launch_bounds__(BIG_T) void ps_big_rows_fwd(const double* __restric
     }
 }
 
-// Column k2 (length L over the first n_in rows, zero padded).  MODE 0: forward
-// transform, product with the stored spectrum, inverse, the first n_out entries
-// back into X.  MODE 1 (plan time): spec_out column = conj(forward) * scale in
-// the (r, q) order.
+// T^out of a length-n_out sequence held as acc[s][e] = element tid + e T + s M:
+// put(m, y_m) for every grid node m.  Windows [wlo, whi) of the sequence go
+// through LDS, overlapping by 3; node m is done in the window with
+// wlo <= s_m <= whi - 4 (exactly one: the next starts at whi - 3).
+template <int M, int SO, typename Put>
+__device__ __forceinline__ void big_windows(const double2 (&acc)[SO][M / BIG_T], double2* lds, const PsOps& o,
+                                            Put&& put) {
+    constexpr int E = M / BIG_T, T = BIG_T, WIN = lds_slots(M);
+    const int tid = threadIdx.x;
+    for (int wlo = 0;;) {
+        const int whi = min(o.n_out, wlo + WIN);
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < SO; ++s)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int j = tid + e * T + s * M;
+                if (j >= wlo && j < whi) lds[j - wlo] = acc[s][e];
+            }
+        __syncthreads();
+        for (int q = tid; q < o.n; q += T) {
+            const int sq = o.tout_s[q];
+            if (sq >= wlo && sq <= whi - 4) put(q, ps_interp(lds, o.tout_s, o.tout_w, q, wlo));
+        }
+        if (whi >= o.n_out) break;
+        wlo = whi - 3;
+    }
+}
+
+// Column k2.  MODE 0: the axis-1 interpolation T^in of its n values (o; n_nz
+// values, zero padded to L), forward transform, product with the stored
+// spectrum, inverse, and the axis-1 T^out of the n_out kept values through LDS
+// windows, n values to Xo.  MODE 1 (plan time): spec_out column = conj(forward
+// of the first n_in values) * scale in the (r, q) order.
 template <int M, int R, int SO, int MODE>
-__global__ __launch_bounds__(BIG_T) void ps_big_cols(double2* __restrict__ X, int ldx, int n_in, int n_out,
+__global__ __launch_bounds__(BIG_T) void ps_big_cols(const double2* __restrict__ X, int ldx, int n_in,
+                                                             double2* __restrict__ Xo, PsOps o,
                                                              const double2* __restrict__ spec,
                                                              double2* __restrict__ spec_out, double scale,
                                                              const double2* __restrict__ twL,
@@ -171,7 +191,7 @@ __global__ __launch_bounds__(BIG_T) void ps_big_cols(double2* __restrict__ X, in
     load_twiddles<M, E>(twM, tw4);
     const int col = blockIdx.x;
     const int tid = threadIdx.x;
-    double2* xc = X + (size_t)col * ldx;
+    const double2* xc = X + (size_t)col * ldx;
     double2 acc[MODE == 0 ? SO : 1][E];
     if constexpr (MODE == 0) {
 #pragma unroll
@@ -191,7 +211,10 @@ __global__ __launch_bounds__(BIG_T) void ps_big_cols(double2* __restrict__ X, in
             for (int e = 0; e < E; ++e) {
                 const int j = tid + e * T + s * M;
                 if (j < n_in) {
-                    const double2 v = cmul(xc[j], w);
+                    double2 z;
+                    if constexpr (MODE == 0) z = ps_interp(xc, o.tin_s, o.tin_w, j, 0);
+                    else z = xc[j];
+                    const double2 v = cmul(z, w);
                     reg[e].x += v.x;
                     reg[e].y += v.y;
                 }
@@ -226,35 +249,28 @@ __global__ __launch_bounds__(BIG_T) void ps_big_cols(double2* __restrict__ X, in
         }
     }
     if constexpr (MODE == 0) {
-        __syncthreads();                                  // every read of the column is done
-#pragma unroll
-        for (int s = 0; s < SO; ++s)
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int j = tid + e * T + s * M;
-                if (j < n_out) xc[j] = acc[s][e];
-            }
+        double2* oc = Xo + (size_t)col * ldx;
+        big_windows<M, SO>(acc, lds, o, [&](int q, double2 y) { oc[q] = y; });
     }
 }
 
-// y^out rows (2p, 2p+1): the inverse length-L transform of A + i B (Hermitian
+// Grid rows (2p, 2p+1): the inverse length-L transform of A + i B (Hermitian
 // completion of the half spectra), then the axis-2 T^out gather through LDS
-// windows of the inverse row: Z[row][m] = sum_t T^out_{m, s_m + t} row[s_m + t].
+// windows of the inverse row: BV[row][m] = sum_t T^out_{m, s_m + t} row[s_m + t].
 template <int M, int R, int SO>
-__global__ __launch_bounds__(BIG_T) void ps_big_rows_inv(const double2* __restrict__ X, double* __restrict__ Z,
+__global__ __launch_bounds__(BIG_T) void ps_big_rows_inv(const double2* __restrict__ X, double* __restrict__ BV,
                                                                  PsOps o, const double2* __restrict__ twL,
                                                                  const double2* __restrict__ twM, const PsCtl* ctl,
                                                                  int k, double tol) {
     if (ps_halted(ctl, k, tol)) return;
     constexpr int E = M / BIG_T, T = BIG_T, L = R * M;
-    constexpr int WIN = lds_slots(M);
     __shared__ double2 lds[lds_slots(M)];
     __shared__ double2 tw4[tw_slots<M, E>()];
     load_twiddles<M, E>(twM, tw4);
-    const int m_out = o.n_out, np = (m_out + 1) >> 1;
+    const int n = o.n, np = (n + 1) >> 1;
     const int p = xcd_remap(blockIdx.x, np);
     const int ra = 2 * p, rb = 2 * p + 1;
-    const bool hasb = rb < m_out;
+    const bool hasb = rb < n;
     const int tid = threadIdx.x;
     double2 acc[SO][E];
 #pragma unroll
@@ -293,31 +309,10 @@ __global__ __launch_bounds__(BIG_T) void ps_big_rows_inv(const double2* __restri
             }
         }
     }
-    // windows [wlo, whi) of the inverse row, overlapping by 3; node m is done in
-    // the window with wlo <= s_m <= whi - 4 (exactly one: the next starts at whi - 3)
-    const int n = o.n;
-    for (int wlo = 0;;) {
-        const int whi = min(m_out, wlo + WIN);
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < SO; ++s)
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int j = tid + e * T + s * M;
-                if (j >= wlo && j < whi) lds[j - wlo] = acc[s][e];
-            }
-        __syncthreads();
-        for (int q = tid; q < n; q += T) {
-            const int sq = o.tout_s[q];
-            if (sq < wlo || sq > whi - 4) continue;
-            const double* w = o.tout_w + 4 * q;
-            const double2* v = lds + (sq - wlo);
-            Z[(size_t)ra * n + q] = w[0] * v[0].x + w[1] * v[1].x + w[2] * v[2].x + w[3] * v[3].x;
-            if (hasb) Z[(size_t)rb * n + q] = w[0] * v[0].y + w[1] * v[1].y + w[2] * v[2].y + w[3] * v[3].y;
-        }
-        if (whi >= m_out) break;
-        wlo = whi - 3;
-    }
+    big_windows<M, SO>(acc, lds, o, [&](int q, double2 y) {
+        BV[(size_t)ra * n + q] = y.x;
+        if (hasb) BV[(size_t)rb * n + q] = y.y;
+    });
 }
 
 }  // namespace ps

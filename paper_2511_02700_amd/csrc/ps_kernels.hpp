@@ -1,24 +1,34 @@
 // Device kernels of the price-space march (Sec. 3.2, Sec. 3.3, Sec. 4
 // settings; gfx950).  Grids are row-major n x n, V[i * n + j] at (x_i, x_j).
 //
-// B_omega v = T^out I~ C T^in v is four passes:
-//   tin2     : U = v (T^in)^T, the axis-2 interpolation to the y^in nodes
-//              inside [0, x_max] (n x n_nz; the rows of T^in beyond x_max are
-//              zero, so those nodes are the zero padding of the transform);
-//   rows_fwd : per pair of y^in rows, the axis-1 interpolation (four rows of
-//              U), one complex length-L FFT, the two half spectra stored
-//              transposed, X[k2 * ldx + i];
-//   cols     : per column k2: FFT over i, times the stored spectrum
-//              conj(FFT(omega placed at j mod L)) / L^2, inverse FFT, the
-//              first n_out entries kept (the rows I~ keeps);
-//   rows_inv : per pair of y^out rows: inverse FFT and the axis-2 T^out
-//              gather from LDS, Z = (C T^in v on y^out x y^out) (T^out)^T,
-//              n_out x n.
-// The axis-1 T^out gather, B v = T^out Z, is taken inside the kernel that
-// uses it (the residual, the explicit part, the stand-alone product).
+// B_omega v = T^out I~ C T^in v is three passes.  The interpolations of an axis
+// commute with the transforms of the other, so each pass interpolates its own
+// axis only and the row passes transform the n grid rows, not the n_nz rows of
+// v^in or the n_out rows of y^out (19 and 17 times as many at N_x = 800, NIG1:
+// the row passes took 3.9 and 2.7 ms there and take 0.1 ms each).  What is left
+// is the column pass, bound by its transforms (at 4096 and n = 401, 69 us: 33
+// the transforms, 9 the interpolation, 9 the spectrum, 14 the rest):
+//   rows_fwd : per pair of grid rows, the axis-2 interpolation T^in (from the
+//              rows in LDS; y^in nodes beyond x_max are the zero padding), one
+//              complex FFT, the two half spectra stored transposed, X[k2 * ldx + i];
+//   cols     : per column k2: the axis-1 interpolation T^in of the n values,
+//              FFT, times the stored spectrum conj(FFT(omega placed at j mod L)) / L^2,
+//              inverse FFT, and the axis-1 interpolation T^out of the rows I~
+//              keeps, n values to Xo[k2 * ldx + i];
+//   rows_inv : per pair of grid rows: inverse FFT and the axis-2 T^out gather
+//              from LDS: B v, n x n.
+// The output axis may be cut into nb tiles (overlap-save): tile b holds the
+// y^out nodes [b vs, b vs + v) and its transform, of length L = v + 2 N_z - 1,
+// reads the y^in nodes [b vs, b vs + L).  Tiles overlap by the three nodes a
+// T^out stencil needs (v = vs + 3), so that each grid node m has its stencil in
+// one tile: the nodes mlo[b] <= m < mlo[b + 1].  Both axes are cut alike; X and
+// Xo hold nb tiles of (L/2 + 1) x n.  nb = 1: one transform of L >= #in.  Above
+// 8192 tiles replace transforms that no workgroup holds: the tiles of a column
+// share its spectrum column in L2 (537 MB of spectrum at 8192 instead of 4.8 GB
+// at 24576), and the column pass of NIG1 at N_x = 800 took 7.3 ms, now 2.6.
 //
 // One fixed-point iteration of a step (c = dt theta) is
-//   tin2, rows_fwd, cols, rows_inv on Y (B Y),
+//   rows_fwd, cols, rows_inv on Y (B Y),
 //   resid_rows: R = W - (I - c (D + B - r_omega)) Y on each grid row, then
 //               the axis-2 solve Q = T_2^{-1} R,
 //   line_cols : the axis-1 solve delta = T_1^{-1} Q, Y += delta and the
@@ -41,9 +51,12 @@ namespace ps {
 
 constexpr int PS_MAXK = 128;   // iterations per step the control block can record
 
-// FFT elements per thread of the price-space transforms: 16 above 4096 (one
-// workgroup of 384 or 512 threads, 104 or 148 KB of LDS at 6144 and 8192).
-constexpr int ps_e(int L) { return L > 4096 ? 16 : conv_e(L); }
+// FFT elements per thread of the price-space transforms: 4 at 3072, else 8 (4
+// where 8 is not allowed; 16 at 7168, where 8 spills).  Column pass at n = 401,
+// one tile, with 4, 8, 16: 50, 72, 56 us at 3072; -, 132, 182 at 4608; -, 151,
+// 179 at 5120; -, 215, 237 at 6144; -, 367, 320 at 7168; -, 361, 394 at 8192 (one
+// workgroup per CU above 4096: 8 gives it twice the waves).
+constexpr int ps_e(int L) { return L == 3072 ? 4 : (L == 7168 ? 16 : conv_e(L)); }
 
 // Control block of a price-space march.
 struct PsCtl {
@@ -56,6 +69,8 @@ struct PsCtl {
 // Spatial operator tables (device pointers) and the coefficients of D.
 struct PsOps {
     int n, n_nz, n_out, ldx;
+    int nb, vs, v;           // tiles per axis, their advance and their kept y^out nodes
+    const int* mlo;          // nb + 1: first grid node of each tile
     const int* tin_s;        // n_nz rows of T^in: stencil start and 4 weights
     const double* tin_w;
     const int* tout_s;       // n rows of T^out (from the n_out nodes of y^out)
@@ -104,31 +119,22 @@ __device__ __forceinline__ double ps_DY(const double* __restrict__ Y, const PsOp
     return d;
 }
 
-// (B Y)(i, j) = sum_t T^out_{i, s_i + t} Z[s_i + t][j].
-__device__ __forceinline__ double ps_BY(const double* __restrict__ Z, const PsOps& o, int i, int j) {
-    const int s = o.tout_s[i];
-    const double* w = o.tout_w + 4 * i;
-    const double* z = Z + (size_t)s * o.n + j;
-    return w[0] * z[0] + w[1] * z[o.n] + w[2] * z[2 * o.n] + w[3] * z[3 * o.n];
+// sum_t w_t v[s + t] for row q of an interpolation table (start s, four weights).
+__device__ __forceinline__ double2 ps_interp(const double2* v, const int* __restrict__ st, const double* __restrict__ wt,
+                                             int q, int off) {
+    const double2* w2 = reinterpret_cast<const double2*>(wt) + 2 * (size_t)q;
+    const double2* r = v + (st[q] - off);
+    const double2 a = w2[0], b = w2[1];
+    const double2 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
+    return make_double2(a.x * r0.x + a.y * r1.x + b.x * r2.x + b.y * r3.x,
+                        a.x * r0.y + a.y * r1.y + b.x * r2.y + b.y * r3.y);
 }
 
-// U[row][q] = sum_t T^in_{q, s_q + t} Y[row][s_q + t]; grid (ceil(n_nz / 256), n).
-static __global__ __launch_bounds__(256) void ps_tin2(const double* __restrict__ Y, double* __restrict__ U, PsOps o,
-                                                      const PsCtl* ctl, int k, double tol) {
-    if (ps_halted(ctl, k, tol)) return;
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= o.n_nz) return;
-    const int row = blockIdx.y;
-    const int s = o.tin_s[q];
-    const double* w = o.tin_w + 4 * q;
-    const double* y = Y + (size_t)row * o.n + s;
-    U[(size_t)row * o.n_nz + q] = w[0] * y[0] + w[1] * y[1] + w[2] * y[2] + w[3] * y[3];
-}
-
-// Rows (2p, 2p+1) of v^in = T^in U (four rows of U each, zero beyond n_nz
-// columns), one complex FFT, the half spectra into X[k2 * ldx + row].
+// Grid rows (2p, 2p+1), tile blockIdx.y: the axis-2 interpolation from the rows
+// in LDS (as one complex row a + i b, n <= L), one complex FFT, the half
+// spectra into X[k2 * ldx + row].
 template <int L>
-__global__ __launch_bounds__(L / ps_e(L)) void ps_rows_fwd(const double* __restrict__ U, double2* __restrict__ X,
+__global__ __launch_bounds__(L / ps_e(L)) void ps_rows_fwd(const double* __restrict__ V, double2* __restrict__ X,
                                                              PsOps o, const double2* __restrict__ tw,
                                                              const PsCtl* ctl, int k, double tol) {
     if (ps_halted(ctl, k, tol)) return;
@@ -136,39 +142,27 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_rows_fwd(const double* __restr
     __shared__ double2 lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, KE>()];
     load_twiddles<L, KE>(tw, tw4);
-    const int m = o.n_nz, np = (m + 1) >> 1;
+    const int n = o.n, np = (n + 1) >> 1;
     const int p = xcd_remap(blockIdx.x, np);
     const int ra = 2 * p, rb = 2 * p + 1;
-    const bool hasb = rb < m;
-    const int sa = o.tin_s[ra], sb = o.tin_s[hasb ? rb : ra];
-    double wa[4], wb[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        wa[t] = o.tin_w[4 * ra + t];
-        wb[t] = hasb ? o.tin_w[4 * rb + t] : 0.0;
-    }
-    const double* ua = U + (size_t)sa * m;
-    const double* ub = U + (size_t)sb * m;
+    const bool hasb = rb < n;
     const int tid = threadIdx.x;
+    for (int j = tid; j < n; j += T)
+        lds[j] = make_double2(V[(size_t)ra * n + j], hasb ? V[(size_t)rb * n + j] : 0.0);
+    __syncthreads();
+    const int i0 = blockIdx.y * o.vs;
     double2 reg[KE];
 #pragma unroll
     for (int e = 0; e < KE; ++e) {
-        const int idx = tid + e * T;
-        double a = 0.0, b = 0.0;
-        if (idx < m) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                a += wa[t] * ua[(size_t)t * m + idx];
-                b += wb[t] * ub[(size_t)t * m + idx];
-            }
-        }
-        reg[e] = make_double2(a, b);
+        const int i = i0 + tid + e * T;
+        reg[e] = i < o.n_nz ? ps_interp(lds, o.tin_s, o.tin_w, i, 0) : make_double2(0.0, 0.0);
     }
     fft_block<L, KE, false>(reg, lds, tw4);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < KE; ++e) lds[tid + e * T] = reg[e];
     __syncthreads();
+    X += (size_t)blockIdx.y * (L / 2 + 1) * o.ldx;
     // Z = FFT(a + i b): A_k = (Z_k + conj Z_{L-k}) / 2, B_k = (Z_k - conj Z_{L-k}) / (2i).
     // Item idx is frequency idx / 2 of row ra + idx mod 2: the two rows of a
     // frequency are adjacent in X, so a lane pair stores them as one 32-byte piece.
@@ -184,33 +178,39 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_rows_fwd(const double* __restr
     }
 }
 
-// Column k2: FFT over the n_nz rows (zero padded to L), times the spectrum,
-// inverse FFT, the first n_out entries back into X.  L/2 blocks for the L/2 + 1
-// columns: block 0 filters the two real columns 0 and L/2 as one complex column
-// (mul_real_pair; the row inverse reads only their real parts).
+// One column k2 of one tile pair (b1 along axis 1, b2 along axis 2); L/2 nb^2
+// blocks for the L/2 + 1 columns: column 0 stands for the two real columns 0
+// and L/2, filtered as one complex column (mul_real_pair; the row inverse reads
+// only their real parts).  The tile pairs of a column follow each other on one
+// XCD, whose L2 then serves the spectrum column that they share.
 template <int L>
-__global__ __launch_bounds__(L / ps_e(L)) void ps_cols(double2* __restrict__ X, const double2* __restrict__ spec,
-                                                         PsOps o, const double2* __restrict__ tw, const PsCtl* ctl,
-                                                         int k, double tol) {
+__global__ __launch_bounds__(L / ps_e(L)) void ps_cols(const double2* __restrict__ X, double2* __restrict__ Xo,
+                                                         const double2* __restrict__ spec, PsOps o,
+                                                         const double2* __restrict__ tw, const PsCtl* ctl, int k,
+                                                         double tol) {
     if (ps_halted(ctl, k, tol)) return;
     constexpr int KE = ps_e(L), T = L / KE;
     __shared__ double2 lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, KE>()];
     load_twiddles<L, KE>(tw, tw4);
-    const int col = blockIdx.x;
-    const int tid = threadIdx.x;
+    const int nt = o.nb * o.nb, g = blockIdx.x >> 3;
+    const int col = (g / nt) * 8 + (blockIdx.x & 7), b1 = (g % nt) / o.nb, b2 = (g % nt) % o.nb;
+    const int tid = threadIdx.x, n = o.n;
     const bool pair = col == 0;
-    double2* xc = X + (size_t)col * o.ldx;
-    double2* xn = X + (size_t)(L / 2) * o.ldx;
+    const size_t tile = (size_t)b2 * (L / 2 + 1);
+    const double2* xc = X + (tile + col) * o.ldx;
+    const double2* xn = X + (tile + L / 2) * o.ldx;
+    for (int j = tid; j < n; j += T) lds[j] = pair ? make_double2(xc[j].x, xn[j].x) : xc[j];
+    __syncthreads();
+    const int i0 = b1 * o.vs;
+    const double2* sc = spec + (size_t)col * L;
     double2 reg[KE];
 #pragma unroll
     for (int e = 0; e < KE; ++e) {
-        const int idx = tid + e * T;
-        if (idx < o.n_nz) reg[e] = pair ? make_double2(xc[idx].x, xn[idx].x) : xc[idx];
-        else reg[e] = make_double2(0.0, 0.0);
+        const int i = i0 + tid + e * T;
+        reg[e] = i < o.n_nz ? ps_interp(lds, o.tin_s, o.tin_w, i, 0) : make_double2(0.0, 0.0);
     }
     fft_block<L, KE, false>(reg, lds, tw4);
-    const double2* sc = spec + (size_t)col * L;
     if (pair) {
         mul_real_pair<L, KE, false>(reg, lds, sc, spec + (size_t)(L / 2) * L);
     } else {
@@ -218,24 +218,33 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_cols(double2* __restrict__ X, 
         for (int e = 0; e < KE; ++e) reg[e] = cmul(reg[e], sc[tid + e * T]);
     }
     fft_block<L, KE, true>(reg, lds, tw4);
+    __syncthreads();
+    const int kept = min(o.v, o.n_out - i0);
 #pragma unroll
     for (int e = 0; e < KE; ++e) {
         const int idx = tid + e * T;
-        if (idx >= o.n_out) continue;
+        if (idx < kept) lds[idx] = reg[e];
+    }
+    __syncthreads();
+    double2* oc = Xo + (tile + col) * o.ldx;
+    double2* on = Xo + (tile + L / 2) * o.ldx;
+    const int m1 = o.mlo[b1 + 1];
+    for (int q = o.mlo[b1] + tid; q < m1; q += T) {
+        const double2 y = ps_interp(lds, o.tout_s, o.tout_w, q, i0);
         if (pair) {
-            xc[idx] = make_double2(reg[e].x, 0.0);
-            xn[idx] = make_double2(reg[e].y, 0.0);
+            oc[q] = make_double2(y.x, 0.0);
+            on[q] = make_double2(y.y, 0.0);
         } else {
-            xc[idx] = reg[e];
+            oc[q] = y;
         }
     }
 }
 
-// y^out rows (2p, 2p+1): Hermitian completion of the two half spectra, inverse
-// FFT, the n_out kept columns staged in LDS, then the axis-2 T^out gather:
-// Z[row][m] = sum_t T^out_{m, s_m + t} row[s_m + t], m < n.
+// Grid rows (2p, 2p+1), tile blockIdx.y: Hermitian completion of the two half
+// spectra, inverse FFT, the kept y^out columns staged in LDS, then the axis-2
+// T^out gather: BV[row][m] = sum_t T^out_{m, s_m + t} row[s_m + t] for the tile's m.
 template <int L>
-__global__ __launch_bounds__(L / ps_e(L)) void ps_rows_inv(const double2* __restrict__ X, double* __restrict__ Z,
+__global__ __launch_bounds__(L / ps_e(L)) void ps_rows_inv(const double2* __restrict__ X, double* __restrict__ BV,
                                                              PsOps o, const double2* __restrict__ tw,
                                                              const PsCtl* ctl, int k, double tol) {
     if (ps_halted(ctl, k, tol)) return;
@@ -243,11 +252,12 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_rows_inv(const double2* __rest
     __shared__ double2 lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, KE>()];
     load_twiddles<L, KE>(tw, tw4);
-    const int m = o.n_out, np = (m + 1) >> 1;
+    const int n = o.n, np = (n + 1) >> 1;
     const int p = xcd_remap(blockIdx.x, np);
     const int ra = 2 * p, rb = 2 * p + 1;
-    const bool hasb = rb < m;
+    const bool hasb = rb < n;
     const int tid = threadIdx.x;
+    X += (size_t)blockIdx.y * (L / 2 + 1) * o.ldx;
     // Z_k = A_k + i B_k for k <= L/2 and Z_{L-k} = conj A_k + i conj B_k (imaginary
     // parts dropped at DC and Nyquist).  Item idx is frequency idx / 2 of row
     // ra + idx mod 2: a lane pair reads the 32 contiguous bytes of one frequency
@@ -275,35 +285,29 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_rows_inv(const double2* __rest
     for (int e = 0; e < KE; ++e) reg[e] = lds[lds_slot(tid + e * T)];
     fft_block<L, KE, true>(reg, lds, tw4);
     __syncthreads();
-    double* rows = reinterpret_cast<double*>(lds);       // row a at [0, L), row b at [L, 2L)
+    const int i0 = blockIdx.y * o.vs, kept = min(o.v, o.n_out - i0);
 #pragma unroll
     for (int e = 0; e < KE; ++e) {
-        const int j = tid + e * T;
-        if (j < m) {
-            rows[j] = reg[e].x;
-            rows[L + j] = reg[e].y;
-        }
+        const int idx = tid + e * T;
+        if (idx < kept) lds[idx] = reg[e];
     }
     __syncthreads();
-    const int n = o.n;
-    for (int q = tid; q < n; q += T) {
-        const int s = o.tout_s[q];
-        const double* w = o.tout_w + 4 * q;
-        Z[(size_t)ra * n + q] = w[0] * rows[s] + w[1] * rows[s + 1] + w[2] * rows[s + 2] + w[3] * rows[s + 3];
-        if (hasb)
-            Z[(size_t)rb * n + q] =
-                w[0] * rows[L + s] + w[1] * rows[L + s + 1] + w[2] * rows[L + s + 2] + w[3] * rows[L + s + 3];
+    const int m1 = o.mlo[blockIdx.y + 1];
+    for (int q = o.mlo[blockIdx.y] + tid; q < m1; q += T) {
+        const double2 y = ps_interp(lds, o.tout_s, o.tout_w, q, i0);
+        BV[(size_t)ra * n + q] = y.x;
+        if (hasb) BV[(size_t)rb * n + q] = y.y;
     }
 }
 
 // Residual of the step equation on grid rows and the axis-2 solve:
 // Q = T_2^{-1} (W - Y + c (D Y + B Y - r_omega Y)).  256 threads: 256 / P rows
-// per block, P chunks per row (P a power of two, n <= MM P).  Z = nullptr:
+// per block, P chunks per row (P a power of two, n <= MM P).  BV = nullptr:
 // no jumps (B = 0).
 template <int MM>
 __global__ __launch_bounds__(256) void ps_resid_rows(const double* __restrict__ Y,
                                                             const double* __restrict__ W,
-                                                            const double* __restrict__ Z, double* __restrict__ Q,
+                                                            const double* __restrict__ BV, double* __restrict__ Q,
                                                             PsOps o, PsStepK sk, int P, const PsCtl* ctl, int k,
                                                             double tol) {
     if (ps_halted(ctl, k, tol)) return;
@@ -322,7 +326,7 @@ __global__ __launch_bounds__(256) void ps_resid_rows(const double* __restrict__ 
             const int j = s + q;
             const size_t o_ = (size_t)i * n + j;
             const double y = Y[o_];
-            const double by = Z ? ps_BY(Z, o, i, j) : 0.0;
+            const double by = BV ? BV[o_] : 0.0;
             x[q] = W[o_] - y + sk.c * (ps_DY(Y, o, i, j) + by - o.r_omega * y);
         }
     }
@@ -582,7 +586,7 @@ static __global__ __launch_bounds__(PS_AA_T) void ps_aa_update(double* __restric
 }
 
 // Explicit part E = V + d (D V + B V - r_omega V), d = dt (1 - theta).
-static __global__ __launch_bounds__(256) void ps_expl(const double* __restrict__ V, const double* __restrict__ Z,
+static __global__ __launch_bounds__(256) void ps_expl(const double* __restrict__ V, const double* __restrict__ BV,
                                                       double* __restrict__ E, PsOps o, double d,
                                                       const PsCtl* ctl) {
     if (ctl && ctl->fail) return;
@@ -591,7 +595,7 @@ static __global__ __launch_bounds__(256) void ps_expl(const double* __restrict__
     if (idx >= (size_t)n * n) return;
     const int i = int(idx / n), j = int(idx % n);
     const double v = V[idx];
-    const double bv = Z ? ps_BY(Z, o, i, j) : 0.0;
+    const double bv = BV ? BV[idx] : 0.0;
     E[idx] = v + d * (ps_DY(V, o, i, j) + bv - o.r_omega * v);
 }
 
@@ -668,15 +672,6 @@ static __global__ void ps_ctl_reset(PsCtl* ctl, int clear_err) {
         for (int k = 0; k < PS_MAXK + 2; ++k) ctl->err[k] = 0ull;
         ctl->last = 0ull;
     }
-}
-
-// Stand-alone product: bv = T^out Z (axis 1).
-static __global__ __launch_bounds__(256) void ps_tout1(const double* __restrict__ Z, double* __restrict__ bv,
-                                                       PsOps o) {
-    const int n = o.n;
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (size_t)n * n) return;
-    bv[idx] = ps_BY(Z, o, int(idx / n), int(idx % n));
 }
 
 static __global__ __launch_bounds__(256) void ps_fill(double* __restrict__ a, size_t cnt, double v) {

@@ -10,13 +10,15 @@
 namespace lpide {
 namespace ps {
 
-// What the four correlation passes of B_omega need.
+// What the three correlation passes of B_omega need (L: the side of one tile's
+// transform).
 struct PsConv {
     hipStream_t stream = nullptr;
     PsOps o{};
-    double* U = nullptr;            // n x n_nz
-    double2* X = nullptr;           // (L/2 + 1) x ldx
-    double* Z = nullptr;            // n_out x n
+    double* U = nullptr;            // sides above 8192: n x n_nz
+    double2* X = nullptr;           // nb tiles of (L/2 + 1) x ldx: row spectra
+    double2* Xo = nullptr;          // the same: filtered columns
+    double* BV = nullptr;           // n x n: B v
     const double2* spec = nullptr;  // (L/2 + 1) x L
     const double2* tw = nullptr;    // L twiddles exp(-2 pi i q / L)
     const double2* twM = nullptr;   // sides above 8192: the twiddles of the inner transforms (length 4096 or 8192)
@@ -26,7 +28,7 @@ struct PsConv {
 
 template <int L>
 struct PsL {
-    // Z = (C T^in Y restricted to y^out) (T^out)^T for iteration k (k = 0: always runs).
+    // BV = T^out I~ C T^in Y for iteration k (k = 0: always runs).
     static void bapply(const PsConv& c, const double* Y, int k);
     // spec = conj(FFT2(G)) / L^2 of the L x L real grid G that holds the W2 x W2
     // weights W (row-major) in its corner [0, W2)^2 and zeros elsewhere (Xf:
