@@ -82,8 +82,10 @@ def algorithmic_bytes(cls, n, L, mixed=False):
         # FP64 iteration 1 by linearity: read 4 stored products (3 in the steps just
         # after the damping), W and Y; write R and the stored B Y^0
         "rows_lin": 8 * 8 * n * n,
-        # SL without the row transform: read E, four history grids; write W and Y^0
-        "sl_lin": 7 * 8 * n * n,
+        # step begin without transforms (explicit part, SL, start value and iteration 1 in
+        # one): read the previous W, four history grids, four stored products; write W,
+        # Y^0, B Y^0 and R
+        "sl_lin": 13 * 8 * n * n,
     }[cls]
 
 
@@ -115,8 +117,8 @@ def kernel_symbol(cls, L, mixed, sl_order, radix=(8, 8, 8, 8), n=None):
         "rows_fwd": "lpide::ks_rows_fwd<%d, %d>" % (L, er),
         "carry": "lpide::ks_carry",
         "expl_id": "lpide::ks_expl_identity",
-        "rows_lin": "lpide::ks_rows_lin",
-        "sl_lin": "lpide::ks_sl_lin<%d>" % sl_order,
+        "rows_lin": "lpide::ks_begin_lin<%d" % sl_order,
+        "sl_lin": "lpide::ks_begin_lin<%d" % sl_order,
     }[cls]
 
 

@@ -67,24 +67,18 @@ __device__ __forceinline__ double apply_D(const double* __restrict__ U, const St
     return d;
 }
 
-// apply_D with all eight neighbours read at indices clamped into the grid
-// (the mixed term's nodes are those neighbours): every read valid and none
-// conditional, so that a node's reads are in flight together; the interior
-// tests select the arithmetic only (a zero a12 adds a zero mixed term).  For
-// row kernels with one element per thread and loop pass; kernels that unroll
-// many elements keep apply_D, whose branches throttle the reads in flight.
-__device__ __forceinline__ double apply_D_ahead(const double* __restrict__ U, const StencilArgs& s, int i, int j,
-                                                double u) {
+// D at (i, j) from the node's value u and its eight neighbours, read at indices
+// clamped into the grid (the mixed term's nodes are those neighbours): u1m, u1p
+// along axis 1, u2m, u2p along axis 2, u00 .. u11 the corners (first index axis
+// 1).  The interior tests select the arithmetic only (a zero a12 adds a zero
+// mixed term), so that none of a node's reads is conditional.  The row c2r
+// kernel, which unrolls many elements, keeps apply_D, whose branches throttle
+// the reads in flight.
+__device__ __forceinline__ double D_of(const StencilArgs& s, int i, int j, double u, double u1m, double u1p, double u2m,
+                                       double u2p, double u00, double u01, double u10, double u11) {
     const int n = s.n;
     const double ih2 = 1.0 / (s.h * s.h), i2h = 0.5 / s.h;
     const bool iin = i > 0 && i < n - 1, jin = j > 0 && j < n - 1;
-    const int im = i > 0 ? i - 1 : 0, ip = i < n - 1 ? i + 1 : n - 1;
-    const int jm = j > 0 ? j - 1 : 0, jp = j < n - 1 ? j + 1 : n - 1;
-    const double* rm = U + (size_t)im * n;
-    const double* rp = U + (size_t)ip * n;
-    const double u1m = rm[j], u1p = rp[j];
-    const double u2m = U[(size_t)i * n + jm], u2p = U[(size_t)i * n + jp];
-    const double u00 = rm[jm], u01 = rm[jp], u10 = rp[jm], u11 = rp[jp];
     double d = 0.0;
     if (iin) d += 0.5 * s.a11 * ((u1p - 2.0 * u + u1m) * ih2 - (u1p - u1m) * i2h);
     if (jin) d += 0.5 * s.a22 * ((u2p - 2.0 * u + u2m) * ih2 - (u2p - u2m) * i2h);

@@ -87,6 +87,26 @@ bool KTime::events(hipEvent_t* a, hipEvent_t* b) {
     return true;
 }
 
+constexpr int kBeginClasses[3] = {LPIDE_K_SL_LIN, LPIDE_K_ROWS_LIN, LPIDE_K_EXPL_ID};
+
+KBegin::KBegin(Plan* pl) : KTime(pl, LPIDE_K_SL_LIN) {
+    for (int c : kBeginClasses) on = on || (pl && ((pl->time_mask >> c) & 1u));
+}
+
+bool KBegin::events(hipEvent_t* a, hipEvent_t* b) {
+    const size_t idx = p->ev_used;
+    *a = next_event(p);
+    *b = next_event(p);
+    if (!*a || !*b) return false;
+    bool first = true;
+    for (int c : kBeginClasses) {
+        if (!((p->time_mask >> c) & 1u)) continue;
+        p->ev_recs.push_back({c, idx, p->tag_step, c == LPIDE_K_ROWS_LIN ? 1 : 0, true, first});
+        first = false;
+    }
+    return true;
+}
+
 }  // namespace detail
 }  // namespace lpide
 
@@ -290,13 +310,14 @@ int harvest_times(Plan* p) {
                 (r.cls == LPIDE_K_EXPL_ID && (anchor || !ident)))
                 continue;
         }
+        // a step either starts with ks_begin_lin or with the kernels it replaces
+        if (known && r.begin && !lin[r.step]) continue;
+        if (known && !r.begin && r.cls == LPIDE_K_EXPL_ID && !p->mixed && lin[r.step]) continue;
         if (known && r.k == 1) {            // iteration 1: B Y^0 by linearity or by the correlation
             if (lin[r.step] && (r.cls == LPIDE_K_COLS || r.cls == LPIDE_K_ROWS_INV)) continue;
-            if (!lin[r.step] && r.cls == LPIDE_K_ROWS_LIN) continue;
         }
         if (known && r.k == 0) {            // the SL kernel with the row transform, or without
             if (lin[r.step] && r.cls == LPIDE_K_SL && !p->mixed && p->jumps) continue;
-            if (!lin[r.step] && r.cls == LPIDE_K_SL_LIN) continue;
         }
         if (!p->mixed && known) {           // FP64: the explicit correlation or the identity kernel
             const bool ident = !p->opts.all_correlations && r.step > p->march_step0 && p->cn_rho[r.step] > 0.0;
@@ -304,9 +325,10 @@ int harvest_times(Plan* p) {
                 (r.cls == LPIDE_K_EXPL_ID && !ident))
                 continue;
         }
+        p->k_launch[r.cls] += 1;
+        if (!r.timed) continue;
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, p->ev_pool[r.idx], p->ev_pool[r.idx + 1]));
-        p->k_launch[r.cls] += 1;
         p->k_ms[r.cls] += ms;
     }
     p->ev_recs.clear();
@@ -364,7 +386,8 @@ MarchArgs march_args(const Plan* p) {
     a.n_sub = p->opts.damping ? 4 : 1;
     a.damping = p->opts.damping ? 1 : 0;
     a.P_cols = p->P_cols;
-    a.W = p->Wb;
+    a.Wb[0] = p->Wb[0];
+    a.Wb[1] = p->Wb[1];
     a.R = p->Rb;
     a.X = p->X;
     a.spec = p->spec;
@@ -952,7 +975,7 @@ int adj_prepare(Plan* p, int C) {
     m.pool[1] = a->lam;
     for (int b = 2; b < POOL; ++b) m.pool[b] = a->dummy;
     m.sets = a->sets_d;
-    m.W = a->ybar;
+    m.Wb[0] = m.Wb[1] = a->ybar;
     m.ctl = a->ctl;
     m.counts = a->counts;
     m.incs = a->incs;
@@ -1437,7 +1460,7 @@ int lpide_plan_create(const lpide_grid* grid, const lpide_levy* levy, const lpid
     if ((rc = upload(p, &p->V0, v0))) return bail(rc);
     for (int b = 0; b < POOL; ++b)
         if ((rc = dalloc(p, &p->pool[b], N))) return bail(rc);
-    if ((rc = dalloc(p, &p->Wb, N))) return bail(rc);
+    if ((rc = dalloc(p, &p->Wb[0], N)) || (rc = dalloc(p, &p->Wb[1], N))) return bail(rc);
     if ((rc = dalloc(p, &p->Rb, N))) return bail(rc);
     if (p->jumps && !p->mixed && !o.all_correlations)    // B of the pool grids, for B Y^0 by linearity
         for (int b = 0; b < POOL; ++b)

@@ -65,6 +65,14 @@ void with_line_cols(const Launch& c, Go&& go) {
     }
 }
 
+// Rows per tile of the step-begin kernel: 8 where tiles of 8 rows still fill the
+// chip, else 2 (more, shorter tiles).
+template <typename Go>
+void with_begin_rows(const Launch& c, Go&& go) {
+    if (begin_tiles(c.xaff, 8) * c.np >= BEGIN_FILL) go(std::integral_constant<int, 8>{});
+    else go(std::integral_constant<int, 2>{});
+}
+
 // The line-row kernel with E elements per thread and the smallest chunk
 // capacity (E, 3E/2 or 2E) that holds the longest chunk of the launch's plans.
 template <int L, int E, bool FFT, bool MIXED, typename Go>
@@ -80,8 +88,8 @@ template <int L, bool FFT, bool MIXED>
 void launch_iteration(const Launch& c, int k) {
     using C = typename std::conditional<MIXED, float2, double2>::type;
     if (c.timer) c.timer->tag_k = k;
-    // steady FP64 slots: iteration 1 is rows_lin alone (the column pass and the
-    // row c2r kernel would exit)
+    // steady FP64 slots: ks_begin_lin left iteration 1's residual (the column pass
+    // and the row c2r kernel would exit)
     const bool lean1 = FFT && !MIXED && c.lean && k == 1;
     if (FFT && !lean1) {
         {
@@ -99,10 +107,6 @@ void launch_iteration(const Launch& c, int k) {
                          k);
             });
         }
-    }
-    if (FFT && !MIXED && k == 1) {        // B Y^0 by linearity (the two above exit then)
-        KTime t(c.timer, LPIDE_K_ROWS_LIN);
-        t.launch(ks_rows_lin, dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A);
     }
     if (!FFT) {
         KTime t(c.timer, LPIDE_K_ROWS_INV);
@@ -137,6 +141,7 @@ void launch_step(const Launch& c, int kmax) {
     if (c.timer) c.timer->tag_k = 0;
     const dim3 gr(c.xrows, c.np), gc(L / 2, c.np);
     const bool lean = FFT && !MIXED && c.lean;
+    // steady slots start with ks_begin_lin alone
     if (FFT && !lean) {
         if (MIXED) {
             KTime t(c.timer, LPIDE_K_ROWS_FWD);
@@ -167,10 +172,7 @@ void launch_step(const Launch& c, int kmax) {
             KTime t(c.timer, LPIDE_K_EXPL_ID);
             t.launch(ks_expl_identity, dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A);
         }
-    } else if (lean) {                    // steady: the explicit part from the previous step's equation
-        KTime t(c.timer, LPIDE_K_EXPL_ID);
-        t.launch(ks_expl_identity, dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A);
-    } else {
+    } else if (!FFT) {
         KTime t(c.timer, LPIDE_K_EXPL_ROWS);
         t.launch((ks_affine_noB<true>), dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A, 0);
     }
@@ -185,12 +187,15 @@ void launch_step(const Launch& c, int kmax) {
         });
     }
     if (FFT && !MIXED) {                  // steps with B Y^0 by linearity (ks_sl exits in them)
-        KTime t(c.timer, LPIDE_K_SL_LIN);
-        const size_t shm = sizeof(double) * c.xaff;   // the combined source rows of the largest plan
-        if (c.sl_order == 1) t.launch(ks_sl_lin<1>, dim3(c.xaff, c.np), dim3(256), shm, c.stream, c.A);
-        else t.launch(ks_sl_lin<3>, dim3(c.xaff, c.np), dim3(256), shm, c.stream, c.A);
+        KBegin t(c.timer);
+        with_begin_rows(c, [&](auto tr) {
+            constexpr int TR = decltype(tr)::value;
+            const dim3 g(begin_tiles(c.xaff, TR), c.np);
+            if (c.sl_order == 1) t.launch(ks_begin_lin<1, TR>, g, dim3(BEGIN_T), 0, c.stream, c.A);
+            else t.launch(ks_begin_lin<3, TR>, g, dim3(BEGIN_T), 0, c.stream, c.A);
+        });
     }
-    if (c.record) hipLaunchKernelGGL(ks_store_E, dim3(c.store_blocks, c.np), dim3(256), 0, c.stream, c.A);
+    if (c.record && !lean) hipLaunchKernelGGL(ks_store_E, dim3(c.store_blocks, c.np), dim3(256), 0, c.stream, c.A);
     for (int k = 1; k <= kmax; ++k) launch_iteration<L, FFT, MIXED>(c, k);
     if (c.timer) c.timer->tag_k = 0;
     {

@@ -108,7 +108,7 @@ struct Plan {
     double* bpool[POOL] = {};      // B applied to the pool grids (FP64 form, B Y^0 by linearity)
     double* V0 = nullptr;
     double* pool[POOL] = {};
-    double* Wb = nullptr;
+    double* Wb[2] = {};            // SL outputs of a step and of the one before it
     double* Rb = nullptr;
     StepDesc* sets_d = nullptr;
     int* step_set_d = nullptr;
@@ -131,7 +131,7 @@ struct Plan {
     // kernel timing (HIP events on the plan's stream around each timed launch)
     uint32_t time_mask = 0;
     std::vector<hipEvent_t> ev_pool;
-    struct EvRec { int cls; size_t idx; int step, k; };
+    struct EvRec { int cls; size_t idx; int step, k; bool begin = false, timed = true; };
     std::vector<EvRec> ev_recs;   // timed launches: class, start event, step and iteration (k = 0: once per step)
     int tag_step = -1, tag_k = 0; // step/iteration of the launches being enqueued
     size_t ev_used = 0;
@@ -153,7 +153,7 @@ struct KTime {
     int cls;
     bool on;
     KTime(Plan* pl, int c);
-    bool events(hipEvent_t* a, hipEvent_t* b);   // a fresh pair, registered for harvest_times
+    virtual bool events(hipEvent_t* a, hipEvent_t* b);   // a fresh pair, registered for harvest_times
 
     template <typename... P, typename... Args>
     void launch(void (*kernel)(P...), const dim3& g, const dim3& b, uint32_t shm, hipStream_t s, Args... args) {
@@ -163,6 +163,14 @@ struct KTime {
         else
             hipLaunchKernelGGL(kernel, g, b, shm, s, static_cast<P>(args)...);
     }
+};
+
+// Timing of a step-begin launch, which does the work of three classes: it counts
+// for each of them that is timed, and its time goes to the first of SL_LIN,
+// ROWS_LIN and EXPL_ID among these.
+struct KBegin : KTime {
+    explicit KBegin(Plan* pl);
+    bool events(hipEvent_t* a, hipEvent_t* b) override;
 };
 
 // State of the adjoint march (allocated on the first lpide_adjoint call).
@@ -215,6 +223,9 @@ void with_E(int E, F&& f) {
     }
     f(std::integral_constant<int, 4>{});
 }
+
+// Tiles that fill the chip (256 CUs, four step-begin blocks each).
+constexpr int BEGIN_FILL = 1024;
 
 // Columns per block of the axis-1 line solves: 4 adjacent columns share cache
 // lines, but when the groups of 4 would leave CUs idle (fewer blocks than

@@ -2,7 +2,8 @@
 //
 // The host enqueues whole time steps without waiting: every step is
 //   [explicit part: cols + rows_inv(explicit)]        (theta < 1 only)
-//   sl        W = T^SL E, Y^0, and the row FFT of Y^0
+//   sl        W = T^SL E, Y^0, and the row FFT of Y^0 (begin_lin instead once
+//             B Y^0 comes by linearity: E, W, Y^0 and iteration 1's R in one)
 //   kmax x {  cols          column pass of B Y (spectrum multiply)
 //             rows_inv      R = W + dt theta ((D - r_omega) Y + B Y) - Y
 //             line_cols     R <- T_1^{-1} R                 (axis 1)
@@ -54,6 +55,7 @@ struct Ctl {
     int nsrc;                         // terms of the starting-value combination
     int hist[4];                      // pool indices, newest first
     int bvalid;                       // bit b: bpool[b] holds B applied to pool[b] (this march)
+    int w;                            // SL buffer of this step (the step before wrote the other one)
     int src[4];
     double coef[4];                   // Y^0 = sum_q coef[q] pool[src[q]]; past nsrc,
                                       // src[q] = src[0] and coef[q] = 0 (so a loop
@@ -86,7 +88,7 @@ struct MarchArgs {
     const StepDesc* sets;
     const int* step_set;
     int n, n_sub, damping, P_cols;
-    double* W;
+    double* Wb[2];                    // SL outputs W of this step and of the one before it (wcur, wprev)
     double* R;
     double2* X;
     const double2* spec;
@@ -167,7 +169,7 @@ __device__ __forceinline__ bool is_anchor(const MarchArgs& a) {
 
 // Explicit part of a step from the implicit equation of the step before it.
 // That step solved (I - c A) V^{n-1} = W (c = dt theta of that step, W still
-// in a.W), so A V^{n-1} = (V^{n-1} - W) / c and
+// in wprev), so A V^{n-1} = (V^{n-1} - W) / c and
 //   E = V^{n-1} + dt (1 - theta) A V^{n-1} = V^{n-1} + rho (V^{n-1} - W),
 // rho = dt (1 - theta) / c: the same explicit part without applying B, exact
 // at the fixed point (the converged iterate leaves the stopping-rule residual).
@@ -200,6 +202,14 @@ __device__ __forceinline__ bool start_by_linearity(const MarchArgs& a) {
 // B V^{n-1} in the mixed form.
 __device__ __forceinline__ bool needs_explicit_fft(const MarchArgs& a) {
     return a.mixed ? is_anchor(a) : (cur_set(a).theta < 1.0 && !explicit_by_identity(a));
+}
+
+// The SL output of this step, and that of the step before it; the latter takes
+// the explicit part E of a step whose E is formed by a kernel of its own
+// (the index made scalar: the pointer is then a scalar too).
+__device__ __forceinline__ double* wcur(const MarchArgs& a) { return a.Wb[__builtin_amdgcn_readfirstlane(a.ctl->w)]; }
+__device__ __forceinline__ double* wprev(const MarchArgs& a) {
+    return a.Wb[__builtin_amdgcn_readfirstlane(a.ctl->w) ^ 1];
 }
 
 // The plan of this block.
@@ -304,7 +314,7 @@ __device__ __forceinline__ void rows_inv_gather(C (&reg)[E], C* lds, const C* __
 }
 
 // Row inverse FFT of the pairs (2p, 2p+1) with a fused epilogue.
-// MODE 0 (once per step, FP64): E = V + dt(1-theta)((D - r_omega) V + B V) into R
+// MODE 0 (once per step, FP64): E = V + dt(1-theta)((D - r_omega) V + B V) into wprev
 //         (theta < 1), and B V into BV (mixed form);
 // MODE 1 (FP64 iteration):  R = W + dt theta((D - r_omega) Y + B Y) - Y;
 // MODE 2 (mixed iteration): B Y = (k == 1 in an anchor step ? BV : B Y) + B32(increment)
@@ -319,7 +329,7 @@ template <int L, int E, int MODE>
 __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict__ A, int k) {
     const MarchArgs& a = plan_args(A);
     if (halted(a, k) || ((MODE == 0 || MODE == 4) && !needs_explicit_fft(a)) ||
-        (MODE == 1 && k == 1 && start_by_linearity(a)))   // ks_rows_lin runs instead
+        (MODE == 1 && k == 1 && start_by_linearity(a)))   // ks_begin_lin ran instead
         return;
     using C = typename std::conditional<MODE == 2, float2, double2>::type;
     constexpr int T = L / E;
@@ -344,8 +354,8 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
     const StepDesc& sd = cur_set(a);
     constexpr bool EXPL = MODE == 0 || MODE == 4;
     const double* U = EXPL ? a.pool[a.ctl->cur] : a.pool[a.ctl->y];
-    const double* P0 = EXPL ? U : a.W;
-    double* out = MODE == 4 ? a.W : a.R;
+    const double* P0 = EXPL ? U : wcur(a);
+    double* out = MODE == 4 ? wcur(a) : (MODE == 0 ? wprev(a) : a.R);
     const double c = EXPL ? sd.dt * (1.0 - sd.theta) : sd.dt * sd.theta;
     const double c0 = EXPL ? 0.0 : -1.0;
     const bool want_r = MODE != 0 || sd.theta < 1.0;
@@ -396,14 +406,15 @@ __global__ __launch_bounds__(256) void ks_affine_noB(const MarchArgs* __restrict
     if (i >= n) return;
     const StepDesc& sd = cur_set(a);
     const double* U = EXPLICIT ? a.pool[a.ctl->cur] : a.pool[a.ctl->y];
-    const double* P0 = EXPLICIT ? U : a.W;
+    const double* P0 = EXPLICIT ? U : wcur(a);
+    double* out = EXPLICIT ? wprev(a) : a.R;
     const double c = EXPLICIT ? sd.dt * (1.0 - sd.theta) : sd.dt * sd.theta;
     const double c0 = EXPLICIT ? 0.0 : -1.0;
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
         const size_t o = (size_t)i * n + j;
         const double u = U[o];
         const double d = apply_D(U, a.st, i, j, u);
-        a.R[o] = P0[o] + c * (d - a.r_omega * u) + c0 * u;
+        out[o] = P0[o] + c * (d - a.r_omega * u) + c0 * u;
     }
 }
 
@@ -423,180 +434,166 @@ static __global__ __launch_bounds__(256) void ks_carry(const MarchArgs* __restri
     const StepDesc& sd = cur_set(a);
     const double* U = a.pool[a.ctl->cur];
     const double c = sd.dt * (1.0 - sd.theta);
+    double* E = wprev(a);
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
         const size_t o = (size_t)i * n + j;
         const double u = U[o];
-        a.R[o] = u + c * (apply_D(U, a.st, i, j, u) + a.BY[o] - a.r_omega * u);
+        E[o] = u + c * (apply_D(U, a.st, i, j, u) + a.BY[o] - a.r_omega * u);
     }
 }
 
-// Explicit part from the previous step's implicit equation (explicit_by_identity):
-// R = V + rho (V - W); one block per grid row.  Mixed form: not in anchor steps.
+// Explicit part from the previous step's implicit equation (explicit_by_identity),
+// over the W it comes from: E = V + rho (V - W); one block per grid row.  Mixed
+// form: not in anchor steps.  Steps that ks_begin_lin takes form it there.
 static __global__ __launch_bounds__(256) void ks_expl_identity(const MarchArgs* __restrict__ A) {
     const MarchArgs& a = plan_args(A);
-    if (halted(a, 0) || !explicit_by_identity(a) || (a.mixed && is_anchor(a))) return;
+    if (halted(a, 0) || !explicit_by_identity(a) || (a.mixed && is_anchor(a)) || start_by_linearity(a)) return;
     const int n = a.n;
     const int i = blockIdx.x;
     if (i >= n) return;
     const double rho = a.cn_rho[a.ctl->step];
     const double* V = a.pool[a.ctl->cur] + (size_t)i * n;
-    const double* W = a.W + (size_t)i * n;
-    double* R = a.R + (size_t)i * n;
+    double* W = wprev(a) + (size_t)i * n;
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
         const double v = V[j];
-        R[j] = v + rho * (v - W[j]);
+        W[j] = v + rho * (v - W[j]);
     }
 }
 
-// FP64 iteration 1 when B Y^0 comes by linearity (start_by_linearity):
-// B Y^0 = sum_q coef_q B V^{src_q} from the stored products, the residual
-// R = W + dt theta((D - r_omega) Y^0 + B Y^0) - Y^0, and B Y^0 stored for the
-// iterate; one block per grid row (the row c2r kernel exits in these steps).
-// The element loop has no branch and the arguments are read once before it (the
-// stores go through plain pointers, after which they would be read again), so
-// that an element's reads are in flight together.  One loop serves every count
-// of stored products: the terms past the count repeat the first product at
-// weight zero (Ctl: reads of lines the thread has just fetched, and the same
-// sums, since adding a signed zero changes no value).  A dispatch to one loop
-// per count cost 10 us per launch at 2048^2 (90 against 80).
-template <int UN = 4>
-__device__ __forceinline__ void rows_lin_row(const MarchArgs& a, int i, double cth) {
-    constexpr int NS = 4;
+// Threads of ks_begin_lin, and the columns of its tiles for a grid side n: at
+// most BEGIN_T - 4, so that one thread per column covers the start value with its
+// stencil's neighbours (two more) and the gather's source columns (P more);
+// rounded to whole cache lines where that fits.
+constexpr int BEGIN_T = 256;
+__host__ __device__ __forceinline__ int begin_cols(int n) {
+    const int t = (n + BEGIN_T - 5) / (BEGIN_T - 4), c = (n + t - 1) / t, r = (c + 15) & ~15;
+    return r <= BEGIN_T - 4 ? r : c;
+}
+// Tiles of TR rows that cover an n x n grid.
+__host__ __device__ __forceinline__ int begin_tiles(int n, int TR) {
+    const int c = begin_cols(n);
+    return ((n + TR - 1) / TR) * ((n + c - 1) / c);
+}
+
+// The start of an FP64 step whose B Y^0 comes by linearity (start_by_linearity),
+// without any transform, on a tile of TR rows:
+//   E = V + rho (V - W_prev) (explicit_by_identity; V when theta = 1; W_prev where
+//       the correlation left E there),
+//   W = T^SL E, the row weights first, then the column taps from LDS,
+//   Y^0 = sum_q coef_q V^{src_q},  B Y^0 = sum_q coef_q B V^{src_q} (stored products),
+//   R = W + dt theta ((D - r_omega) Y^0 + B Y^0) - Y^0, the residual of iteration 1.
+// One streaming pass (13 n^2 reads and writes of FP64) in place of three kernels
+// of 3, 7 and 8 that passed E, W and Y^0 through memory: 119 us instead of 17 + 62
+// + 66 at 2048^2, 11.8 instead of 4.8 + 7.8 + 7.0 at 512^2.  A tile's start value is
+// formed once per node and halo row and its stencil reads LDS, so the history is
+// read (TR + 2) / TR times; the terms past the count of stored grids repeat the
+// first at weight zero (Ctl), so that one loop serves every count.
+template <int P, int TR>
+__global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restrict__ A) {
+    const MarchArgs& a = plan_args(A);
+    if (halted(a, 0) || !start_by_linearity(a)) return;
+    constexpr int T = BEGIN_T, NS = 4;
+    __shared__ double ys[TR + 2][T];              // Y^0, rows r0 - 1 .., columns c0 - 1 ..
+    __shared__ double ec[TR][T];                  // row-combined E, columns k0 ..
+    const int n = a.n, tcw = begin_cols(n), tc = (n + tcw - 1) / tcw, nt = ((n + TR - 1) / TR) * tc;
+    if ((int)blockIdx.x >= nt) return;
+    const int tile = xcd_remap(blockIdx.x, nt);   // neighbouring tiles on one XCD (halo rows share L2)
+    const int r0 = (tile / tc) * TR, c0 = (tile % tc) * tcw, c1 = min(n, c0 + tcw), t = threadIdx.x;
     const Ctl* c = a.ctl;
-    const int n = a.n;
+    const StepDesc& sd = cur_set(a);
+    const double* __restrict__ V = a.pool[c->cur];
+    const double* __restrict__ Wp = wprev(a);
+    double* __restrict__ W = wcur(a);
+    double* __restrict__ Y = a.pool[c->y];
+    double* __restrict__ R = a.R;
+    double* __restrict__ Bout = a.bpool[c->y];
+    const double* __restrict__ H[NS];
     const double* __restrict__ Hb[NS];
     double cf[NS];
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
+        H[q] = a.pool[c->src[q]];
         Hb[q] = a.bpool[c->src[q]];
         cf[q] = c->coef[q];
     }
-    const double* __restrict__ U = a.pool[c->y];
-    const double* __restrict__ W = a.W;
-    double* __restrict__ R = a.R;
-    double* __restrict__ Bout = a.bpool[c->y];
-    const double r_omega = a.r_omega;
+    const double cth = sd.dt * sd.theta, r_omega = a.r_omega;
     const StencilArgs st = a.st;
-    // UN elements per thread and pass, the products and W of all of them read
-    // first (their reads in flight together: 90 -> 80 -> 71 us per launch at
-    // 2048^2 with one loop per count, one loop, one loop of UN = 4)
-    for (int j0 = threadIdx.x; j0 < n; j0 += UN * blockDim.x) {
-        double bu[UN], w[UN];
+    // E of a node: 0 V, 1 the identity, 2 already in Wp
+    const int emode = sd.theta >= 1.0 ? 0 : (explicit_by_identity(a) ? 1 : 2);
+    const double rho = emode == 1 ? a.cn_rho[c->step] : 0.0;
+    auto e_at = [&](size_t o) -> double {
+        if (emode == 2) return Wp[o];
+        const double v = V[o];
+        return emode == 1 ? v + rho * (v - Wp[o]) : v;
+    };
+    // start value of this thread's column, its rows and the two around them
+    double y[TR + 2];
+    {
+        const int j = min(max(c0 - 1 + t, 0), n - 1);
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int j = j0 + u * blockDim.x;
-            const size_t o = (size_t)i * n + (j < n ? j : j0);   // past the row end: a repeated read, not used
-            bu[u] = 0.0;
+        for (int q = 0; q < TR + 2; ++q) {
+            const size_t o = (size_t)min(max(r0 - 1 + q, 0), n - 1) * n + j;
+            double v = cf[0] * H[0][o];
 #pragma unroll
-            for (int q = 0; q < NS; ++q) bu[u] += cf[q] * Hb[q][o];
-            w[u] = W[o];
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int j = j0 + u * blockDim.x;
-            if (j >= n) break;
-            const size_t o = (size_t)i * n + j;
-            const double y = U[o];
-            const double d = apply_D_ahead(U, st, i, j, y);
-            R[o] = w[u] + cth * (d + bu[u] - r_omega * y) - y;
-            Bout[o] = bu[u];
+            for (int h = 1; h < NS; ++h) v += cf[h] * H[h][o];
+            y[q] = v;
+            ys[q][t] = v;
         }
     }
-}
-
-static __global__ __launch_bounds__(256) void ks_rows_lin(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 1) || !start_by_linearity(a)) return;
-    const int n = a.n;
-    const int i = xcd_remap(blockIdx.x, gridDim.x);   // neighbouring rows on one XCD (stencil reads share L2)
-    if (i >= n) return;
-    const StepDesc& sd = cur_set(a);
-    rows_lin_row(a, i, sd.dt * sd.theta);
-}
-
-// The row of ks_sl_lin with NS history grids in the start value.  The gather
-// is taken in its separable order: the row weights combine the P + 1 source
-// rows into ec (LDS, n values: four coalesced reads per element instead of
-// (P + 1)^2 stencil reads), then each node takes its P + 1 column taps from ec.
-// Two elements per thread and pass, their history reads issued together; no
-// branch in the element loop and the step's tables read once before it.
-template <int P, int NS>
-__device__ __forceinline__ void sl_lin_row(const MarchArgs& a, int i, double* __restrict__ ec) {
-    const Ctl* c = a.ctl;
-    const int n = a.n;
-    const StepDesc& sd = cur_set(a);
-    // the grids read (E, history) and written (W, Y) are distinct pool, R and W buffers
-    const double* __restrict__ Ex = sd.theta < 1.0 ? a.R : a.pool[c->cur];
-    double* __restrict__ Y = a.pool[c->y];
-    double* __restrict__ Wo = a.W;
-    const double* __restrict__ H[NS];
-    double cf[NS];
+    // E's source rows combined by the row weights.  Away from the grid's ends the
+    // source rows of consecutive rows are consecutive (one set of reads per tile).
+    const int k0 = sd.s2[c0], k = k0 + t;
+    if (k <= sd.s2[c1 - 1] + P) {
+        const int rl = min(TR, n - r0), a0 = sd.s1[r0];
+        bool run = true;
 #pragma unroll
-    for (int q = 0; q < NS; ++q) {
-        H[q] = a.pool[c->src[q]];
-        cf[q] = c->coef[q];
-    }
-    const int a0 = sd.s1[i];
-    double w1[P + 1];
+        for (int r = 1; r < TR; ++r) run = run && (r >= rl || sd.s1[r0 + r] == a0 + r);
+        if (run) {
+            double e[TR + P];
 #pragma unroll
-    for (int q = 0; q <= P; ++q) w1[q] = sd.w1[i * (P + 1) + q];
-    const double* __restrict__ er0 = Ex + (size_t)a0 * n;
-    const int T = blockDim.x;
-    for (int k = threadIdx.x; k < n; k += T) {
-        double v = 0.0;
+            for (int q = 0; q < TR + P; ++q) e[q] = e_at((size_t)min(a0 + q, n - 1) * n + k);
 #pragma unroll
-        for (int q = 0; q <= P; ++q) v += w1[q] * er0[(size_t)q * n + k];
-        ec[k] = v;
+            for (int r = 0; r < TR; ++r) {
+                double v = 0.0;
+#pragma unroll
+                for (int q = 0; q <= P; ++q) v += sd.w1[(size_t)min(r0 + r, n - 1) * (P + 1) + q] * e[r + q];
+                ec[r][t] = v;
+            }
+        } else {
+            for (int r = 0; r < rl; ++r) {
+                double v = 0.0;
+                for (int q = 0; q <= P; ++q)
+                    v += sd.w1[(size_t)(r0 + r) * (P + 1) + q] * e_at((size_t)(sd.s1[r0 + r] + q) * n + k);
+                ec[r][t] = v;
+            }
+        }
     }
     __syncthreads();
-    const int* __restrict__ s2 = sd.s2;
-    const double* __restrict__ wt2 = sd.w2;
-    constexpr int UN = 2;
-    for (int j0 = threadIdx.x; j0 < n; j0 += UN * T) {
-        double hv[UN][NS];
+    const int j = c0 - 1 + t;
+    if (t == 0 || j >= c1) return;
+    const int b0 = sd.s2[j] - k0;
+    double w2[P + 1];
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int j = j0 + u * T;
-            const size_t o = (size_t)i * n + (j < n ? j : j0);   // past the row end: a repeated read, not used
+    for (int b = 0; b <= P; ++b) w2[b] = sd.w2[(size_t)j * (P + 1) + b];
+    double* segE = a.segE && sd.theta < 1.0 ? a.segE + (size_t)(c->step - a.seg_base) * n * n : nullptr;
 #pragma unroll
-            for (int q = 0; q < NS; ++q) hv[u][q] = H[q][o];
-        }
+    for (int r = 0; r < TR; ++r) {
+        const int i = r0 + r;
+        if (i >= n) break;
+        const size_t o = (size_t)i * n + j;
+        double bu = 0.0, w = 0.0;
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int j = j0 + u * T;
-            if (j >= n) break;
-            const int b0 = s2[j];
-            double acc = 0.0;
+        for (int q = 0; q < NS; ++q) bu += cf[q] * Hb[q][o];
 #pragma unroll
-            for (int b = 0; b <= P; ++b) acc += wt2[j * (P + 1) + b] * ec[b0 + b];
-            const size_t o = (size_t)i * n + j;
-            double y = cf[0] * hv[u][0];
-#pragma unroll
-            for (int q = 1; q < NS; ++q) y += cf[q] * hv[u][q];
-            Wo[o] = acc;
-            Y[o] = y;
-        }
-    }
-}
-
-// SL gather W = T^SL E and start value Y^0 of an FP64 step whose B Y^0 comes by
-// linearity (no row transform of Y^0): one block per grid row, streaming; at
-// least 8 waves per SIMD (64 registers), so that the reads hoisted out of the
-// branch-free loop do not cost occupancy.  Dynamic LDS: n doubles (the largest
-// n of the launch's plans).
-template <int P>
-__global__ __launch_bounds__(256, 8) void ks_sl_lin(const MarchArgs* __restrict__ A) {
-    extern __shared__ double sl_ec[];
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0) || a.mixed || !start_by_linearity(a)) return;
-    const int n = a.n;
-    const int i = xcd_remap(blockIdx.x, gridDim.x);   // neighbouring rows share E rows in L2
-    if (i >= n) return;
-    switch (a.ctl->nsrc) {                           // uniform: one loop per count of history grids (1..4)
-        case 1: sl_lin_row<P, 1>(a, i, sl_ec); break;
-        case 2: sl_lin_row<P, 2>(a, i, sl_ec); break;
-        case 3: sl_lin_row<P, 3>(a, i, sl_ec); break;
-        default: sl_lin_row<P, 4>(a, i, sl_ec); break;
+        for (int b = 0; b <= P; ++b) w += w2[b] * ec[r][b0 + b];
+        const double u = y[r + 1];
+        const double d = D_of(st, i, j, u, y[r], y[r + 2], ys[r + 1][t - 1], ys[r + 1][t + 1], ys[r][t - 1],
+                              ys[r][t + 1], ys[r + 2][t - 1], ys[r + 2][t + 1]);
+        W[o] = w;
+        Y[o] = u;
+        Bout[o] = bu;
+        R[o] = w + cth * (d + bu - r_omega * u) - u;
+        if (segE) segE[o] = e_at(o);
     }
 }
 
@@ -663,7 +660,7 @@ template <int L, int E, int P, bool FFT, bool MIXED>
 __global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A) {
     const MarchArgs& a = plan_args(A);
     // FP64 steps whose B Y^0 comes by linearity need no row transform of Y^0:
-    // ks_sl_lin does their gather and start value
+    // ks_begin_lin does their gather and start value
     if (halted(a, 0) || (FFT && !MIXED && start_by_linearity(a))) return;
     constexpr int T = L / E;
     using C = typename std::conditional<MIXED, float2, double2>::type;
@@ -678,7 +675,8 @@ __global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A) 
     const int tid = threadIdx.x;
     const Ctl* c = a.ctl;
     const StepDesc& sd = cur_set(a);
-    const double* Ex = sd.theta < 1.0 ? a.R : a.pool[c->cur];   // explicit part E_s
+    const double* Ex = sd.theta < 1.0 ? wprev(a) : a.pool[c->cur];   // explicit part E_s
+    double* W = wcur(a);
     double* Y = a.pool[c->y];
     const int nsrc = c->nsrc;
     const double* H[4];
@@ -738,7 +736,7 @@ __global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A) 
             for (int r = 0; r < 2; ++r) {
                 if (r == 1 && !hasb) break;
                 const size_t o = (size_t)(ra + r) * n + j;
-                a.W[o] = wv[e][r];
+                W[o] = wv[e][r];
                 Y[o] = yv[e][r];
                 y0[r] = yf[e][r];
             }
@@ -934,6 +932,7 @@ static __global__ void ks_step_end(const MarchArgs* __restrict__ A, int kmax) {
                 }
                 c->y = fr;
                 c->bvalid &= ~(1 << fr);                  // the free grid takes the next iterate
+                c->w ^= 1;
                 const int s2 = s + 1;
                 c->step = s2;
                 for (int q = 0; q < 4; ++q) { c->src[q] = c->hist[q]; c->coef[q] = 0.0; }
@@ -956,17 +955,18 @@ static __global__ void ks_step_end(const MarchArgs* __restrict__ A, int kmax) {
     if (ok) err_reset_upto(c, kmax);
 }
 
-// Recording for the adjoint march.  After sl (once per step): E_s, held in R
-// when theta < 1, to segE.  After step_end: the current state to seg when its
+// Recording for the adjoint march.  After sl (once per step): E_s, held in wprev
+// when theta < 1, to segE (ks_begin_lin records it itself).  After step_end: the current state to seg when its
 // step index is on the recording stride (idempotent: a slot whose step did not
 // advance writes the same state again).
 static __global__ void ks_store_E(const MarchArgs* __restrict__ A) {
     const MarchArgs& a = plan_args(A);
-    if (halted(a, 0) || !a.segE || cur_set(a).theta >= 1.0) return;
+    if (halted(a, 0) || !a.segE || cur_set(a).theta >= 1.0 || start_by_linearity(a)) return;
     const size_t N = (size_t)a.n * a.n;
+    const double* src = wprev(a);
     double* dst = a.segE + (size_t)(a.ctl->step - a.seg_base) * N;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (size_t)gridDim.x * blockDim.x)
-        dst[i] = a.R[i];
+        dst[i] = src[i];
 }
 
 static __global__ void ks_store_V(const MarchArgs* __restrict__ A) {
@@ -987,7 +987,7 @@ static __global__ void ks_store_V(const MarchArgs* __restrict__ A) {
 // (I - dt theta A)^T lam = Ybar by the transposed preconditioned iteration
 // (the forward iteration kernels with B^T, D^T and the transposed line factors),
 // mu = (T^SL)^T lam, and the cotangent of V^s is (I + dt (1 - theta) A)^T mu.
-// Buffers of the adjoint MarchArgs: pool[1] = lam, pool[0] = mu, W = Ybar.
+// Buffers of the adjoint MarchArgs: pool[1] = lam, pool[0] = mu, Wb = Ybar.
 
 // Control block for reverse step s: iterate in pool[1], no failure, stopping values reset.
 static __global__ void ks_adj_begin(const MarchArgs* __restrict__ A, int s) {
@@ -1000,6 +1000,7 @@ static __global__ void ks_adj_begin(const MarchArgs* __restrict__ A, int s) {
         c->hold = 0;
         c->cur = 0;
         c->y = 1;
+        c->w = 0;
     }
 }
 
@@ -1026,6 +1027,7 @@ __global__ __launch_bounds__(L / E) void ks_adj_start(const MarchArgs* __restric
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
     double* lam = a.pool[a.ctl->y];
+    const double* Yb = wcur(a);
     double2 reg[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -1033,11 +1035,11 @@ __global__ __launch_bounds__(L / E) void ks_adj_start(const MarchArgs* __restric
         double va = 0.0, vb = 0.0;
         if (j < n) {
             const size_t oa = (size_t)ra * n + j, ob = (size_t)rb * n + j;
-            va = a.W[oa] + (c1 ? w1 * c1[oa] : 0.0) + (c2 ? w2 * c2[oa] : 0.0) + (c3 ? w3 * c3[oa] : 0.0) +
+            va = Yb[oa] + (c1 ? w1 * c1[oa] : 0.0) + (c2 ? w2 * c2[oa] : 0.0) + (c3 ? w3 * c3[oa] : 0.0) +
                  (c4 ? w4 * c4[oa] : 0.0);
             lam[oa] = va;
             if (hasb) {
-                vb = a.W[ob] + (c1 ? w1 * c1[ob] : 0.0) + (c2 ? w2 * c2[ob] : 0.0) + (c3 ? w3 * c3[ob] : 0.0) +
+                vb = Yb[ob] + (c1 ? w1 * c1[ob] : 0.0) + (c2 ? w2 * c2[ob] : 0.0) + (c3 ? w3 * c3[ob] : 0.0) +
                      (c4 ? w4 * c4[ob] : 0.0);
                 lam[ob] = vb;
             }
@@ -1054,8 +1056,9 @@ static __global__ void ks_adj_corr(const MarchArgs* __restrict__ A, double* __re
     if (halted(a, 0)) return;
     const size_t N = (size_t)a.n * a.n;
     const double* lam = a.pool[a.ctl->y];
+    const double* Yb = wcur(a);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (size_t)gridDim.x * blockDim.x)
-        corr[i] = lam[i] - a.W[i];
+        corr[i] = lam[i] - Yb[i];
 }
 
 // Verdict of the adjoint fixed point of the current reverse step: iteration
@@ -1322,6 +1325,7 @@ static __global__ void ks_init(const MarchArgs* __restrict__ A) {
         c->hc = 1;
         c->nsrc = 1;
         c->bvalid = 0;
+        c->w = 0;
         for (int q = 0; q < 4; ++q) { c->hist[q] = 0; c->src[q] = 0; c->coef[q] = 0.0; }
         c->coef[0] = 1.0;
     }
