@@ -106,7 +106,8 @@ def kernel_symbol(cls, L, mixed, sl_order, radix=(8, 8, 8, 8), n=None):
     ec, er, el, es = radix
     return {
         "cols": "lpide::ks_cols<%d, %d, HIP_vector_type<%s, 2u>, false>" % (L, ec, c),
-        "expl_cols": "lpide::ks_cols<%d, %d, HIP_vector_type<double, 2u>, false>" % (L, ec),
+        "expl_cols": ("lpide::ks_cols_anchor<%d, %d>" if mixed else
+                      "lpide::ks_cols<%d, %d, HIP_vector_type<double, 2u>, false>") % (L, ec),
         "rows_inv": "lpide::ks_rows_inv<%d, %d, %d>" % (L, er, 2 if mixed else 1),
         "expl_rows": "lpide::ks_rows_inv<%d, %d, 0>" % (L, er),
         "line_cols": "lpide::ks_line_cols",

@@ -317,10 +317,11 @@ struct TwTab {
 template <int L, int E>
 constexpr int tw_slots() { return TwTab<L, E>::size > 0 ? TwTab<L, E>::size : 1; }
 
-// Build the stage tables in LDS from the full table tw[q] = exp(-2 pi i q / L);
+// Build the stage tables in LDS from the full table tw[q] = exp(-2 pi i q / L)
+// (a pointer or an indexable view of global memory);
 // visible to the FFT stages after the next barrier (stage 0 needs none).
-template <int L, int E>
-__device__ __forceinline__ void load_twiddles(const double2* __restrict__ tw, double2* tab) {
+template <int L, int E, typename Tw>
+__device__ __forceinline__ void load_twiddles(Tw tw, double2* tab) {
     using TT = TwTab<L, E>;
     for (int i = threadIdx.x; i < TT::size; i += L / E) {
 #pragma unroll
@@ -511,9 +512,8 @@ __device__ __forceinline__ void fft_block(C (&reg)[E], C* lds, const double2* ta
 // LDS once (the partner W sits in another thread); all threads of the block call it.
 // The spectrum reads are not hoisted ahead of each other (one block of a launch
 // runs this; its registers must not raise the kernel's count).
-template <int L, int E, bool CONJ, typename C>
-__device__ __forceinline__ void mul_real_pair(C (&reg)[E], C* lds, const C* __restrict__ sa,
-                                              const C* __restrict__ sb) {
+template <int L, int E, bool CONJ, typename C, typename Spec>
+__device__ __forceinline__ void mul_real_pair(C (&reg)[E], C* lds, Spec sa, Spec sb) {
     using Rl = typename CplxOps<C>::real;
     constexpr int T = L / E;
     const int tid = threadIdx.x;

@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include "fft.hpp"
+#include "gmem.hpp"
 
 namespace lpide {
 
@@ -38,17 +39,16 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 // D applied to U at (i, j).  Second differences only on interior indices of
 // their own axis (the log form of the boundary rule "v linear in x"); the
 // mixed term uses d~ = central inside, forward at 0, backward at n-1.
-__device__ __forceinline__ double apply_D(const double* __restrict__ U, const StencilArgs& s, int i, int j,
-                                          double u) {
+__device__ __forceinline__ double apply_D(GP<double> U, const StencilArgs& s, int i, int j, double u) {
     const int n = s.n;
     const double ih2 = 1.0 / (s.h * s.h), i2h = 0.5 / s.h;
     double d = 0.0;
     if (i > 0 && i < n - 1) {
-        const double um = U[(size_t)(i - 1) * n + j], up = U[(size_t)(i + 1) * n + j];
+        const double um = U[(i - 1) * n + j], up = U[(i + 1) * n + j];
         d += 0.5 * s.a11 * ((up - 2.0 * u + um) * ih2 - (up - um) * i2h);
     }
     if (j > 0 && j < n - 1) {
-        const double um = U[(size_t)i * n + j - 1], up = U[(size_t)i * n + j + 1];
+        const double um = U[i * n + j - 1], up = U[i * n + j + 1];
         d += 0.5 * s.a22 * ((up - 2.0 * u + um) * ih2 - (up - um) * i2h);
     }
     if (s.a12 != 0.0) {
@@ -60,8 +60,8 @@ __device__ __forceinline__ double apply_D(const double* __restrict__ U, const St
         if (j == 0) { j0 = 0; j1 = 1; gj = 1.0 / s.h; }
         else if (j == n - 1) { j0 = n - 2; j1 = n - 1; gj = 1.0 / s.h; }
         else { j0 = j - 1; j1 = j + 1; gj = i2h; }
-        const double u00 = U[(size_t)i0 * n + j0], u01 = U[(size_t)i0 * n + j1];
-        const double u10 = U[(size_t)i1 * n + j0], u11 = U[(size_t)i1 * n + j1];
+        const double u00 = U[i0 * n + j0], u01 = U[i0 * n + j1];
+        const double u10 = U[i1 * n + j0], u11 = U[i1 * n + j1];
         d += s.a12 * gi * gj * ((u11 - u10) - (u01 - u00));
     }
     return d;
@@ -89,16 +89,16 @@ __device__ __forceinline__ double D_of(const StencilArgs& s, int i, int j, doubl
 
 // The three unit-coefficient parts of D at (i, j): D u = a11 d11 + a12 d12 + a22 d22
 // (the derivative of D u with respect to each coefficient).
-__device__ __forceinline__ void apply_D_parts(const double* __restrict__ U, int n, double h, int i, int j, double u,
-                                              double& d11, double& d12, double& d22) {
+__device__ __forceinline__ void apply_D_parts(GP<double> U, int n, double h, int i, int j, double u, double& d11,
+                                              double& d12, double& d22) {
     const double ih2 = 1.0 / (h * h), i2h = 0.5 / h;
     d11 = d12 = d22 = 0.0;
     if (i > 0 && i < n - 1) {
-        const double um = U[(size_t)(i - 1) * n + j], up = U[(size_t)(i + 1) * n + j];
+        const double um = U[(i - 1) * n + j], up = U[(i + 1) * n + j];
         d11 = 0.5 * ((up - 2.0 * u + um) * ih2 - (up - um) * i2h);
     }
     if (j > 0 && j < n - 1) {
-        const double um = U[(size_t)i * n + j - 1], up = U[(size_t)i * n + j + 1];
+        const double um = U[i * n + j - 1], up = U[i * n + j + 1];
         d22 = 0.5 * ((up - 2.0 * u + um) * ih2 - (up - um) * i2h);
     }
     int i0, i1, j0, j1;
@@ -109,8 +109,8 @@ __device__ __forceinline__ void apply_D_parts(const double* __restrict__ U, int 
     if (j == 0) { j0 = 0; j1 = 1; gj = 1.0 / h; }
     else if (j == n - 1) { j0 = n - 2; j1 = n - 1; gj = 1.0 / h; }
     else { j0 = j - 1; j1 = j + 1; gj = i2h; }
-    const double u00 = U[(size_t)i0 * n + j0], u01 = U[(size_t)i0 * n + j1];
-    const double u10 = U[(size_t)i1 * n + j0], u11 = U[(size_t)i1 * n + j1];
+    const double u00 = U[i0 * n + j0], u01 = U[i0 * n + j1];
+    const double u10 = U[i1 * n + j0], u11 = U[i1 * n + j1];
     d12 = gi * gj * ((u11 - u10) - (u01 - u00));
 }
 
@@ -131,8 +131,7 @@ __device__ __forceinline__ int diff_T(int n, double h, int p, int* r, double* c)
 
 // D^T applied to U at (i, j): the transposed log-grid stencil, boundary rows
 // included (the adjoint of apply_D).
-__device__ __forceinline__ double apply_DT(const double* __restrict__ U, const StencilArgs& s, int i, int j,
-                                           double u) {
+__device__ __forceinline__ double apply_DT(GP<double> U, const StencilArgs& s, int i, int j, double u) {
     const int n = s.n;
     const double ih2 = 1.0 / (s.h * s.h), i2h = 0.5 / s.h;
     // Away from the edges (every neighbour an interior node) the transposed
@@ -140,14 +139,13 @@ __device__ __forceinline__ double apply_DT(const double* __restrict__ U, const S
     // second differences and the product of two central differences are
     // symmetric, a central difference is antisymmetric.
     if (i >= 2 && i <= n - 3 && j >= 2 && j <= n - 3) {
-        const double u1m = U[(size_t)(i - 1) * n + j], u1p = U[(size_t)(i + 1) * n + j];
-        const double u2m = U[(size_t)i * n + j - 1], u2p = U[(size_t)i * n + j + 1];
+        const double u1m = U[(i - 1) * n + j], u1p = U[(i + 1) * n + j];
+        const double u2m = U[i * n + j - 1], u2p = U[i * n + j + 1];
         double d = 0.5 * s.a11 * ((u1p - 2.0 * u + u1m) * ih2 + (u1p - u1m) * i2h) +
                    0.5 * s.a22 * ((u2p - 2.0 * u + u2m) * ih2 + (u2p - u2m) * i2h);
         if (s.a12 != 0.0) {
-            const double* rm = U + (size_t)(i - 1) * n;
-            const double* rp = U + (size_t)(i + 1) * n;
-            d += s.a12 * i2h * i2h * ((rp[j + 1] - rp[j - 1]) - (rm[j + 1] - rm[j - 1]));
+            const int rm = (i - 1) * n, rp = (i + 1) * n;
+            d += s.a12 * i2h * i2h * ((U[rp + j + 1] - U[rp + j - 1]) - (U[rm + j + 1] - U[rm + j - 1]));
         }
         return d;
     }
@@ -158,15 +156,15 @@ __device__ __forceinline__ double apply_DT(const double* __restrict__ U, const S
     {
         double t = 0.0;
         if (i > 0 && i < n - 1) t -= ih2 * u;
-        if (i - 1 >= 1 && i - 1 <= n - 2) t += cu * U[(size_t)(i - 1) * n + j];
-        if (i + 1 >= 1 && i + 1 <= n - 2) t += cl * U[(size_t)(i + 1) * n + j];
+        if (i - 1 >= 1 && i - 1 <= n - 2) t += cu * U[(i - 1) * n + j];
+        if (i + 1 >= 1 && i + 1 <= n - 2) t += cl * U[(i + 1) * n + j];
         d += s.a11 * t;
     }
     {
         double t = 0.0;
         if (j > 0 && j < n - 1) t -= ih2 * u;
-        if (j - 1 >= 1 && j - 1 <= n - 2) t += cu * U[(size_t)i * n + j - 1];
-        if (j + 1 >= 1 && j + 1 <= n - 2) t += cl * U[(size_t)i * n + j + 1];
+        if (j - 1 >= 1 && j - 1 <= n - 2) t += cu * U[i * n + j - 1];
+        if (j + 1 >= 1 && j + 1 <= n - 2) t += cl * U[i * n + j + 1];
         d += s.a22 * t;
     }
     if (s.a12 != 0.0) {
@@ -175,7 +173,7 @@ __device__ __forceinline__ double apply_DT(const double* __restrict__ U, const S
         const int mi = diff_T(n, s.h, i, ri, ci), mj = diff_T(n, s.h, j, rj, cj);
         double t = 0.0;
         for (int a = 0; a < mi; ++a)
-            for (int b = 0; b < mj; ++b) t += ci[a] * cj[b] * U[(size_t)ri[a] * n + rj[b]];
+            for (int b = 0; b < mj; ++b) t += ci[a] * cj[b] * U[ri[a] * n + rj[b]];
         d += s.a12 * t;
     }
     return d;

@@ -617,7 +617,6 @@ int make_group(const std::vector<Plan*>& plans, hipStream_t stream, Group** out)
     g->args_h.resize(np);
     for (int i = 0; i < np; ++i) {
         MarchArgs a = march_args(plans[i]);
-        a.ctl = g->ctl + i;
         a.counts = g->counts + (size_t)i * g->maxsteps;
         a.incs = g->incs + (size_t)i * g->maxsteps;
         a.P_cols = c.P_cols;
@@ -693,7 +692,7 @@ int read_back(Group* g) {
 int complete_step(Group* g, int i, int kused, int* k_out) {
     const Launch& c = g->lc;
     Plan* p = g->plans[i];
-    hipLaunchKernelGGL(ks_hold, dim3(1), dim3(256), 0, c.stream, c.A, c.np, i);
+    hipLaunchKernelGGL(ks_hold, dim3(1), dim3(256), 0, c.stream, c.C, c.np, i);
     int k = kused;
     const int sf = g->ctl_h[i].fail_step;
     int rc = LPIDE_OK;
@@ -711,15 +710,15 @@ int complete_step(Group* g, int i, int kused, int* k_out) {
             break;
         }
         ++k;
-        hipLaunchKernelGGL(ks_clear_fail, dim3(1), dim3(64), 0, c.stream, c.A, i);
+        hipLaunchKernelGGL(ks_clear_fail, dim3(1), dim3(64), 0, c.stream, c.C, i);
         if (c.timer) c.timer->tag_step = sf;
         if ((rc = issue_iteration(c, k))) break;
-        hipLaunchKernelGGL(ks_step_end, dim3(1, c.np), dim3(64), 0, c.stream, c.A, k);
-        if (c.record) hipLaunchKernelGGL(ks_store_V, dim3(c.store_blocks, c.np), dim3(256), 0, c.stream, c.A);
+        hipLaunchKernelGGL(ks_step_end, dim3(1, c.np), dim3(64), 0, c.stream, c.A, c.C, k);
+        if (c.record) hipLaunchKernelGGL(ks_store_V, dim3(c.store_blocks, c.np), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C);
         if ((rc = read_back(g))) break;
         if (!g->ctl_h[i].fail) break;
     }
-    hipLaunchKernelGGL(ks_hold, dim3(1), dim3(256), 0, c.stream, c.A, c.np, -1);
+    hipLaunchKernelGGL(ks_hold, dim3(1), dim3(256), 0, c.stream, c.C, c.np, -1);
     if (rc == LPIDE_OK) HIP_TRY(hipGetLastError());
     *k_out = k;
     return rc;
@@ -771,9 +770,10 @@ int march_begin(Group* g, MarchState& st, const int* nsteps, int step0, const do
         }
     }
     HIP_TRY(hipMemcpyAsync(g->A, g->args_h.data(), sizeof(MarchArgs) * np, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(ks_init, dim3(1, np), dim3(64), 0, s, g->A);
+    hipLaunchKernelGGL(ks_init, dim3(1, np), dim3(64), 0, s, (const MarchArgs*)g->A, g->ctl);
     HIP_TRY(hipGetLastError());
     g->lc.A = g->A;
+    g->lc.C = g->ctl;
     st.maxit = 1;
     for (Plan* p : g->plans) st.maxit = std::max(st.maxit, p->opts.max_iter);
     st.kpred = std::min(8, st.maxit);
@@ -976,7 +976,6 @@ int adj_prepare(Plan* p, int C) {
     for (int b = 2; b < POOL; ++b) m.pool[b] = a->dummy;
     m.sets = a->sets_d;
     m.Wb[0] = m.Wb[1] = a->ybar;
-    m.ctl = a->ctl;
     m.counts = a->counts;
     m.incs = a->incs;
     m.mixed = 0;
@@ -1139,6 +1138,7 @@ int adjoint(Plan* p, const double* v_bar, int C, std::vector<double>& native, lp
     Launch c;
     c.stream = s;
     c.A = a->A;
+    c.C = a->ctl;
     c.np = 1;
     c.L = p->Lr;
     c.xrows = (n + 1) / 2;

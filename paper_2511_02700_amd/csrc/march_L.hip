@@ -96,34 +96,34 @@ void launch_iteration(const Launch& c, int k) {
             KTime t(c.timer, LPIDE_K_COLS);
             with_E<L>(c.E_cols, [&](auto e) {
                 constexpr int E = decltype(e)::value;
-                t.launch((ks_cols<L, E, C>), dim3(L / 2, c.np), dim3(L / E), 0, c.stream, c.A, k);
+                t.launch((ks_cols<L, E, C>), dim3(L / 2, c.np), dim3(L / E), 0, c.stream, c.A, c.C, k);
             });
         }
         {
             KTime t(c.timer, LPIDE_K_ROWS_INV);
             with_E<L>(c.E_rinv, [&](auto e) {
                 constexpr int E = decltype(e)::value;
-                t.launch((ks_rows_inv<L, E, MIXED ? 2 : 1>), dim3(c.xrows, c.np), dim3(L / E), 0, c.stream, c.A,
+                t.launch((ks_rows_inv<L, E, MIXED ? 2 : 1>), dim3(c.xrows, c.np), dim3(L / E), 0, c.stream, c.A, c.C,
                          k);
             });
         }
     }
     if (!FFT) {
         KTime t(c.timer, LPIDE_K_ROWS_INV);
-        t.launch((ks_affine_noB<false>), dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A, k);
+        t.launch((ks_affine_noB<false>), dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A, c.C, k);
     }
     {
         KTime t(c.timer, LPIDE_K_LINE_COLS);
         with_line_cols(c, [&](auto kern) {
             t.launch(kern, dim3(c.xcols, c.np), dim3(c.cpb * c.P_cols), sizeof(double2) * c.cpb * c.P_cols, c.stream,
-                     c.A, k);
+                     c.A, c.C, k);
         });
     }
     KTime t(c.timer, LPIDE_K_LINE_ROWS);
     with_E<L>(c.E_lrows, [&](auto e) {
         constexpr int E = decltype(e)::value;
         with_line_rows<L, E, FFT, MIXED>(c, [&](auto kern) {
-            t.launch(kern, dim3(c.xrows, c.np), dim3(L / E), 0, c.stream, c.A, k);
+            t.launch(kern, dim3(c.xrows, c.np), dim3(L / E), 0, c.stream, c.A, c.C, k);
         });
     });
 }
@@ -147,43 +147,44 @@ void launch_step(const Launch& c, int kmax) {
             KTime t(c.timer, LPIDE_K_ROWS_FWD);
             with_E<L>(c.E_rinv, [&](auto e) {
                 constexpr int E = decltype(e)::value;
-                t.launch((ks_rows_fwd<L, E>), gr, dim3(L / E), 0, c.stream, c.A);
+                t.launch((ks_rows_fwd<L, E>), gr, dim3(L / E), 0, c.stream, c.A, c.C);
             });
         }
         {
             KTime t(c.timer, LPIDE_K_EXPL_COLS);
             with_E<L>(c.E_cols, [&](auto e) {
                 constexpr int E = decltype(e)::value;
-                t.launch((ks_cols<L, E, double2>), gc, dim3(L / E), 0, c.stream, c.A, 0);
+                if constexpr (MIXED) t.launch((ks_cols_anchor<L, E>), gc, dim3(L / E), 0, c.stream, c.A, c.C);
+                else t.launch((ks_cols<L, E, double2>), gc, dim3(L / E), 0, c.stream, c.A, c.C, 0);
             });
         }
         {
             KTime t(c.timer, LPIDE_K_EXPL_ROWS);
             with_E<L>(c.E_rinv, [&](auto e) {
                 constexpr int E = decltype(e)::value;
-                t.launch((ks_rows_inv<L, E, 0>), gr, dim3(L / E), 0, c.stream, c.A, 0);
+                t.launch((ks_rows_inv<L, E, 0>), gr, dim3(L / E), 0, c.stream, c.A, c.C, 0);
             });
         }
         if (MIXED) {                      // steps between anchors without the identity (the three above exit)
             KTime t(c.timer, LPIDE_K_CARRY);
-            t.launch(ks_carry, dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A);
+            t.launch(ks_carry, dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A, c.C);
         }
         {                                 // explicit part from the previous step's equation (the two above exit)
             KTime t(c.timer, LPIDE_K_EXPL_ID);
-            t.launch(ks_expl_identity, dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A);
+            t.launch(ks_expl_identity, dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A, c.C);
         }
     } else if (!FFT) {
         KTime t(c.timer, LPIDE_K_EXPL_ROWS);
-        t.launch((ks_affine_noB<true>), dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A, 0);
+        t.launch((ks_affine_noB<true>), dim3(c.xaff, c.np), dim3(256), 0, c.stream, c.A, c.C, 0);
     }
     if (!lean) {
         KTime t(c.timer, LPIDE_K_SL);
         with_E<L>(c.E_sl, [&](auto e) {
             constexpr int E = decltype(e)::value;
             if (c.sl_order == 1)
-                t.launch((ks_sl<L, E, 1, FFT, MIXED>), gr, dim3(L / E), 0, c.stream, c.A);
+                t.launch((ks_sl<L, E, 1, FFT, MIXED>), gr, dim3(L / E), 0, c.stream, c.A, c.C);
             else
-                t.launch((ks_sl<L, E, 3, FFT, MIXED>), gr, dim3(L / E), 0, c.stream, c.A);
+                t.launch((ks_sl<L, E, 3, FFT, MIXED>), gr, dim3(L / E), 0, c.stream, c.A, c.C);
         });
     }
     if (FFT && !MIXED) {                  // steps with B Y^0 by linearity (ks_sl exits in them)
@@ -191,18 +192,18 @@ void launch_step(const Launch& c, int kmax) {
         with_begin_rows(c, [&](auto tr) {
             constexpr int TR = decltype(tr)::value;
             const dim3 g(begin_tiles(c.xaff, TR), c.np);
-            if (c.sl_order == 1) t.launch(ks_begin_lin<1, TR>, g, dim3(BEGIN_T), 0, c.stream, c.A);
-            else t.launch(ks_begin_lin<3, TR>, g, dim3(BEGIN_T), 0, c.stream, c.A);
+            if (c.sl_order == 1) t.launch(ks_begin_lin<1, TR>, g, dim3(BEGIN_T), 0, c.stream, c.A, c.C);
+            else t.launch(ks_begin_lin<3, TR>, g, dim3(BEGIN_T), 0, c.stream, c.A, c.C);
         });
     }
-    if (c.record && !lean) hipLaunchKernelGGL(ks_store_E, dim3(c.store_blocks, c.np), dim3(256), 0, c.stream, c.A);
+    if (c.record && !lean) hipLaunchKernelGGL(ks_store_E, dim3(c.store_blocks, c.np), dim3(256), 0, c.stream, c.A, c.C);
     for (int k = 1; k <= kmax; ++k) launch_iteration<L, FFT, MIXED>(c, k);
     if (c.timer) c.timer->tag_k = 0;
     {
         KTime t(c.timer, LPIDE_K_STEP_END);
-        t.launch(ks_step_end, dim3(1, c.np), dim3(64), 0, c.stream, c.A, kmax);
+        t.launch(ks_step_end, dim3(1, c.np), dim3(64), 0, c.stream, c.A, c.C, kmax);
     }
-    if (c.record) hipLaunchKernelGGL(ks_store_V, dim3(c.store_blocks, c.np), dim3(256), 0, c.stream, c.A);
+    if (c.record) hipLaunchKernelGGL(ks_store_V, dim3(c.store_blocks, c.np), dim3(256), 0, c.stream, c.A, c.C);
 }
 
 template <int L>
@@ -226,20 +227,20 @@ template <int L>
 void launch_adj_iteration(const Launch& c, int k) {
     with_E<L>(c.E_cols, [&](auto e) {
         constexpr int E = decltype(e)::value;
-        hipLaunchKernelGGL((ks_cols<L, E, double2, true>), dim3(L / 2, 1), dim3(L / E), 0, c.stream, c.A, k);
+        hipLaunchKernelGGL((ks_cols<L, E, double2, true>), dim3(L / 2, 1), dim3(L / E), 0, c.stream, c.A, c.C, k);
     });
     with_E<L>(c.E_rinv, [&](auto e) {
         constexpr int E = decltype(e)::value;
-        hipLaunchKernelGGL((ks_rows_inv<L, E, 3>), dim3(c.xrows, 1), dim3(L / E), 0, c.stream, c.A, k);
+        hipLaunchKernelGGL((ks_rows_inv<L, E, 3>), dim3(c.xrows, 1), dim3(L / E), 0, c.stream, c.A, c.C, k);
     });
     with_line_cols(c, [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(c.xcols, 1), dim3(c.cpb * c.P_cols), sizeof(double2) * c.cpb * c.P_cols,
-                           c.stream, c.A, k);
+                           c.stream, c.A, c.C, k);
     });
     with_E<L>(c.E_lrows, [&](auto e) {
         constexpr int E = decltype(e)::value;
         with_line_rows<L, E, true, false>(c, [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(c.xrows, 1), dim3(L / E), 0, c.stream, c.A, k);
+            hipLaunchKernelGGL(kern, dim3(c.xrows, 1), dim3(L / E), 0, c.stream, c.A, c.C, k);
         });
     });
 }
@@ -253,7 +254,7 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
     const size_t N = (size_t)n * n;
     const StepDesc& sd = p->sets[p->step_set[s]];
     const dim3 gr(c.xrows, 1);
-    hipLaunchKernelGGL(ks_adj_begin, dim3(1), dim3(64), 0, c.stream, c.A, s);
+    hipLaunchKernelGGL(ks_adj_begin, dim3(1), dim3(64), 0, c.stream, c.A, c.C, s);
     const double cth = sd.dt * sd.theta;
     // the correction lam - Ybar = dt theta A^T lam of the previous reverse
     // steps, rescaled to this step's dt theta and extrapolated over the run of
@@ -273,12 +274,12 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
     }
     with_E<L>(c.E_rinv, [&](auto e) {
         constexpr int E = decltype(e)::value;
-        hipLaunchKernelGGL((ks_adj_start<L, E>), gr, dim3(L / E), 0, c.stream, c.A, cp[0], cw[0], cp[1], cw[1], cp[2],
+        hipLaunchKernelGGL((ks_adj_start<L, E>), gr, dim3(L / E), 0, c.stream, c.A, (const Ctl*)c.C, cp[0], cw[0], cp[1], cw[1], cp[2],
                            cw[2], cp[3], cw[3]);
     });
     int k = *kpred;
     for (int q = 1; q <= k; ++q) launch_adj_iteration<L>(c, q);
-    hipLaunchKernelGGL(ks_adj_end, dim3(1), dim3(64), 0, c.stream, c.A, k);
+    hipLaunchKernelGGL(ks_adj_end, dim3(1), dim3(64), 0, c.stream, c.A, c.C, k);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(a->ctl_h, a->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, c.stream));
     HIP_TRY(hipStreamSynchronize(c.stream));
@@ -292,9 +293,9 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
             return fail(LPIDE_E_NOCONV, buf);
         }
         ++k;
-        hipLaunchKernelGGL(ks_clear_fail, dim3(1), dim3(64), 0, c.stream, c.A, 0);
+        hipLaunchKernelGGL(ks_clear_fail, dim3(1), dim3(64), 0, c.stream, c.C, 0);
         launch_adj_iteration<L>(c, k);
-        hipLaunchKernelGGL(ks_adj_end, dim3(1), dim3(64), 0, c.stream, c.A, k);
+        hipLaunchKernelGGL(ks_adj_end, dim3(1), dim3(64), 0, c.stream, c.A, c.C, k);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipMemcpyAsync(a->ctl_h, a->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, c.stream));
         HIP_TRY(hipStreamSynchronize(c.stream));
@@ -317,7 +318,7 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
         }
         a->corr[0] = oldest;
     }
-    hipLaunchKernelGGL(ks_adj_corr, dim3(sb), dim3(256), 0, c.stream, c.A, a->corr[0]);
+    hipLaunchKernelGGL(ks_adj_corr, dim3(sb), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, a->corr[0]);
     a->have_corr = std::min(4, a->have_corr + 1);
     a->corr_c[0] = cth;
     // mu = (T^SL)^T lam (its row transform also into XC for the spectral
@@ -327,24 +328,24 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
     const bool narrow = sd.wt1 <= 8 && sd.wt2 <= 8;
     with_E<L>(c.E_sl, [&](auto e) {
         constexpr int E = decltype(e)::value;
-        if (narrow) hipLaunchKernelGGL((ks_adj_sl<L, E, 8>), gr, dim3(L / E), 0, c.stream, c.A, x2);
-        else hipLaunchKernelGGL((ks_adj_sl<L, E, 0>), gr, dim3(L / E), 0, c.stream, c.A, x2);
+        if (narrow) hipLaunchKernelGGL((ks_adj_sl<L, E, 8>), gr, dim3(L / E), 0, c.stream, c.A, (const Ctl*)c.C, x2);
+        else hipLaunchKernelGGL((ks_adj_sl<L, E, 0>), gr, dim3(L / E), 0, c.stream, c.A, (const Ctl*)c.C, x2);
     });
     if (sd.theta < 1.0) {
         with_E<L>(c.E_cols, [&](auto e) {
             constexpr int E = decltype(e)::value;
-            hipLaunchKernelGGL((ks_cols<L, E, double2, true>), dim3(L / 2, 1), dim3(L / E), 0, c.stream, c.A, 0);
+            hipLaunchKernelGGL((ks_cols<L, E, double2, true>), dim3(L / 2, 1), dim3(L / E), 0, c.stream, c.A, c.C, 0);
         });
         with_E<L>(c.E_rinv, [&](auto e) {
             constexpr int E = decltype(e)::value;
-            hipLaunchKernelGGL((ks_rows_inv<L, E, 4>), gr, dim3(L / E), 0, c.stream, c.A, 0);
+            hipLaunchKernelGGL((ks_rows_inv<L, E, 4>), gr, dim3(L / E), 0, c.stream, c.A, c.C, 0);
         });
     }
     // gradient terms (they read lam and mu; the new cotangent is written last)
     if (p->hp.sl_order == 1)
-        hipLaunchKernelGGL(ks_adj_accum<1>, dim3(n, 1), dim3(256), 0, c.stream, c.A, Y, V, E, a->acc);
+        hipLaunchKernelGGL(ks_adj_accum<1>, dim3(n, 1), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, Y, V, E, a->acc);
     else
-        hipLaunchKernelGGL(ks_adj_accum<3>, dim3(n, 1), dim3(256), 0, c.stream, c.A, Y, V, E, a->acc);
+        hipLaunchKernelGGL(ks_adj_accum<3>, dim3(n, 1), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, Y, V, E, a->acc);
     if (p->jumps) {
         const int np = (n + 1) / 2;
         // the row transform of Y = V^{s+1} is the V transform of reverse step s + 1 when it had one;

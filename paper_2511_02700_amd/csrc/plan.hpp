@@ -41,6 +41,7 @@ struct Schedule { int cols, rinv, lrows, sl; };
 struct Launch {
     hipStream_t stream = nullptr;
     const MarchArgs* A = nullptr;   // device array, np entries
+    Ctl* C = nullptr;               // their control blocks
     int np = 0;
     int L = 0;                      // Lr of the plans (transform side of the row kernels)
     int xrows = 0;                  // max row pairs

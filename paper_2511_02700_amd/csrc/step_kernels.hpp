@@ -44,29 +44,6 @@ constexpr int NX = 8;                 // stopping-rule partial maxima per iterat
 constexpr int MAX_ITER_CAP = 128;
 constexpr int POOL = 6;               // grid buffers: history (4) + start state + iterate
 
-struct Ctl {
-    int step;                         // completed entries of the step list
-    int fail;                         // current step not converged within its launched iterations
-    int fail_step;
-    int hold;                         // set by the host while another plan of the group is being completed
-    int cur;                          // pool index of the state the current step starts from
-    int y;                            // pool index of the iterate
-    int hc;                           // history length (main steps)
-    int nsrc;                         // terms of the starting-value combination
-    int hist[4];                      // pool indices, newest first
-    int bvalid;                       // bit b: bpool[b] holds B applied to pool[b] (this march)
-    int w;                            // SL buffer of this step (the step before wrote the other one)
-    int src[4];
-    double coef[4];                   // Y^0 = sum_q coef[q] pool[src[q]]; past nsrc,
-                                      // src[q] = src[0] and coef[q] = 0 (so a loop
-                                      // over all four terms gives the same sums)
-    // stopping-rule value after iteration k: the maximum over x of err[x][k]
-    // (bit patterns of non-negative doubles).  The row blocks of the line-solve
-    // kernel reduce into the partial of their XCD, so the atomics of one launch
-    // go to eight cache lines instead of one (they are serialised per line).
-    unsigned long long err[NX][KSLOTS];
-};
-
 struct StepDesc {
     double theta, dt;
     const double *fl1, *bu1, *bc1;    // axis-1 line factors of I - dt theta A_1
@@ -82,13 +59,55 @@ struct StepDesc {
     const double *w1d, *w2d;
 };
 
+// What the kernels of one step need, resolved from the step list and the pool
+// bookkeeping by the kernel that starts the step (ks_init, ks_step_end,
+// ks_adj_begin), so that every kernel reads it in one go instead of following
+// step -> set -> pointer through memory.
+struct StepNow {
+    int lin;                          // B Y^0 by linearity: every source of the start value has its product stored
+    int expl;                         // explicit part E: EXPL_NONE, EXPL_IDENTITY, EXPL_CORR
+    int anchor;                       // mixed form: B V^{n-1} afresh by the FP64 correlation
+    int set;                          // index of the step's set
+    double cth, cex, rho;             // dt theta, dt (1 - theta), rho of the identity
+    const double* V;                  // state the step starts from
+    double *Y, *W, *Wp;               // iterate, SL output, SL output of the step before (takes E where E is formed apart)
+    double* B;                        // store of B applied to the iterate (or null)
+    const double *H[4], *Hb[4];       // sources of the start value and their stored products
+    double coef[4];                   // Y^0 = sum_q coef[q] H[q]; past the count of sources H[0] at weight 0
+                                      // (so a loop over all four terms gives the same sums)
+    const double *fl1, *bu1, *bc1, *fl2, *bu2, *bc2;
+    const int *s1, *s2;
+    const double *w1, *w2;
+};
+constexpr int EXPL_NONE = 0, EXPL_IDENTITY = 1, EXPL_CORR = 2;
+
+struct Ctl {
+    int step;                         // completed entries of the step list
+    int fail;                         // current step not converged within its launched iterations
+    int fail_step;
+    int hold;                         // set by the host while another plan of the group is being completed
+    StepNow now;                      // the current step (valid while step < nsteps)
+    int cur;                          // pool index of the state the current step starts from
+    int y;                            // pool index of the iterate
+    int hc;                           // history length (main steps)
+    int nsrc;                         // terms of the starting-value combination
+    int hist[4];                      // pool indices, newest first
+    int bvalid;                       // bit b: bpool[b] holds B applied to pool[b] (this march)
+    int w;                            // SL buffer of this step (the step before wrote the other one)
+    int src[4];                       // pool indices of the start value's sources
+    // stopping-rule value after iteration k: the maximum over x of err[x][k]
+    // (bit patterns of non-negative doubles).  The row blocks of the line-solve
+    // kernel reduce into the partial of their XCD, so the atomics of one launch
+    // go to eight cache lines instead of one (they are serialised per line).
+    unsigned long long err[NX][KSLOTS];
+};
+
 struct MarchArgs {
-    Ctl* ctl;
     double* pool[POOL];
     const StepDesc* sets;
     const int* step_set;
     int n, n_sub, damping, P_cols;
-    double* Wb[2];                    // SL outputs W of this step and of the one before it (wcur, wprev)
+    double* Wb[2];                    // SL outputs W of a step and of the one before it, in turn
     double* R;
     double2* X;
     const double2* spec;
@@ -113,20 +132,17 @@ struct MarchArgs {
     double* bpool[POOL];              // B applied to the pool grids (FP64 form; bpool[0] null: off)
 };
 
-template <typename C> __device__ __forceinline__ C* xbuf(const MarchArgs& a);
-template <> __device__ __forceinline__ double2* xbuf<double2>(const MarchArgs& a) { return a.X; }
-template <> __device__ __forceinline__ float2* xbuf<float2>(const MarchArgs& a) { return a.X32; }
-template <typename C> __device__ __forceinline__ const C* specbuf(const MarchArgs& a);
-template <> __device__ __forceinline__ const double2* specbuf<double2>(const MarchArgs& a) { return a.spec; }
-template <> __device__ __forceinline__ const float2* specbuf<float2>(const MarchArgs& a) { return a.spec32; }
+using Args = const LPIDE_CONST MarchArgs;      // the plan's arguments and its control block, as every
+using CtlK = const LPIDE_CONST Ctl;            // kernel but the controlling ones reads them (KRef)
 
 __device__ __forceinline__ double bits_to_d(unsigned long long b) { return __longlong_as_double((long long)b); }
 
 // Stopping-rule value after iteration k (maximum of the partials).
-__device__ __forceinline__ double err_max(const Ctl* c, int k) {
-    unsigned long long m = c->err[0][k];
+template <typename C>
+__device__ __forceinline__ double err_max(C& c, int k) {
+    unsigned long long m = c.err[0][k];
 #pragma unroll
-    for (int x = 1; x < NX; ++x) m = c->err[x][k] > m ? c->err[x][k] : m;
+    for (int x = 1; x < NX; ++x) m = c.err[x][k] > m ? c.err[x][k] : m;
     return bits_to_d(m);
 }
 
@@ -145,31 +161,39 @@ __device__ __forceinline__ void err_reset_upto(Ctl* c, int kmax) {
 }
 
 // Uniform early-exit test of iteration k (k = 0: parts that run once per step).
-__device__ __forceinline__ bool halted(const MarchArgs& a, int k) {
-    const Ctl* c = a.ctl;
-    if (c->fail || c->hold || c->step >= a.nsteps) return true;
-    return k > 0 && err_max(c, k - 1) < a.tol;
+// No read waits for another's test (the partial maxima are compared one by one,
+// as bit patterns: a NaN lies above every tol), so all are in flight together.
+__device__ __forceinline__ bool halted(Args& a, CtlK& c, int k) {
+    const int kp = k > 0 ? k - 1 : 0;            // err[.][0] is the sentinel: never below tol
+    unsigned long long e[NX];
+#pragma unroll
+    for (int x = 0; x < NX; ++x) e[x] = c.err[x][kp];
+    const int off = c.fail | c.hold, left = a.nsteps - c.step;
+    const unsigned long long tol = (unsigned long long)__double_as_longlong(a.tol);
+    int open = 0;                                // partials that have not met tol
+#pragma unroll
+    for (int x = 0; x < NX; ++x) open |= e[x] >= tol ? 1 : 0;
+    return off != 0 || left <= 0 || open == 0;
 }
 
-// The explicit part (and the FP64 correlation of V^{n-1}) is needed when
-// theta < 1, and in every step of the mixed form.
-__device__ __forceinline__ bool needs_explicit(const MarchArgs& a);
+// The plan and the control block of this thread block.
+__device__ __forceinline__ Args& plan_args(const MarchArgs* A) { return kref(A + blockIdx.y); }
+__device__ __forceinline__ CtlK& plan_ctl(const Ctl* C) { return kref(C + blockIdx.y); }
 
-__device__ __forceinline__ const StepDesc& cur_set(const MarchArgs& a) { return a.sets[a.step_set[a.ctl->step]]; }
-
-__device__ __forceinline__ bool needs_explicit(const MarchArgs& a) { return a.mixed || cur_set(a).theta < 1.0; }
-
-// Mixed form: the steps whose B V^{n-1} is computed afresh by the FP64
-// correlation (every anchor_every-th step of the march, its first step
-// included).  In the others B V^{n-1} is carried from the previous step: its
-// last accumulated B Y, still in BY when the step's first iteration adds to it.
-__device__ __forceinline__ bool is_anchor(const MarchArgs& a) {
-    return (a.ctl->step - a.step0) % a.anchor_every == 0;
+__device__ __forceinline__ StencilArgs stencil(Args& a) {
+    return StencilArgs{a.st.n, a.st.h, a.st.a11, a.st.a12, a.st.a22};
 }
 
-// Explicit part of a step from the implicit equation of the step before it.
-// That step solved (I - c A) V^{n-1} = W (c = dt theta of that step, W still
-// in wprev), so A V^{n-1} = (V^{n-1} - W) / c and
+template <typename C> __device__ __forceinline__ GP<C> xbuf(Args& a);
+template <> __device__ __forceinline__ GP<double2> xbuf<double2>(Args& a) { return GP<double2>(a.X); }
+template <> __device__ __forceinline__ GP<float2> xbuf<float2>(Args& a) { return GP<float2>(a.X32); }
+template <typename C> __device__ __forceinline__ GP<C> specbuf(Args& a);
+template <> __device__ __forceinline__ GP<double2> specbuf<double2>(Args& a) { return GP<double2>(a.spec); }
+template <> __device__ __forceinline__ GP<float2> specbuf<float2>(Args& a) { return GP<float2>(a.spec32); }
+
+// Explicit part of a step from the implicit equation of the step before it
+// (EXPL_IDENTITY).  That step solved (I - c A) V^{n-1} = W (c = dt theta of that
+// step, W still in now.Wp), so A V^{n-1} = (V^{n-1} - W) / c and
 //   E = V^{n-1} + dt (1 - theta) A V^{n-1} = V^{n-1} + rho (V^{n-1} - W),
 // rho = dt (1 - theta) / c: the same explicit part without applying B, exact
 // at the fixed point (the converged iterate leaves the stopping-rule residual).
@@ -177,86 +201,170 @@ __device__ __forceinline__ bool is_anchor(const MarchArgs& a) {
 // theta > 0 (cn_rho > 0, set by the host; null with every product by the
 // correlation and in the adjoint march); in the mixed form outside its anchor
 // steps, whose FP64 correlation forms the explicit part.
-__device__ __forceinline__ bool explicit_by_identity(const MarchArgs& a) {
-    return a.cn_rho && a.ctl->step > a.step0 && a.cn_rho[a.ctl->step] > 0.0;
-}
-
-// B Y^0 of the first iteration by linearity: Y^0 = sum_q coef_q V^{src_q}, so
+//
+// B Y^0 of the first iteration by linearity (lin): Y^0 = sum_q coef_q V^{src_q}, so
 // B Y^0 = sum_q coef_q B V^{src_q}, with B V^{src_q} stored by the row kernel of
 // the step that produced V^{src_q} (B applied to its last iterate before the
 // final update, so B V^{src_q} is off by B of an increment below the stopping
 // tolerance; the first iteration only sets where the iteration starts, its
 // fixed point is unchanged).  Needs every source grid from this march.
-__device__ __forceinline__ bool start_by_linearity(const MarchArgs& a) {
-    if (!a.bpool[0]) return false;
-    const Ctl* c = a.ctl;
-    bool ok = true;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (q < c->nsrc) ok = ok && ((c->bvalid >> c->src[q]) & 1);
-    return ok;
+//
+// Mixed form: the steps whose B V^{n-1} is computed afresh by the FP64
+// correlation (anchor: every anchor_every-th step of the march, its first step
+// included).  In the others B V^{n-1} is carried from the previous step: its
+// last accumulated B Y, still in BY when the step's first iteration adds to it.
+
+// Fill c->now for step c->step (below nsteps) from the pool bookkeeping and the
+// step's set sd (index id); cn: cn_rho of the step.  One thread.
+__device__ __forceinline__ void step_setup(Args& a, Ctl* c, const StepDesc& sd, int id, double cn) {
+    StepNow& w = c->now;
+    const double rho = a.cn_rho && c->step > a.step0 ? cn : 0.0;
+    w.set = id;
+    w.cth = sd.dt * sd.theta;
+    w.cex = sd.dt * (1.0 - sd.theta);
+    w.rho = rho;
+    w.expl = sd.theta >= 1.0 ? EXPL_NONE : (rho > 0.0 ? EXPL_IDENTITY : EXPL_CORR);
+    w.anchor = a.mixed && (c->step - a.step0) % a.anchor_every == 0;
+    w.V = a.pool[c->cur];
+    w.Y = a.pool[c->y];
+    w.W = a.Wb[c->w];
+    w.Wp = a.Wb[c->w ^ 1];
+    w.B = a.bpool[c->y];
+    bool lin = a.bpool[0] != nullptr;
+    for (int q = 0; q < 4; ++q) {
+        const int b = c->src[q < c->nsrc ? q : 0];
+        if (q < c->nsrc) lin = lin && ((c->bvalid >> b) & 1);
+        else w.coef[q] = 0.0;
+        w.H[q] = a.pool[b];
+        w.Hb[q] = a.bpool[b];
+    }
+    w.lin = lin;
+    w.fl1 = sd.fl1; w.bu1 = sd.bu1; w.bc1 = sd.bc1;
+    w.fl2 = sd.fl2; w.bu2 = sd.bu2; w.bc2 = sd.bc2;
+    w.s1 = sd.s1; w.s2 = sd.s2; w.w1 = sd.w1; w.w2 = sd.w2;
 }
 
 // Whether the step runs the FP64 correlation of V^{n-1}: for the explicit part
 // (theta < 1, unless it comes from the previous step's equation), or to anchor
 // B V^{n-1} in the mixed form.
-__device__ __forceinline__ bool needs_explicit_fft(const MarchArgs& a) {
-    return a.mixed ? is_anchor(a) : (cur_set(a).theta < 1.0 && !explicit_by_identity(a));
+__device__ __forceinline__ bool needs_explicit_fft(Args& a, CtlK& c) {
+    return a.mixed ? c.now.anchor != 0 : c.now.expl == EXPL_CORR;
 }
-
-// The SL output of this step, and that of the step before it; the latter takes
-// the explicit part E of a step whose E is formed by a kernel of its own
-// (the index made scalar: the pointer is then a scalar too).
-__device__ __forceinline__ double* wcur(const MarchArgs& a) { return a.Wb[__builtin_amdgcn_readfirstlane(a.ctl->w)]; }
-__device__ __forceinline__ double* wprev(const MarchArgs& a) {
-    return a.Wb[__builtin_amdgcn_readfirstlane(a.ctl->w) ^ 1];
-}
-
-// The plan of this block.
-__device__ __forceinline__ const MarchArgs& plan_args(const MarchArgs* __restrict__ A) { return A[blockIdx.y]; }
 
 // Column pass of the correlation on the intermediate X (transposed half
-// spectra), FP64 (C = double2) or FP32 (C = float2); L/2 blocks for the
-// L/2 + 1 columns.  Columns 0 (DC) and L/2 (Nyquist) hold real values (the row
-// transforms of real rows; the row c2r kernels read only their real parts), so
-// block 0 filters both as one complex column (mul_real_pair): a launch of
-// L/2 + 1 blocks would end with one block running alone after the last full
-// set of resident blocks had finished.
+// spectra); L/2 blocks for the L/2 + 1 columns.  Columns 0 (DC) and L/2 (Nyquist)
+// hold real values (the row transforms of real rows; the row c2r kernels read
+// only their real parts), so block 0 filters both as one complex column
+// (mul_real_pair): a launch of L/2 + 1 blocks would end with one block running
+// alone after the last full set of resident blocks had finished.
+//
+// FP64: the spectrum is read after the forward transform; held in registers
+// from the start it costs the 3072-point pass (E = 4) its second block per CU
+// (45 -> 60 us at 2048^2).  FP32, half the registers: fetched up front.
 // CONJ (adjoint march): multiply by the conjugate spectrum, which applies B^T
 // (the correlation with the reflected kernel).
 template <int L, int E, typename C, bool CONJ = false>
-__global__ __launch_bounds__(L / E) void ks_cols(const MarchArgs* __restrict__ A, int k) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, k) || (k == 0 && !needs_explicit_fft(a)) || (k == 1 && start_by_linearity(a))) return;
+__global__ __launch_bounds__(L / E) void ks_cols(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs, int k) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, k) || (k == 0 && !needs_explicit_fft(a, c)) || (k == 1 && c.now.lin)) return;
     constexpr int T = L / E;
     __shared__ C lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, E>()];
-    load_twiddles<L, E>(a.tw, tw4);
+    load_twiddles<L, E>(GP<double2>(a.tw), tw4);
     const int n = a.n, col = blockIdx.x, tid = threadIdx.x;
     C reg[E];
     if (col == 0) {
-        C* x0 = xbuf<C>(a);
-        C* xh = x0 + (size_t)(L / 2) * n;
+        const GP<C> x0 = xbuf<C>(a), xh(x0, (size_t)(L / 2) * n);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int idx = tid + e * T;
             reg[e] = idx < n ? CplxOps<C>::make(x0[idx].x, xh[idx].x) : CplxOps<C>::make(0, 0);
         }
         fft_block<L, E, false>(reg, lds, tw4);
-        mul_real_pair<L, E, CONJ>(reg, lds, specbuf<C>(a), specbuf<C>(a) + (size_t)(L / 2) * L);
+        const GP<C> s0 = specbuf<C>(a);
+        mul_real_pair<L, E, CONJ>(reg, lds, s0, GP<C>(s0, (size_t)(L / 2) * L));
         fft_block<L, E, true>(reg, lds, tw4);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int idx = tid + e * T;
             if (idx < n) {
-                x0[idx] = CplxOps<C>::make(reg[e].x, 0);
-                xh[idx] = CplxOps<C>::make(reg[e].y, 0);
+                x0.put(idx, CplxOps<C>::make(reg[e].x, 0));
+                xh.put(idx, CplxOps<C>::make(reg[e].y, 0));
             }
         }
         return;
     }
-    C* xc = xbuf<C>(a) + (size_t)col * n;
-    const C* sc = specbuf<C>(a) + (size_t)col * L;
+    const GP<C> xc(xbuf<C>(a), (size_t)col * n), sc(specbuf<C>(a), (size_t)col * L);
+    if constexpr (sizeof(C) == sizeof(float2)) {
+        C sp[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int idx = tid + e * T;
+            reg[e] = idx < n ? xc[idx] : CplxOps<C>::make(0, 0);
+            sp[e] = sc[idx];              // spectrum fetched up front, used after the forward FFT
+        }
+        fft_block<L, E, false>(reg, lds, tw4);
+#pragma unroll
+        for (int e = 0; e < E; ++e) reg[e] = CONJ ? cmulc(reg[e], sp[e]) : cmul(reg[e], sp[e]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int idx = tid + e * T;
+            reg[e] = idx < n ? xc[idx] : CplxOps<C>::make(0, 0);
+        }
+        fft_block<L, E, false>(reg, lds, tw4);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const C sv = sc[tid + e * T];
+            reg[e] = CONJ ? cmulc(reg[e], sv) : cmul(reg[e], sv);
+        }
+    }
+    fft_block<L, E, true>(reg, lds, tw4);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int idx = tid + e * T;
+        if (idx < n) xc.put(idx, reg[e]);
+    }
+}
+
+// The FP64 pass of the mixed form's anchor steps, its spectrum fetched up front.
+// A kernel of its own because the FP32 increments answer any change of the
+// rounding here with differences of their own size (2e-9 of the deltas).
+template <int L, int E>
+__global__ __launch_bounds__(L / E) void ks_cols_anchor(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs) {
+    using C = double2;
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0) || !c.now.anchor) return;
+    constexpr int T = L / E;
+    __shared__ C lds[lds_slots(L)];
+    __shared__ double2 tw4[tw_slots<L, E>()];
+    load_twiddles<L, E>(GP<double2>(a.tw), tw4);
+    const int n = a.n, col = blockIdx.x, tid = threadIdx.x;
+    C reg[E];
+    if (col == 0) {
+        const GP<C> x0 = xbuf<C>(a), xh(x0, (size_t)(L / 2) * n);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int idx = tid + e * T;
+            reg[e] = idx < n ? CplxOps<C>::make(x0[idx].x, xh[idx].x) : CplxOps<C>::make(0, 0);
+        }
+        fft_block<L, E, false>(reg, lds, tw4);
+        const GP<C> s0 = specbuf<C>(a);
+        mul_real_pair<L, E, false>(reg, lds, s0, GP<C>(s0, (size_t)(L / 2) * L));
+        fft_block<L, E, true>(reg, lds, tw4);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int idx = tid + e * T;
+            if (idx < n) {
+                x0.put(idx, CplxOps<C>::make(reg[e].x, 0));
+                xh.put(idx, CplxOps<C>::make(reg[e].y, 0));
+            }
+        }
+        return;
+    }
+    const GP<C> xc(xbuf<C>(a), (size_t)col * n), sc(specbuf<C>(a), (size_t)col * L);
     C sp[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -266,19 +374,19 @@ __global__ __launch_bounds__(L / E) void ks_cols(const MarchArgs* __restrict__ A
     }
     fft_block<L, E, false>(reg, lds, tw4);
 #pragma unroll
-    for (int e = 0; e < E; ++e) reg[e] = CONJ ? cmulc(reg[e], sp[e]) : cmul(reg[e], sp[e]);
+    for (int e = 0; e < E; ++e) reg[e] = cmul(reg[e], sp[e]);
     fft_block<L, E, true>(reg, lds, tw4);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int idx = tid + e * T;
-        if (idx < n) xc[idx] = reg[e];
+        if (idx < n) xc.put(idx, reg[e]);
     }
 }
 
 // Forward FFT of the row pair (ra, ra+1) of the FP64 grid U at the step start
 // (mixed form: the FP64 correlation of V^{n-1}).
 template <int L, int E>
-__global__ __launch_bounds__(L / E) void ks_rows_fwd(const MarchArgs* __restrict__ A);
+__global__ __launch_bounds__(L / E) void ks_rows_fwd(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs);
 
 // The packed spectrum of the row pair (ra, ra+1) from the transposed half
 // spectra, into the canonical registers: z[k] = X_a[k] + i X_b[k] for k <= L/2
@@ -288,8 +396,7 @@ __global__ __launch_bounds__(L / E) void ks_rows_fwd(const MarchArgs* __restrict
 // values, the even lane forms z[k], the odd one z[L-k], and both go through LDS
 // to the canonical layout.
 template <int L, int E, typename C>
-__device__ __forceinline__ void rows_inv_gather(C (&reg)[E], C* lds, const C* __restrict__ X, int n, int ra,
-                                                bool hasb) {
+__device__ __forceinline__ void rows_inv_gather(C (&reg)[E], C* lds, GP<C> X, int n, int ra, bool hasb) {
     constexpr int T = L / E, NI = (L + 2 + T - 1) / T;
     const int tid = threadIdx.x;
 #pragma unroll
@@ -297,7 +404,7 @@ __device__ __forceinline__ void rows_inv_gather(C (&reg)[E], C* lds, const C* __
         const int idx = tid + it * T;
         const int kk = idx >> 1, r = idx & 1;
         const bool in = kk <= L / 2;
-        const C v = (in && (r == 0 || hasb)) ? X[(size_t)kk * n + ra + r] : CplxOps<C>::make(0, 0);
+        const C v = (in && (r == 0 || hasb)) ? X[kk * n + ra + r] : CplxOps<C>::make(0, 0);
         // every lane of the wave takes part in the swap (pairs never straddle the range end)
         const C u = CplxOps<C>::make(__shfl_xor(v.x, 1), __shfl_xor(v.y, 1));
         const bool real_bin = kk == 0 || kk == L / 2;
@@ -326,10 +433,12 @@ __device__ __forceinline__ void rows_inv_gather(C (&reg)[E], C* lds, const C* __
 // MODE 4 (once per step, theta < 1): W = mu + dt (1 - theta)((D^T - r_omega) mu + B^T mu),
 //         mu in pool[cur]: the cotangent of V^{n-1}.
 template <int L, int E, int MODE>
-__global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict__ A, int k) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, k) || ((MODE == 0 || MODE == 4) && !needs_explicit_fft(a)) ||
-        (MODE == 1 && k == 1 && start_by_linearity(a)))   // ks_begin_lin ran instead
+__global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict__ A,
+                                                     const Ctl* __restrict__ Cs, int k) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, k) || ((MODE == 0 || MODE == 4) && !needs_explicit_fft(a, c)) ||
+        (MODE == 1 && k == 1 && c.now.lin))               // ks_begin_lin ran instead
         return;
     using C = typename std::conditional<MODE == 2, float2, double2>::type;
     constexpr int T = L / E;
@@ -338,34 +447,25 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
     if (p >= np) return;
     __shared__ C lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, E>()];
-    load_twiddles<L, E>(a.tw, tw4);
+    load_twiddles<L, E>(GP<double2>(a.tw), tw4);
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
     const int tid = threadIdx.x;
-    const C* X = xbuf<C>(a);
     C reg[E];
-    rows_inv_gather<L, E>(reg, lds, X, n, ra, hasb);
+    rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
     fft_block<L, E, true>(reg, lds, tw4);
-    // FP64 iterations store B Y of the iterate for the start of later steps
-    double* Bout = nullptr;
-    if constexpr (MODE == 1) {
-        if (a.bpool[0]) Bout = a.bpool[a.ctl->y];
-    }
-    const StepDesc& sd = cur_set(a);
     constexpr bool EXPL = MODE == 0 || MODE == 4;
-    const double* U = EXPL ? a.pool[a.ctl->cur] : a.pool[a.ctl->y];
-    const double* P0 = EXPL ? U : wcur(a);
-    double* out = MODE == 4 ? wcur(a) : (MODE == 0 ? wprev(a) : a.R);
-    const double c = EXPL ? sd.dt * (1.0 - sd.theta) : sd.dt * sd.theta;
-    const double c0 = EXPL ? 0.0 : -1.0;
-    const bool want_r = MODE != 0 || sd.theta < 1.0;
-    const double* base = (MODE == 2 && k == 1 && is_anchor(a)) ? a.BV : a.BY;
-    // the arguments the loop needs, read once: the stores below go through
-    // plain pointers, after which every field of a would be read again
-    const StencilArgs st = a.st;
+    // FP64 iterations store B Y of the iterate for the start of later steps
+    const bool keepB = MODE == 1 && c.now.B != nullptr;
+    const GP<double> Bout(c.now.B);
+    const GP<double> U(EXPL ? c.now.V : c.now.Y), P0(EXPL ? c.now.V : c.now.W);
+    const GP<double> out(MODE == 4 ? c.now.W : (MODE == 0 ? c.now.Wp : a.R));
+    const double cf = EXPL ? c.now.cex : c.now.cth, c0 = EXPL ? 0.0 : -1.0;
+    const bool want_r = MODE != 0 || c.now.expl != EXPL_NONE;
+    const GP<double> base((MODE == 2 && k == 1 && c.now.anchor) ? a.BV : a.BY), BY(a.BY), BV(a.BV);
+    const bool mixed = a.mixed != 0;
+    const StencilArgs st = stencil(a);
     const double r_omega = a.r_omega;
-    double* const BY = a.BY;
-    double* const BV = a.mixed ? a.BV : nullptr;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int j = tid + e * T;
@@ -373,23 +473,22 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             if (r == 1 && !hasb) break;
-            const int i = ra + r;
-            const size_t o = (size_t)i * n + j;
+            const int i = ra + r, o = i * n + j;
             double bu = r == 0 ? (double)reg[e].x : (double)reg[e].y;
             if constexpr (MODE == 1) {
-                if (Bout) Bout[o] = bu;
+                if (keepB) Bout.put(o, bu);
             }
             if constexpr (MODE == 2) {
                 bu += base[o];
-                BY[o] = bu;
+                BY.put(o, bu);
             }
             if constexpr (MODE == 0) {
-                if (BV) BV[o] = bu;
+                if (mixed) BV.put(o, bu);
             }
             if (want_r) {
                 const double u = U[o];
                 const double d = MODE >= 3 ? apply_DT(U, st, i, j, u) : apply_D(U, st, i, j, u);
-                out[o] = P0[o] + c * (d + bu - r_omega * u) + c0 * u;
+                out.put(o, P0[o] + cf * (d + bu - r_omega * u) + c0 * u);
             }
         }
     }
@@ -398,23 +497,22 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
 // The same affine forms without the correlation (zero Levy measure); one
 // block per grid row.
 template <bool EXPLICIT>
-__global__ __launch_bounds__(256) void ks_affine_noB(const MarchArgs* __restrict__ A, int k) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, k) || (EXPLICIT && !needs_explicit(a))) return;
+__global__ __launch_bounds__(256) void ks_affine_noB(const MarchArgs* __restrict__ A,
+                                                     const Ctl* __restrict__ Cs, int k) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, k) || (EXPLICIT && c.now.expl == EXPL_NONE)) return;
     const int n = a.n;
     const int i = xcd_remap(blockIdx.x, gridDim.x);   // neighbouring rows on one XCD (stencil reads share L2)
     if (i >= n) return;
-    const StepDesc& sd = cur_set(a);
-    const double* U = EXPLICIT ? a.pool[a.ctl->cur] : a.pool[a.ctl->y];
-    const double* P0 = EXPLICIT ? U : wcur(a);
-    double* out = EXPLICIT ? wprev(a) : a.R;
-    const double c = EXPLICIT ? sd.dt * (1.0 - sd.theta) : sd.dt * sd.theta;
-    const double c0 = EXPLICIT ? 0.0 : -1.0;
+    const GP<double> U(EXPLICIT ? c.now.V : c.now.Y), P0(EXPLICIT ? c.now.V : c.now.W), out(EXPLICIT ? c.now.Wp : a.R);
+    const double cf = EXPLICIT ? c.now.cex : c.now.cth, c0 = EXPLICIT ? 0.0 : -1.0, r_omega = a.r_omega;
+    const StencilArgs st = stencil(a);
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
-        const size_t o = (size_t)i * n + j;
+        const int o = i * n + j;
         const double u = U[o];
-        const double d = apply_D(U, a.st, i, j, u);
-        out[o] = P0[o] + c * (d - a.r_omega * u) + c0 * u;
+        const double d = apply_D(U, st, i, j, u);
+        out.put(o, P0[o] + cf * (d - r_omega * u) + c0 * u);
     }
 }
 
@@ -425,38 +523,38 @@ __global__ __launch_bounds__(256) void ks_affine_noB(const MarchArgs* __restrict
 // which is below the stopping tolerance), and the explicit part
 // E = V + dt (1 - theta)((D - r_omega) V + B V) (theta < 1) is formed without
 // a correlation.  One block per grid row.
-static __global__ __launch_bounds__(256) void ks_carry(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0) || !a.mixed || is_anchor(a) || explicit_by_identity(a) || cur_set(a).theta >= 1.0) return;
+static __global__ __launch_bounds__(256) void ks_carry(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0) || !a.mixed || c.now.anchor || c.now.expl != EXPL_CORR) return;
     const int n = a.n;
     const int i = xcd_remap(blockIdx.x, gridDim.x);   // neighbouring rows on one XCD (stencil reads share L2)
     if (i >= n) return;
-    const StepDesc& sd = cur_set(a);
-    const double* U = a.pool[a.ctl->cur];
-    const double c = sd.dt * (1.0 - sd.theta);
-    double* E = wprev(a);
+    const GP<double> U(c.now.V), E(c.now.Wp), BY(a.BY);
+    const double cf = c.now.cex, r_omega = a.r_omega;
+    const StencilArgs st = stencil(a);
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
-        const size_t o = (size_t)i * n + j;
+        const int o = i * n + j;
         const double u = U[o];
-        E[o] = u + c * (apply_D(U, a.st, i, j, u) + a.BY[o] - a.r_omega * u);
+        E.put(o, u + cf * (apply_D(U, st, i, j, u) + BY[o] - r_omega * u));
     }
 }
 
-// Explicit part from the previous step's implicit equation (explicit_by_identity),
-// over the W it comes from: E = V + rho (V - W); one block per grid row.  Mixed
-// form: not in anchor steps.  Steps that ks_begin_lin takes form it there.
-static __global__ __launch_bounds__(256) void ks_expl_identity(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0) || !explicit_by_identity(a) || (a.mixed && is_anchor(a)) || start_by_linearity(a)) return;
-    const int n = a.n;
-    const int i = blockIdx.x;
+// Explicit part from the previous step's implicit equation (EXPL_IDENTITY), over
+// the W it comes from: E = V + rho (V - W); one block per grid row.  Mixed form:
+// not in anchor steps.  Steps that ks_begin_lin takes form it there.
+static __global__ __launch_bounds__(256) void ks_expl_identity(const MarchArgs* __restrict__ A,
+                                                               const Ctl* __restrict__ Cs) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0) || c.now.expl != EXPL_IDENTITY || c.now.anchor || c.now.lin) return;
+    const int n = a.n, i = blockIdx.x;
     if (i >= n) return;
-    const double rho = a.cn_rho[a.ctl->step];
-    const double* V = a.pool[a.ctl->cur] + (size_t)i * n;
-    double* W = wprev(a) + (size_t)i * n;
+    const double rho = c.now.rho;
+    const GP<double> V(c.now.V), W(c.now.Wp);
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
-        const double v = V[j];
-        W[j] = v + rho * (v - W[j]);
+        const double v = V[i * n + j];
+        W.put(i * n + j, v + rho * (v - W[i * n + j]));
     }
 }
 
@@ -475,23 +573,24 @@ __host__ __device__ __forceinline__ int begin_tiles(int n, int TR) {
     return ((n + TR - 1) / TR) * ((n + c - 1) / c);
 }
 
-// The start of an FP64 step whose B Y^0 comes by linearity (start_by_linearity),
+// The start of an FP64 step whose B Y^0 comes by linearity (StepNow::lin),
 // without any transform, on a tile of TR rows:
-//   E = V + rho (V - W_prev) (explicit_by_identity; V when theta = 1; W_prev where
-//       the correlation left E there),
+//   E = V + rho (V - W_prev) (EXPL_IDENTITY; V when theta = 1; W_prev where the
+//       correlation left E there),
 //   W = T^SL E, the row weights first, then the column taps from LDS,
 //   Y^0 = sum_q coef_q V^{src_q},  B Y^0 = sum_q coef_q B V^{src_q} (stored products),
 //   R = W + dt theta ((D - r_omega) Y^0 + B Y^0) - Y^0, the residual of iteration 1.
 // One streaming pass (13 n^2 reads and writes of FP64) in place of three kernels
-// of 3, 7 and 8 that passed E, W and Y^0 through memory: 119 us instead of 17 + 62
-// + 66 at 2048^2, 11.8 instead of 4.8 + 7.8 + 7.0 at 512^2.  A tile's start value is
+// of 3, 7 and 8 that passed E, W and Y^0 through memory: 92 us instead of 17 + 62
+// + 66 at 2048^2, 9.1 instead of 4.8 + 7.8 + 7.0 at 512^2.  A tile's start value is
 // formed once per node and halo row and its stencil reads LDS, so the history is
 // read (TR + 2) / TR times; the terms past the count of stored grids repeat the
-// first at weight zero (Ctl), so that one loop serves every count.
+// first at weight zero (StepNow), so that one loop serves every count.
 template <int P, int TR>
-__global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0) || !start_by_linearity(a)) return;
+__global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0) || !c.now.lin) return;
     constexpr int T = BEGIN_T, NS = 4;
     __shared__ double ys[TR + 2][T];              // Y^0, rows r0 - 1 .., columns c0 - 1 ..
     __shared__ double ec[TR][T];                  // row-combined E, columns k0 ..
@@ -499,32 +598,22 @@ __global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restr
     if ((int)blockIdx.x >= nt) return;
     const int tile = xcd_remap(blockIdx.x, nt);   // neighbouring tiles on one XCD (halo rows share L2)
     const int r0 = (tile / tc) * TR, c0 = (tile % tc) * tcw, c1 = min(n, c0 + tcw), t = threadIdx.x;
-    const Ctl* c = a.ctl;
-    const StepDesc& sd = cur_set(a);
-    const double* __restrict__ V = a.pool[c->cur];
-    const double* __restrict__ Wp = wprev(a);
-    double* __restrict__ W = wcur(a);
-    double* __restrict__ Y = a.pool[c->y];
-    double* __restrict__ R = a.R;
-    double* __restrict__ Bout = a.bpool[c->y];
-    const double* __restrict__ H[NS];
-    const double* __restrict__ Hb[NS];
+    const GP<double> V(c.now.V), Wp(c.now.Wp), W(c.now.W), Y(c.now.Y), R(a.R), Bout(c.now.B), w1(c.now.w1), w2t(c.now.w2);
+    const GP<int> s1(c.now.s1), s2(c.now.s2);
+    const GP<double> H[NS] = {GP<double>(c.now.H[0]), GP<double>(c.now.H[1]), GP<double>(c.now.H[2]),
+                              GP<double>(c.now.H[3])};
+    const GP<double> Hb[NS] = {GP<double>(c.now.Hb[0]), GP<double>(c.now.Hb[1]), GP<double>(c.now.Hb[2]),
+                               GP<double>(c.now.Hb[3])};
     double cf[NS];
 #pragma unroll
-    for (int q = 0; q < NS; ++q) {
-        H[q] = a.pool[c->src[q]];
-        Hb[q] = a.bpool[c->src[q]];
-        cf[q] = c->coef[q];
-    }
-    const double cth = sd.dt * sd.theta, r_omega = a.r_omega;
-    const StencilArgs st = a.st;
-    // E of a node: 0 V, 1 the identity, 2 already in Wp
-    const int emode = sd.theta >= 1.0 ? 0 : (explicit_by_identity(a) ? 1 : 2);
-    const double rho = emode == 1 ? a.cn_rho[c->step] : 0.0;
-    auto e_at = [&](size_t o) -> double {
-        if (emode == 2) return Wp[o];
+    for (int q = 0; q < NS; ++q) cf[q] = c.now.coef[q];
+    const double cth = c.now.cth, r_omega = a.r_omega, rho = c.now.rho;
+    const int expl = c.now.expl;
+    const StencilArgs st = stencil(a);
+    auto e_at = [&](int o) -> double {
+        if (expl == EXPL_CORR) return Wp[o];
         const double v = V[o];
-        return emode == 1 ? v + rho * (v - Wp[o]) : v;
+        return expl == EXPL_IDENTITY ? v + rho * (v - Wp[o]) : v;
     };
     // start value of this thread's column, its rows and the two around them
     double y[TR + 2];
@@ -532,7 +621,7 @@ __global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restr
         const int j = min(max(c0 - 1 + t, 0), n - 1);
 #pragma unroll
         for (int q = 0; q < TR + 2; ++q) {
-            const size_t o = (size_t)min(max(r0 - 1 + q, 0), n - 1) * n + j;
+            const int o = min(max(r0 - 1 + q, 0), n - 1) * n + j;
             double v = cf[0] * H[0][o];
 #pragma unroll
             for (int h = 1; h < NS; ++h) v += cf[h] * H[h][o];
@@ -542,28 +631,27 @@ __global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restr
     }
     // E's source rows combined by the row weights.  Away from the grid's ends the
     // source rows of consecutive rows are consecutive (one set of reads per tile).
-    const int k0 = sd.s2[c0], k = k0 + t;
-    if (k <= sd.s2[c1 - 1] + P) {
-        const int rl = min(TR, n - r0), a0 = sd.s1[r0];
+    const int k0 = s2[c0], k = k0 + t;
+    if (k <= s2[c1 - 1] + P) {
+        const int rl = min(TR, n - r0), a0 = s1[r0];
         bool run = true;
 #pragma unroll
-        for (int r = 1; r < TR; ++r) run = run && (r >= rl || sd.s1[r0 + r] == a0 + r);
+        for (int r = 1; r < TR; ++r) run = run && (r >= rl || s1[r0 + r] == a0 + r);
         if (run) {
             double e[TR + P];
 #pragma unroll
-            for (int q = 0; q < TR + P; ++q) e[q] = e_at((size_t)min(a0 + q, n - 1) * n + k);
+            for (int q = 0; q < TR + P; ++q) e[q] = e_at(min(a0 + q, n - 1) * n + k);
 #pragma unroll
             for (int r = 0; r < TR; ++r) {
                 double v = 0.0;
 #pragma unroll
-                for (int q = 0; q <= P; ++q) v += sd.w1[(size_t)min(r0 + r, n - 1) * (P + 1) + q] * e[r + q];
+                for (int q = 0; q <= P; ++q) v += w1[min(r0 + r, n - 1) * (P + 1) + q] * e[r + q];
                 ec[r][t] = v;
             }
         } else {
             for (int r = 0; r < rl; ++r) {
                 double v = 0.0;
-                for (int q = 0; q <= P; ++q)
-                    v += sd.w1[(size_t)(r0 + r) * (P + 1) + q] * e_at((size_t)(sd.s1[r0 + r] + q) * n + k);
+                for (int q = 0; q <= P; ++q) v += w1[(r0 + r) * (P + 1) + q] * e_at((s1[r0 + r] + q) * n + k);
                 ec[r][t] = v;
             }
         }
@@ -571,16 +659,17 @@ __global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restr
     __syncthreads();
     const int j = c0 - 1 + t;
     if (t == 0 || j >= c1) return;
-    const int b0 = sd.s2[j] - k0;
+    const int b0 = s2[j] - k0;
     double w2[P + 1];
 #pragma unroll
-    for (int b = 0; b <= P; ++b) w2[b] = sd.w2[(size_t)j * (P + 1) + b];
-    double* segE = a.segE && sd.theta < 1.0 ? a.segE + (size_t)(c->step - a.seg_base) * n * n : nullptr;
+    for (int b = 0; b <= P; ++b) w2[b] = w2t[j * (P + 1) + b];
+    const bool rec = a.segE && expl != EXPL_NONE;
+    const GP<double> segE(GP<double>(a.segE), rec ? (size_t)(c.step - a.seg_base) * n * n : 0);
 #pragma unroll
     for (int r = 0; r < TR; ++r) {
         const int i = r0 + r;
         if (i >= n) break;
-        const size_t o = (size_t)i * n + j;
+        const int o = i * n + j;
         double bu = 0.0, w = 0.0;
 #pragma unroll
         for (int q = 0; q < NS; ++q) bu += cf[q] * Hb[q][o];
@@ -589,11 +678,11 @@ __global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restr
         const double u = y[r + 1];
         const double d = D_of(st, i, j, u, y[r], y[r + 2], ys[r + 1][t - 1], ys[r + 1][t + 1], ys[r][t - 1],
                               ys[r][t + 1], ys[r + 2][t - 1], ys[r + 2][t + 1]);
-        W[o] = w;
-        Y[o] = u;
-        Bout[o] = bu;
-        R[o] = w + cth * (d + bu - r_omega * u) - u;
-        if (segE) segE[o] = e_at(o);
+        W.put(o, w);
+        Y.put(o, u);
+        Bout.put(o, bu);
+        R.put(o, w + cth * (d + bu - r_omega * u) - u);
+        if (rec) segE.put(o, e_at(o));
     }
 }
 
@@ -601,8 +690,8 @@ __global__ __launch_bounds__(BEGIN_T) void ks_begin_lin(const MarchArgs* __restr
 // transposed half spectra X[k2 * n + row].
 // X2, if not null, receives a second copy.
 template <int L, int E, typename C>
-__device__ __forceinline__ void rows_fwd_store(C (&reg)[E], C* lds, const double2* tw4, C* __restrict__ X, int n,
-                                               int ra, bool hasb, C* __restrict__ X2 = nullptr) {
+__device__ __forceinline__ void rows_fwd_store(C (&reg)[E], C* lds, const double2* tw4, GP<C> X, int n, int ra,
+                                               bool hasb, const C* X2 = nullptr) {
     constexpr int T = L / E;
     using Rl = typename CplxOps<C>::real;
     const int tid = threadIdx.x;
@@ -623,45 +712,45 @@ __device__ __forceinline__ void rows_fwd_store(C (&reg)[E], C* lds, const double
         const C z = lds[kk], w = lds[kk == 0 ? 0 : L - kk];
         const C v = r == 0 ? CplxOps<C>::make(Rl(0.5) * (z.x + w.x), Rl(0.5) * (z.y - w.y))
                            : CplxOps<C>::make(Rl(0.5) * (z.y + w.y), Rl(-0.5) * (z.x - w.x));
-        const size_t o = (size_t)kk * n + ra + r;
-        X[o] = v;
-        if (X2) X2[o] = v;
+        X.put(kk * n + ra + r, v);
+        if (X2) GP<C>(X2).put(kk * n + ra + r, v);
     }
 }
 
 template <int L, int E>
-__global__ __launch_bounds__(L / E) void ks_rows_fwd(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0) || !a.mixed || !is_anchor(a)) return;
+__global__ __launch_bounds__(L / E) void ks_rows_fwd(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0) || !c.now.anchor) return;
     constexpr int T = L / E;
     const int n = a.n, np = (n + 1) >> 1;
     const int p = xcd_remap(blockIdx.x, gridDim.x);
     if (p >= np) return;
     __shared__ double2 lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, E>()];
-    load_twiddles<L, E>(a.tw, tw4);
+    load_twiddles<L, E>(GP<double2>(a.tw), tw4);
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
-    const double* U = a.pool[a.ctl->cur];
+    const GP<double> U(c.now.V);
     double2 reg[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int j = threadIdx.x + e * T;
-        reg[e] = j < n ? make_double2(U[(size_t)ra * n + j], hasb ? U[(size_t)rb * n + j] : 0.0)
-                       : make_double2(0.0, 0.0);
+        reg[e] = j < n ? make_double2(U[ra * n + j], hasb ? U[rb * n + j] : 0.0) : make_double2(0.0, 0.0);
     }
-    rows_fwd_store<L, E>(reg, lds, tw4, a.X, n, ra, hasb);
+    rows_fwd_store<L, E>(reg, lds, tw4, xbuf<double2>(a), n, ra, hasb);
 }
 
 // Semi-Lagrangian gather W = (T_1 (x) T_2) E (order P), starting value Y^0 into
 // the iterate buffer, and (FFT) the row transform of Y^0 (FP64) or, in the
 // mixed form, of Y^0 - V^{n-1} (FP32); one row pair per block.
 template <int L, int E, int P, bool FFT, bool MIXED>
-__global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
+__global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
     // FP64 steps whose B Y^0 comes by linearity need no row transform of Y^0:
     // ks_begin_lin does their gather and start value
-    if (halted(a, 0) || (FFT && !MIXED && start_by_linearity(a))) return;
+    if (halted(a, c, 0) || (FFT && !MIXED && c.now.lin)) return;
     constexpr int T = L / E;
     using C = typename std::conditional<MIXED, float2, double2>::type;
     const int n = a.n, np = (n + 1) >> 1;
@@ -669,24 +758,18 @@ __global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A) 
     if (p >= np) return;
     __shared__ C lds[FFT ? lds_slots(L) : 1];
     __shared__ double2 tw4[FFT ? tw_slots<L, E>() : 1];
-    if constexpr (FFT) load_twiddles<L, E>(a.tw, tw4);
+    if constexpr (FFT) load_twiddles<L, E>(GP<double2>(a.tw), tw4);
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
     const int tid = threadIdx.x;
-    const Ctl* c = a.ctl;
-    const StepDesc& sd = cur_set(a);
-    const double* Ex = sd.theta < 1.0 ? wprev(a) : a.pool[c->cur];   // explicit part E_s
-    double* W = wcur(a);
-    double* Y = a.pool[c->y];
-    const int nsrc = c->nsrc;
-    const double* H[4];
+    const GP<double> Ex(c.now.expl != EXPL_NONE ? c.now.Wp : c.now.V);   // explicit part E_s
+    const GP<double> W(c.now.W), Y(c.now.Y), V(c.now.V), w1t(c.now.w1), w2t(c.now.w2);
+    const GP<int> s1(c.now.s1), s2(c.now.s2);
+    const int nsrc = c.nsrc;
+    const GP<double> H[4] = {GP<double>(c.now.H[0]), GP<double>(c.now.H[1]), GP<double>(c.now.H[2]), GP<double>(c.now.H[3])};
     double cf[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        H[q] = a.pool[c->src[q]];
-        cf[q] = c->coef[q];
-    }
-    const double* V = a.pool[c->cur];
+    for (int q = 0; q < 4; ++q) cf[q] = c.now.coef[q];
     // Two phases: the gathers and the history reads of every element first,
     // then the writes (the compiler cannot tell that W and Y alias none of the
     // read grids, so reads after writes would wait for each element in turn).
@@ -696,25 +779,25 @@ __global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A) 
         const int j = tid + e * T;
         wv[e][0] = wv[e][1] = yv[e][0] = yv[e][1] = yf[e][0] = yf[e][1] = 0.0;
         if (j < n) {
-            const int b0 = sd.s2[j];
+            const int b0 = s2[j];
             double w2[P + 1];
 #pragma unroll
-            for (int b = 0; b <= P; ++b) w2[b] = sd.w2[j * (P + 1) + b];
+            for (int b = 0; b <= P; ++b) w2[b] = w2t[j * (P + 1) + b];
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 const int i = ra + r;
                 if (r == 1 && !hasb) break;
-                const int a0 = sd.s1[i];
+                const int a0 = s1[i];
                 double acc = 0.0;
 #pragma unroll
                 for (int aa = 0; aa <= P; ++aa) {
-                    const double* er = Ex + (size_t)(a0 + aa) * n + b0;
+                    const int eo = (a0 + aa) * n + b0;
                     double s = 0.0;
 #pragma unroll
-                    for (int b = 0; b <= P; ++b) s += w2[b] * er[b];
-                    acc += sd.w1[i * (P + 1) + aa] * s;
+                    for (int b = 0; b <= P; ++b) s += w2[b] * Ex[eo + b];
+                    acc += w1t[i * (P + 1) + aa] * s;
                 }
-                const size_t o = (size_t)i * n + j;
+                const int o = i * n + j;
                 wv[e][r] = acc;
                 // unrolled with a predicate, so the history reads are all in flight together
                 double y = 0.0;
@@ -735,9 +818,9 @@ __global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A) 
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 if (r == 1 && !hasb) break;
-                const size_t o = (size_t)(ra + r) * n + j;
-                W[o] = wv[e][r];
-                Y[o] = yv[e][r];
+                const int o = (ra + r) * n + j;
+                W.put(o, wv[e][r]);
+                Y.put(o, yv[e][r]);
                 y0[r] = yf[e][r];
             }
         }
@@ -750,26 +833,28 @@ __global__ __launch_bounds__(L / E) void ks_sl(const MarchArgs* __restrict__ A) 
 // (thread = column + CPB * chunk); launched with CPB * P <= MAXT threads.
 // MM: chunk capacity (at least ceil(n / P_cols)).
 template <int CPB, int MAXT, int MM>
-__global__ __launch_bounds__(MAXT) void ks_line_cols(const MarchArgs* __restrict__ A, int k) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, k)) return;
+__global__ __launch_bounds__(MAXT) void ks_line_cols(const MarchArgs* __restrict__ A,
+                                                     const Ctl* __restrict__ Cs, int k) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, k)) return;
     extern __shared__ double2 sbuf[];
     const int n = a.n, P = a.P_cols;
-    const int c = threadIdx.x % CPB, t = threadIdx.x / CPB;
+    const int cc = threadIdx.x % CPB, t = threadIdx.x / CPB;
     const int g = xcd_remap(blockIdx.x, gridDim.x);
     if (CPB * g >= n) return;
-    const int col = g * CPB + c;
+    const int col = g * CPB + cc;
     const int m = (n + P - 1) / P;
     const int s = t * m;
     const int cnt = col < n ? max(0, min(m, n - s)) : 0;
-    const StepDesc& sd = cur_set(a);
+    const GP<double> R(a.R);
     double x[MM];
 #pragma unroll
-    for (int q = 0; q < MM; ++q) x[q] = q < cnt ? a.R[(size_t)(s + q) * n + col] : 0.0;
-    chunk_solve<MM>(x, s, cnt, c, t, P, CPB, sd.fl1, sd.bu1, sd.bc1, sbuf);
+    for (int q = 0; q < MM; ++q) x[q] = q < cnt ? R[(s + q) * n + col] : 0.0;
+    chunk_solve<MM>(x, s, cnt, cc, t, P, CPB, c.now.fl1, c.now.bu1, c.now.bc1, sbuf);
 #pragma unroll
     for (int q = 0; q < MM; ++q)
-        if (q < cnt) a.R[(size_t)(s + q) * n + col] = x[q];
+        if (q < cnt) R.put((s + q) * n + col, x[q]);
 }
 
 // Axis-2 line solves of a row pair, the update Y += delta, the stopping-rule
@@ -780,10 +865,12 @@ __global__ __launch_bounds__(MAXT) void ks_line_cols(const MarchArgs* __restrict
 // over all MM slots, so the host takes the smallest of E, 3E/2 and 2E that
 // holds the chunks (24 instead of 32 at n = 2048, L = 3072: 65 -> 55 us alone).
 template <int L, int E, bool FFT, bool MIXED, int MM = 2 * E>
-__global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restrict__ A, int k) {
+__global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restrict__ A,
+                                                     const Ctl* __restrict__ Cs, int k) {
     static_assert(MM <= 2 * E && MM % 2 == 0, "chunk capacity: even, at most 2E");
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, k)) return;
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, k)) return;
     constexpr int T = L / E, PR = T / 2;
     using C = typename std::conditional<MIXED, float2, double2>::type;
     const int n = a.n, np = (n + 1) >> 1;
@@ -792,15 +879,14 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
     // union: row buffer 2 (n + PR + 1) doubles (n <= L) | scan totals | FFT exchange buffer
     __shared__ double2 lds[L + (PR > L / 16 ? PR : L / 16) + 2];
     __shared__ double2 tw4[FFT ? tw_slots<L, E>() : 1];
-    if constexpr (FFT) load_twiddles<L, E>(a.tw, tw4);
+    if constexpr (FFT) load_twiddles<L, E>(GP<double2>(a.tw), tw4);
     double* rows = reinterpret_cast<double*>(lds);
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
     const int tid = threadIdx.x;
     const int m = (n + PR - 1) / PR;
     const int stride = n + PR + 1;
-    const StepDesc& sd = cur_set(a);
-    double* Y = a.pool[a.ctl->y];
+    const GP<double> Y(c.now.Y);
     // each thread reads its chunk of the residual row straight from memory: the
     // chunks of consecutive lanes are adjacent, so the reads stay coalesced
     const int r = tid / PR, ch = tid % PR;
@@ -808,24 +894,25 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
     const int cnt = (r == 1 && !hasb) ? 0 : max(0, min(m, n - s));
     double x[MM];
     {
-        const double* Rr = a.R + (size_t)(r == 0 ? ra : rb) * n + s;
+        const int o = (r == 0 ? ra : rb) * n + s;
         if (((n | m) & 1) == 0) {
             // 16-byte loads: the chunk starts at an even element of a row of
             // even length, so every pair is aligned (half the load
             // instructions and addresses of element-wise reads)
-            const double2* R2 = reinterpret_cast<const double2*>(Rr);
+            const GP<double2> R2(reinterpret_cast<const double2*>(a.R));
 #pragma unroll
             for (int q = 0; q < MM / 2; ++q) {
-                const double2 v = 2 * q < cnt ? R2[q] : make_double2(0.0, 0.0);
+                const double2 v = 2 * q < cnt ? R2[(o >> 1) + q] : make_double2(0.0, 0.0);
                 x[2 * q] = v.x;
                 x[2 * q + 1] = v.y;
             }
         } else {
+            const GP<double> Rr(a.R);
 #pragma unroll
-            for (int q = 0; q < MM; ++q) x[q] = q < cnt ? Rr[q] : 0.0;
+            for (int q = 0; q < MM; ++q) x[q] = q < cnt ? Rr[o + q] : 0.0;
         }
     }
-    chunk_solve<MM>(x, s, cnt, r, ch, PR, 1, sd.fl2, sd.bu2, sd.bc2, lds);
+    chunk_solve<MM>(x, s, cnt, r, ch, PR, 1, c.now.fl2, c.now.bu2, c.now.bc2, lds);
 #pragma unroll
     for (int q = 0; q < MM; ++q)
         if (q < cnt) rows[r * stride + s + q + ch] = x[q];
@@ -839,8 +926,8 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int j = tid + e * T;
-        yoa[e] = j < n ? Y[(size_t)ra * n + j] : 0.0;
-        yob[e] = (j < n && hasb) ? Y[(size_t)rb * n + j] : 0.0;
+        yoa[e] = j < n ? Y[ra * n + j] : 0.0;
+        yob[e] = (j < n && hasb) ? Y[rb * n + j] : 0.0;
     }
     double emax = 0.0;
     C reg[E];
@@ -850,16 +937,14 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
         double ya = 0.0, yb = 0.0, da = 0.0, db = 0.0;
         if (j < n) {
             da = rows[j + j / m];
-            const size_t oa = (size_t)ra * n + j;
             ya = yoa[e] + da;
-            Y[oa] = ya;
+            Y.put(ra * n + j, ya);
             double ev = fabs(da) / fmax(1.0, fabs(ya));
             emax = (ev > emax || ev != ev) ? ev : emax;
             if (hasb) {
                 db = rows[stride + j + j / m];
-                const size_t ob = (size_t)rb * n + j;
                 yb = yob[e] + db;
-                Y[ob] = yb;
+                Y.put(rb * n + j, yb);
                 ev = fabs(db) / fmax(1.0, fabs(yb));
                 emax = (ev > emax || ev != ev) ? ev : emax;
             }
@@ -884,7 +969,7 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
         double b = wmax[0];
 #pragma unroll
         for (int w = 1; w < NWV; ++w) b = (wmax[w] > b || wmax[w] != wmax[w]) ? wmax[w] : b;
-        atomicMax(&a.ctl->err[(blockIdx.x + blockIdx.y * gridDim.x) & (NX - 1)][k],
+        atomicMax(&const_cast<Ctl*>(Cs + blockIdx.y)->err[(blockIdx.x + blockIdx.y * gridDim.x) & (NX - 1)][k],
                   (unsigned long long)__double_as_longlong(b));
     }
     if constexpr (FFT) rows_fwd_store<L, E>(reg, reinterpret_cast<C*>(lds), tw4, xbuf<C>(a), n, ra, hasb);
@@ -892,13 +977,18 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
 
 // End of a step: convergence verdict, history rotation, next starting value.
 // One block per plan.
-static __global__ void ks_step_end(const MarchArgs* __restrict__ A, int kmax) {
-    const MarchArgs& a = plan_args(A);
-    Ctl* c = a.ctl;
+static __global__ void ks_step_end(const MarchArgs* __restrict__ A, Ctl* __restrict__ Cs, int kmax) {
+    Args& a = plan_args(A);
+    Ctl* c = Cs + blockIdx.y;
     if (c->hold || c->step >= a.nsteps) return;
     __shared__ int ok;
     __shared__ double ek[KSLOTS];
-    for (int q = threadIdx.x; q <= kmax; q += blockDim.x) ek[q] = err_max(c, q);
+    // the next step's set, read ahead of the verdict
+    const int s2 = c->step + 1, sn = s2 < a.nsteps ? s2 : c->step;
+    const int id = a.step_set[sn];
+    const double cn = a.cn_rho ? a.cn_rho[sn] : 0.0;
+    const StepDesc sd = a.sets[id];
+    for (int q = threadIdx.x; q <= kmax; q += blockDim.x) ek[q] = err_max(*c, q);
     __syncthreads();
     if (threadIdx.x == 0) {
         ok = 0;
@@ -933,21 +1023,21 @@ static __global__ void ks_step_end(const MarchArgs* __restrict__ A, int kmax) {
                 c->y = fr;
                 c->bvalid &= ~(1 << fr);                  // the free grid takes the next iterate
                 c->w ^= 1;
-                const int s2 = s + 1;
                 c->step = s2;
-                for (int q = 0; q < 4; ++q) { c->src[q] = c->hist[q]; c->coef[q] = 0.0; }
+                double* cf = c->now.coef;
+                for (int q = 0; q < 4; ++q) c->src[q] = c->hist[q];
                 if (a.damping && s2 < a.n_sub) {
                     c->nsrc = 1;
                     c->src[0] = c->cur;
-                    c->coef[0] = 1.0;
+                    cf[0] = 1.0;
                 } else {
                     c->nsrc = c->hc;
-                    if (c->hc == 1) { c->coef[0] = 1.0; }
-                    else if (c->hc == 2) { c->coef[0] = 2.0; c->coef[1] = -1.0; }
-                    else if (c->hc == 3) { c->coef[0] = 3.0; c->coef[1] = -3.0; c->coef[2] = 1.0; }
-                    else { c->coef[0] = 4.0; c->coef[1] = -6.0; c->coef[2] = 4.0; c->coef[3] = -1.0; }
+                    if (c->hc == 1) { cf[0] = 1.0; }
+                    else if (c->hc == 2) { cf[0] = 2.0; cf[1] = -1.0; }
+                    else if (c->hc == 3) { cf[0] = 3.0; cf[1] = -3.0; cf[2] = 1.0; }
+                    else { cf[0] = 4.0; cf[1] = -6.0; cf[2] = 4.0; cf[3] = -1.0; }
                 }
-                for (int q = c->nsrc; q < 4; ++q) c->src[q] = c->src[0];   // weight 0 (above)
+                if (s2 < a.nsteps) step_setup(a, c, sd, id, cn);
             }
         }
     }
@@ -955,31 +1045,30 @@ static __global__ void ks_step_end(const MarchArgs* __restrict__ A, int kmax) {
     if (ok) err_reset_upto(c, kmax);
 }
 
-// Recording for the adjoint march.  After sl (once per step): E_s, held in wprev
+// Recording for the adjoint march.  After sl (once per step): E_s, held in now.Wp
 // when theta < 1, to segE (ks_begin_lin records it itself).  After step_end: the current state to seg when its
 // step index is on the recording stride (idempotent: a slot whose step did not
 // advance writes the same state again).
-static __global__ void ks_store_E(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0) || !a.segE || cur_set(a).theta >= 1.0 || start_by_linearity(a)) return;
+static __global__ void ks_store_E(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0) || !a.segE || c.now.expl == EXPL_NONE || c.now.lin) return;
     const size_t N = (size_t)a.n * a.n;
-    const double* src = wprev(a);
-    double* dst = a.segE + (size_t)(a.ctl->step - a.seg_base) * N;
+    const GP<double> src(c.now.Wp), dst(GP<double>(a.segE), (size_t)(c.step - a.seg_base) * N);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (size_t)gridDim.x * blockDim.x)
-        dst[i] = src[i];
+        dst.put(i, src[i]);
 }
 
-static __global__ void ks_store_V(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
-    const Ctl* c = a.ctl;
-    if (!a.seg || c->hold) return;
-    const int rel = c->step - a.seg_base;
+static __global__ void ks_store_V(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (!a.seg || c.hold) return;
+    const int rel = c.step - a.seg_base;
     if (rel < 0 || rel % a.seg_every != 0) return;
     const size_t N = (size_t)a.n * a.n;
-    const double* src = a.pool[c->cur];
-    double* dst = a.seg + (size_t)(rel / a.seg_every) * N;
+    const GP<double> src(a.pool[c.cur]), dst(GP<double>(a.seg), (size_t)(rel / a.seg_every) * N);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (size_t)gridDim.x * blockDim.x)
-        dst[i] = src[i];
+        dst.put(i, src[i]);
 }
 
 // ---- adjoint march (reverse time steps) ----
@@ -990,10 +1079,12 @@ static __global__ void ks_store_V(const MarchArgs* __restrict__ A) {
 // Buffers of the adjoint MarchArgs: pool[1] = lam, pool[0] = mu, Wb = Ybar.
 
 // Control block for reverse step s: iterate in pool[1], no failure, stopping values reset.
-static __global__ void ks_adj_begin(const MarchArgs* __restrict__ A, int s) {
-    Ctl* c = A[0].ctl;
+static __global__ void ks_adj_begin(const MarchArgs* __restrict__ A, Ctl* __restrict__ Cs, int s) {
+    Ctl* c = Cs;
     err_reset(c);
     if (threadIdx.x == 0) {
+        Args& a = kref(A);
+        const int id = a.step_set[s];
         c->step = s;
         c->fail = 0;
         c->fail_step = -1;
@@ -1001,6 +1092,10 @@ static __global__ void ks_adj_begin(const MarchArgs* __restrict__ A, int s) {
         c->cur = 0;
         c->y = 1;
         c->w = 0;
+        c->nsrc = 0;
+        c->bvalid = 0;
+        for (int q = 0; q < 4; ++q) c->src[q] = 0;
+        step_setup(a, c, a.sets[id], id, 0.0);
     }
 }
 
@@ -1010,65 +1105,66 @@ static __global__ void ks_adj_begin(const MarchArgs* __restrict__ A, int s) {
 // extrapolated over the previous steps of the same kind and rescaled to this
 // step's dt theta; unused c are null.
 template <int L, int E>
-__global__ __launch_bounds__(L / E) void ks_adj_start(const MarchArgs* __restrict__ A,
+__global__ __launch_bounds__(L / E) void ks_adj_start(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs,
                                                      const double* __restrict__ c1, double w1,
                                                      const double* __restrict__ c2, double w2,
                                                      const double* __restrict__ c3, double w3,
                                                      const double* __restrict__ c4, double w4) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0)) return;
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0)) return;
     constexpr int T = L / E;
     const int n = a.n, np = (n + 1) >> 1;
     const int p = xcd_remap(blockIdx.x, gridDim.x);
     if (p >= np) return;
     __shared__ double2 lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, E>()];
-    load_twiddles<L, E>(a.tw, tw4);
+    load_twiddles<L, E>(GP<double2>(a.tw), tw4);
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
-    double* lam = a.pool[a.ctl->y];
-    const double* Yb = wcur(a);
+    const GP<double> lam(c.now.Y), Yb(c.now.W);
+    const GP<double> g1(c1), g2(c2), g3(c3), g4(c4);
+    auto start = [&](int o) {
+        return Yb[o] + (c1 ? w1 * g1[o] : 0.0) + (c2 ? w2 * g2[o] : 0.0) + (c3 ? w3 * g3[o] : 0.0) +
+               (c4 ? w4 * g4[o] : 0.0);
+    };
     double2 reg[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int j = threadIdx.x + e * T;
-        double va = 0.0, vb = 0.0;
-        if (j < n) {
-            const size_t oa = (size_t)ra * n + j, ob = (size_t)rb * n + j;
-            va = Yb[oa] + (c1 ? w1 * c1[oa] : 0.0) + (c2 ? w2 * c2[oa] : 0.0) + (c3 ? w3 * c3[oa] : 0.0) +
-                 (c4 ? w4 * c4[oa] : 0.0);
-            lam[oa] = va;
-            if (hasb) {
-                vb = Yb[ob] + (c1 ? w1 * c1[ob] : 0.0) + (c2 ? w2 * c2[ob] : 0.0) + (c3 ? w3 * c3[ob] : 0.0) +
-                     (c4 ? w4 * c4[ob] : 0.0);
-                lam[ob] = vb;
-            }
-        }
+        const double va = j < n ? start(ra * n + j) : 0.0, vb = j < n && hasb ? start(rb * n + j) : 0.0;
         reg[e] = make_double2(va, vb);
     }
-    rows_fwd_store<L, E>(reg, lds, tw4, a.X, n, ra, hasb);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int j = threadIdx.x + e * T;
+        if (j < n) lam.put(ra * n + j, reg[e].x);
+        if (j < n && hasb) lam.put(rb * n + j, reg[e].y);
+    }
+    rows_fwd_store<L, E>(reg, lds, tw4, xbuf<double2>(a), n, ra, hasb);
 }
 
 // corr = lam - Ybar after the adjoint fixed point converged (start of the next
 // reverse step).
-static __global__ void ks_adj_corr(const MarchArgs* __restrict__ A, double* __restrict__ corr) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0)) return;
+static __global__ void ks_adj_corr(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs,
+                                   double* __restrict__ corr) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0)) return;
     const size_t N = (size_t)a.n * a.n;
-    const double* lam = a.pool[a.ctl->y];
-    const double* Yb = wcur(a);
+    const GP<double> lam(c.now.Y), Yb(c.now.W);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (size_t)gridDim.x * blockDim.x)
         corr[i] = lam[i] - Yb[i];
 }
 
 // Verdict of the adjoint fixed point of the current reverse step: iteration
 // count (first k with err_k < tol) or the failure flag.
-static __global__ void ks_adj_end(const MarchArgs* __restrict__ A, int kmax) {
-    const MarchArgs& a = A[0];
-    Ctl* c = a.ctl;
+static __global__ void ks_adj_end(const MarchArgs* __restrict__ A, Ctl* __restrict__ Cs, int kmax) {
+    Args& a = kref(A);
+    Ctl* c = Cs;
     if (c->fail) return;
     __shared__ double ek[KSLOTS];
-    for (int q = threadIdx.x; q <= kmax; q += blockDim.x) ek[q] = err_max(c, q);
+    for (int q = threadIdx.x; q <= kmax; q += blockDim.x) ek[q] = err_max(*c, q);
     __syncthreads();
     if (threadIdx.x != 0) return;
     int kk = 0;
@@ -1090,22 +1186,24 @@ static __global__ void ks_adj_end(const MarchArgs* __restrict__ A, int kmax) {
 // each thread holds its columns' sources and weights in registers and the
 // loops have fixed bounds; WM = 0: any width.
 template <int L, int E, int WM>
-__global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__ A, double2* __restrict__ X2) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0)) return;
+__global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs,
+                                                  double2* __restrict__ X2) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0)) return;
     constexpr int T = L / E;
     const int n = a.n, np = (n + 1) >> 1;
     const int p = xcd_remap(blockIdx.x, gridDim.x);
     if (p >= np) return;
     __shared__ double2 lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, E>()];
-    const StepDesc& sd = cur_set(a);
+    KRef<StepDesc> sd = kref(a.sets + c.now.set);
     const bool fft = sd.theta < 1.0;
-    if (fft) load_twiddles<L, E>(a.tw, tw4);
+    if (fft) load_twiddles<L, E>(GP<double2>(a.tw), tw4);
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
-    const double* __restrict__ lam = a.pool[a.ctl->y];
-    double* __restrict__ mu = a.pool[a.ctl->cur];
+    const GP<double> lam(c.now.Y), mu(c.now.V), t1w(sd.t1w), t2w(sd.t2w);
+    const GP<int> t1i(sd.t1i), t2i(sd.t2i);
     const int W1 = sd.wt1, W2 = sd.wt2;
     double outv[E][2];
     if constexpr (WM > 0) {
@@ -1115,10 +1213,10 @@ __global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__
 #pragma unroll
         for (int q = 0; q < WM; ++q) {
             const bool in = q < W1;
-            ia[q] = in ? sd.t1i[(size_t)ra * W1 + q] : ra;
-            wa[q] = in ? sd.t1w[(size_t)ra * W1 + q] : 0.0;
-            ib[q] = (in && hasb) ? sd.t1i[(size_t)rb * W1 + q] : ra;
-            wb[q] = (in && hasb) ? sd.t1w[(size_t)rb * W1 + q] : 0.0;
+            ia[q] = in ? t1i[ra * W1 + q] : ra;
+            wa[q] = in ? t1w[ra * W1 + q] : 0.0;
+            ib[q] = (in && hasb) ? t1i[rb * W1 + q] : ra;
+            wb[q] = (in && hasb) ? t1w[rb * W1 + q] : 0.0;
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -1130,20 +1228,19 @@ __global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__
 #pragma unroll
                 for (int q = 0; q < WM; ++q) {
                     const bool in = q < W2;
-                    jc[q] = in ? sd.t2i[(size_t)j * W2 + q] : j;
-                    wc[q] = in ? sd.t2w[(size_t)j * W2 + q] : 0.0;
+                    jc[q] = in ? t2i[j * W2 + q] : j;
+                    wc[q] = in ? t2w[j * W2 + q] : 0.0;
                 }
 #pragma unroll
                 for (int q1 = 0; q1 < WM; ++q1) {
                     if (q1 >= W1) break;
-                    const double* la = lam + (size_t)ia[q1] * n;
-                    const double* lb = lam + (size_t)ib[q1] * n;
+                    const int la = ia[q1] * n, lb = ib[q1] * n;
                     double ta = 0.0, tb = 0.0;
 #pragma unroll
                     for (int q2 = 0; q2 < WM; ++q2) {
                         if (q2 < W2) {
-                            ta += wc[q2] * la[jc[q2]];
-                            tb += wc[q2] * lb[jc[q2]];
+                            ta += wc[q2] * lam[la + jc[q2]];
+                            tb += wc[q2] * lam[lb + jc[q2]];
                         }
                     }
                     sa += wa[q1] * ta;
@@ -1164,11 +1261,11 @@ __global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__
                     if (r == 1 && !hasb) break;
                     double acc = 0.0;
                     for (int q1 = 0; q1 < W1; ++q1) {
-                        const double w = sd.t1w[(size_t)i * W1 + q1];
-                        const double* lr = lam + (size_t)sd.t1i[(size_t)i * W1 + q1] * n;
+                        const double w = t1w[i * W1 + q1];
+                        const int lr = t1i[i * W1 + q1] * n;
                         double s2 = 0.0;
                         for (int q2 = 0; q2 < W2; ++q2)
-                            s2 += sd.t2w[(size_t)j * W2 + q2] * lr[sd.t2i[(size_t)j * W2 + q2]];
+                            s2 += t2w[j * W2 + q2] * lam[lr + t2i[j * W2 + q2]];
                         acc += w * s2;
                     }
                     outv[e][r] = acc;
@@ -1183,12 +1280,12 @@ __global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__
     for (int e = 0; e < E; ++e) {
         const int j = threadIdx.x + e * T;
         if (j < n) {
-            mu[(size_t)ra * n + j] = outv[e][0];
-            if (hasb) mu[(size_t)rb * n + j] = outv[e][1];
+            mu.put(ra * n + j, outv[e][0]);
+            if (hasb) mu.put(rb * n + j, outv[e][1]);
         }
         reg[e] = make_double2(outv[e][0], outv[e][1]);
     }
-    if (fft) rows_fwd_store<L, E>(reg, lds, tw4, a.X, n, ra, hasb, X2);
+    if (fft) rows_fwd_store<L, E>(reg, lds, tw4, xbuf<double2>(a), n, ra, hasb, X2);
 }
 
 // Per-step gradient terms of the reverse step (one block per row pair,
@@ -1198,52 +1295,55 @@ __global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__
 //   q = 4, 5:    lam . ((dT_1 (x) T_2) E), lam . ((T_1 (x) dT_2) E)   (kappa_omega^(1,2))
 // with Y = V^{s+1}, V = V^s and E = E_s (V^s when theta = 1).
 template <int P>
-__global__ __launch_bounds__(256) void ks_adj_accum(const MarchArgs* __restrict__ A, const double* __restrict__ Yg,
+__global__ __launch_bounds__(256) void ks_adj_accum(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs,
+                                                    const double* __restrict__ Yg,
                                                     const double* __restrict__ Vg, const double* __restrict__ Eg,
                                                     double* __restrict__ acc) {
-    const MarchArgs& a = plan_args(A);
-    if (halted(a, 0)) return;
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0)) return;
     const int n = a.n;
     const int i = xcd_remap(blockIdx.x, gridDim.x);   // neighbouring rows on one XCD (stencil reads share L2)
     if (i >= n) return;
-    const StepDesc& sd = cur_set(a);
-    const double* lam = a.pool[a.ctl->y];
-    const double* mu = a.pool[a.ctl->cur];
-    const double ci = sd.dt * sd.theta, ce = sd.dt * (1.0 - sd.theta);
+    KRef<StepDesc> sd = kref(a.sets + c.now.set);
+    const GP<double> lam(c.now.Y), mu(c.now.V), Yp(Yg), Vp(Vg), Ep(Eg), w1t(sd.w1), w1dt(sd.w1d), w2t(sd.w2), w2dt(sd.w2d);
+    const GP<int> s2(sd.s2);
+    const double ci = c.now.cth, ce = c.now.cex, h = a.st.h;
     double t[6] = {0, 0, 0, 0, 0, 0};
-    const int a0 = sd.s1[i];
+    const int a0 = GP<int>(sd.s1)[i];
     double w1[P + 1], w1d[P + 1];
 #pragma unroll
     for (int q = 0; q <= P; ++q) {
-        w1[q] = sd.w1[i * (P + 1) + q];
-        w1d[q] = sd.w1d[i * (P + 1) + q];
+        w1[q] = w1t[i * (P + 1) + q];
+        w1d[q] = w1dt[i * (P + 1) + q];
     }
     for (int j = threadIdx.x; j < n; j += blockDim.x) {
-        const size_t o = (size_t)i * n + j;
-        const double l = lam[o], m = mu[o], y = Yg[o], v = Vg[o];
+        const int o = i * n + j;
+        const double l = lam[o], m = mu[o], y = Yp[o], v = Vp[o];
         double y11, y12, y22, v11 = 0.0, v12 = 0.0, v22 = 0.0;
-        apply_D_parts(Yg, n, a.st.h, i, j, y, y11, y12, y22);
-        if (ce != 0.0) apply_D_parts(Vg, n, a.st.h, i, j, v, v11, v12, v22);
+        apply_D_parts(Yp, n, h, i, j, y, y11, y12, y22);
+        if (ce != 0.0) apply_D_parts(Vp, n, h, i, j, v, v11, v12, v22);
         t[0] += ci * l * y11 + ce * m * v11;
         t[1] += ci * l * y12 + ce * m * v12;
         t[2] += ci * l * y22 + ce * m * v22;
         t[3] -= ci * l * y + ce * m * v;
-        const int b0 = sd.s2[j];
+        const int b0 = s2[j];
         double w2[P + 1], w2d[P + 1];
 #pragma unroll
         for (int b = 0; b <= P; ++b) {
-            w2[b] = sd.w2[j * (P + 1) + b];
-            w2d[b] = sd.w2d[j * (P + 1) + b];
+            w2[b] = w2t[j * (P + 1) + b];
+            w2d[b] = w2dt[j * (P + 1) + b];
         }
         double g1 = 0.0, g2 = 0.0;
 #pragma unroll
         for (int aa = 0; aa <= P; ++aa) {
-            const double* er = Eg + (size_t)(a0 + aa) * n + b0;
+            const int eo = (a0 + aa) * n + b0;
             double s0 = 0.0, sdd = 0.0;
 #pragma unroll
             for (int b = 0; b <= P; ++b) {
-                s0 += w2[b] * er[b];
-                sdd += w2d[b] * er[b];
+                const double ev = Ep[eo + b];
+                s0 += w2[b] * ev;
+                sdd += w2d[b] * ev;
             }
             g1 += w1d[aa] * s0;
             g2 += w1[aa] * sdd;
@@ -1311,9 +1411,9 @@ __global__ __launch_bounds__(L / E) void ks_adj_spec(const double2* __restrict__
 
 // Control block at the start of a march: the state of step-list entry step0
 // in pool[0], the iterate in pool[1], no history before it.  One block per plan.
-static __global__ void ks_init(const MarchArgs* __restrict__ A) {
-    const MarchArgs& a = plan_args(A);
-    Ctl* c = a.ctl;
+static __global__ void ks_init(const MarchArgs* __restrict__ A, Ctl* __restrict__ Cs) {
+    Args& a = plan_args(A);
+    Ctl* c = Cs + blockIdx.y;
     err_reset(c);
     if (threadIdx.x == 0) {
         c->step = a.step0;
@@ -1322,22 +1422,26 @@ static __global__ void ks_init(const MarchArgs* __restrict__ A) {
         c->hold = 0;
         c->cur = 0;
         c->y = 1;
+        c->w = 0;
         c->hc = 1;
         c->nsrc = 1;
         c->bvalid = 0;
-        c->w = 0;
-        for (int q = 0; q < 4; ++q) { c->hist[q] = 0; c->src[q] = 0; c->coef[q] = 0.0; }
-        c->coef[0] = 1.0;
+        for (int q = 0; q < 4; ++q) { c->hist[q] = 0; c->src[q] = 0; }
+        c->now.coef[0] = 1.0;
+        if (a.step0 < a.nsteps) {
+            const int id = a.step_set[a.step0];
+            step_setup(a, c, a.sets[id], id, a.cn_rho ? a.cn_rho[a.step0] : 0.0);
+        }
     }
 }
 
-static __global__ void ks_clear_fail(const MarchArgs* __restrict__ A, int plan) {
-    if (threadIdx.x == 0) A[plan].ctl->fail = 0;
+static __global__ void ks_clear_fail(Ctl* __restrict__ Cs, int plan) {
+    if (threadIdx.x == 0) Cs[plan].fail = 0;
 }
 
 // hold = 1 on every plan of the group except `keep` (keep < 0: release all).
-static __global__ void ks_hold(const MarchArgs* __restrict__ A, int np, int keep) {
-    for (int q = threadIdx.x; q < np; q += blockDim.x) A[q].ctl->hold = (keep >= 0 && q != keep) ? 1 : 0;
+static __global__ void ks_hold(Ctl* __restrict__ Cs, int np, int keep) {
+    for (int q = threadIdx.x; q < np; q += blockDim.x) Cs[q].hold = (keep >= 0 && q != keep) ? 1 : 0;
 }
 
 }  // namespace lpide

@@ -49,7 +49,7 @@ CLASS_OF = [
 # The sources that define the march kernels and their launch sequences (grid,
 # block, radix): a kernel's measured traffic holds while these are unchanged.
 # Host-only code (plans, the C ABI, pricing) is not part of it.
-KERNEL_SOURCES = ("fft.hpp", "kernels.hpp", "linesolve.hpp", "step_kernels.hpp", "conv_kernels.hpp",
+KERNEL_SOURCES = ("fft.hpp", "gmem.hpp", "kernels.hpp", "linesolve.hpp", "step_kernels.hpp", "conv_kernels.hpp",
                   "march_L.hip", "plan.hpp")
 
 
