@@ -450,25 +450,32 @@ std::vector<char> linearity_steps(const Plan* p, int step0, int nend) {
     return out;
 }
 
-// Default radix schedule.  From measurements on MI355X (each kernel alone):
-// the column pass gains from radix 16 at L >= 1024; the row c2r, line-row and
-// SL kernels from radix 4 up to L = 1024 and radix 8 above.
-// Preferred E per kernel class, from single-kernel timings at n = 512 (L = 768,
-// 1024) and n = 2048 (L = 3072, 4096); lowered to the next supported value
-// where the size does not allow it (L = 3 * 2^m needs whole waves: L / E a
-// multiple of 64).
+// Preferred E per kernel class, from each class's time per launch in marches of
+// one plan at every E (below); lowered to the next supported value where the
+// size does not allow it (L = 3 * 2^m needs whole waves: L / E a multiple of 64).
 static int supported_e(int L, int E) {
     while (E > 4 && !e_supported(L, E)) E /= 2;
     return E;
 }
 
-Schedule default_schedule(int L) {
+// FP64 (us per launch at E = 4, 8, 16 where the choice turns on it):
+//   columns   128 4.7 6.0 -; 256 4.5 5.3 7.6; 1024 8.6 8.9 11.5; 1536 14.6 12.9 -;
+//             2048 23.7 17.4 19.9; 3072 44.8 64.9 50.0; 4096 98.8 62.5 59.1;
+//   row c2r   2048 18.1 21.5 32.2 (n = 1024); 3072 54.5 95.0 95.9; 4096 79.1 73.7 106;
+//   line rows 1024 9.2 10.2 13.4; 2048 17.7 16.5 20.4; 3072 45.8 67.1 50.6 (n = 2048),
+//             31.2 42.9 39.6 (n = 1500); 4096 68.6 49.8 60.7.
+// The mixed form keeps the schedule it was tuned with: another radix rounds its
+// FP32 transforms differently, which its results show at 1e-9.
+Schedule default_schedule(int L, bool mixed) {
     Schedule s;
+    if (!mixed) {
+        s.cols = supported_e(L, L == 4096 ? 16 : (L == 512 || L == 1536 || L == 2048 ? 8 : 4));
+        s.rinv = L == 4096 ? 8 : 4;
+        s.lrows = L == 2048 || L == 4096 ? 8 : 4;
+        s.sl = L == 4096 ? 8 : 4;
+        return s;
+    }
     if (fft_odd(L) == 3) {
-        // the radix-3 stage favours many threads per transform in the row
-        // passes; the column pass takes E = 8 at 1536 and 4 at 3072; the axis-2
-        // line-row kernel E = 4 at 1536 (4% faster than 8 on a 1024^2 solve) and
-        // E = 16 at 3072 (fewest registers per chunk of the FFT's operands)
         s.cols = L == 1536 ? 8 : 4;
         s.rinv = 4;
         s.lrows = supported_e(L, L >= 3072 ? 16 : 4);
@@ -1568,7 +1575,7 @@ int lpide_plan_create(const lpide_grid* grid, const lpide_levy* levy, const lpid
             if (e != hipSuccess) return bail(fail(LPIDE_E_HIP, std::string("spectrum32: ") + hipGetErrorString(e)));
         }
     }
-    p->sched = o.fft_radix ? uniform_schedule(o.fft_radix) : default_schedule(p->Lr);
+    p->sched = o.fft_radix ? uniform_schedule(o.fft_radix) : default_schedule(p->Lr, p->mixed);
     if (!schedule_ok(p->Lr, p->sched))
         return bail(fail(LPIDE_E_PARAM, "fft_radix " + std::to_string(o.fft_radix) + " is not supported at transform side " +
                                             std::to_string(p->Lr)));
@@ -1969,7 +1976,7 @@ int lpide_batch_tune(void* batch, int32_t trial_steps) {
         int rc = LPIDE_OK;
         // pass 1: radix schedule, one kernel class at a time from the default
         Schedule bs = g->lc.E_cols ? Schedule{g->lc.E_cols, g->lc.E_rinv, g->lc.E_lrows, g->lc.E_sl}
-                                   : default_schedule(g->lc.L);
+                                   : default_schedule(g->lc.L, g->lc.mixed);
         g->use_graph = true;
         g->slots = 32;
         if ((rc = set_schedule(g, bs)) || (rc = trial(&best))) return rc;

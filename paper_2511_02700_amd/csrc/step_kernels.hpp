@@ -452,12 +452,49 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
     const bool hasb = rb < n;
     const int tid = threadIdx.x;
     C reg[E];
+    if constexpr (MODE == 1) {
+        // everything but the B Y term first: its reads need no transform and are in
+        // flight with the gather's, and only stores follow the transform.  The two
+        // rows share their stencils' reads (twelve nodes for both).  Per launch at
+        // 2048^2 56 -> 47 us, at 512^2 9.9 -> 8.5, at 64^2 8.0 -> 6.7.
+        const GP<double> U(c.now.Y), W(c.now.W), R(a.R), Bout(c.now.B);
+        const double cf = c.now.cth, r_omega = a.r_omega;
+        const StencilArgs st = stencil(a);
+        const int o0 = max(ra - 1, 0) * n, o1 = ra * n, o2 = min(rb, n - 1) * n, o3 = min(rb + 1, n - 1) * n;
+        double g[E][2];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = min(tid + e * T, n - 1), jm = max(j - 1, 0), jp = min(j + 1, n - 1);
+            const double a0 = U[o0 + jm], a1 = U[o0 + j], a2 = U[o0 + jp], b0 = U[o1 + jm], b1 = U[o1 + j], b2 = U[o1 + jp];
+            const double c0 = U[o2 + jm], c1 = U[o2 + j], c2 = U[o2 + jp], d0 = U[o3 + jm], d1 = U[o3 + j], d2 = U[o3 + jp];
+            g[e][0] = W[o1 + j] + cf * (D_of(st, ra, j, b1, a1, c1, b0, b2, a0, a2, c0, c2) - r_omega * b1) - b1;
+            g[e][1] = W[o2 + j] + cf * (D_of(st, rb, j, c1, b1, d1, c0, c2, b0, b2, d0, d2) - r_omega * c1) - c1;
+            if constexpr (L > 1024) asm volatile("" : "+v"(g[e][0]), "+v"(g[e][1])::"memory");
+        }
+        // formed here: left to the compiler, the arithmetic moves behind the transform
+        // and the 14 values read per element stay in registers instead of g's two.  Up
+        // to 1024 all elements' reads are in flight together, above one element's.
+#pragma unroll
+        for (int e = 0; e < E; ++e) asm volatile("" : "+v"(g[e][0]), "+v"(g[e][1]));
+        rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
+        fft_block<L, E, true>(reg, lds, tw4);
+        const bool keepB = c.now.B != nullptr;       // B Y of the iterate, for the start of later steps
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = tid + e * T;
+            if (j >= n) continue;
+            if (keepB) Bout.put(o1 + j, reg[e].x);
+            R.put(o1 + j, g[e][0] + cf * reg[e].x);
+            if (hasb) {
+                if (keepB) Bout.put(o2 + j, reg[e].y);
+                R.put(o2 + j, g[e][1] + cf * reg[e].y);
+            }
+        }
+        return;
+    }
     rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
     fft_block<L, E, true>(reg, lds, tw4);
     constexpr bool EXPL = MODE == 0 || MODE == 4;
-    // FP64 iterations store B Y of the iterate for the start of later steps
-    const bool keepB = MODE == 1 && c.now.B != nullptr;
-    const GP<double> Bout(c.now.B);
     const GP<double> U(EXPL ? c.now.V : c.now.Y), P0(EXPL ? c.now.V : c.now.W);
     const GP<double> out(MODE == 4 ? c.now.W : (MODE == 0 ? c.now.Wp : a.R));
     const double cf = EXPL ? c.now.cex : c.now.cth, c0 = EXPL ? 0.0 : -1.0;
@@ -475,9 +512,6 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
             if (r == 1 && !hasb) break;
             const int i = ra + r, o = i * n + j;
             double bu = r == 0 ? (double)reg[e].x : (double)reg[e].y;
-            if constexpr (MODE == 1) {
-                if (keepB) Bout.put(o, bu);
-            }
             if constexpr (MODE == 2) {
                 bu += base[o];
                 BY.put(o, bu);
