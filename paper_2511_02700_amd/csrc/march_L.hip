@@ -20,24 +20,25 @@ namespace {
 template <int L>
 void launch_conv(Plan* p, const double* Y, double* out, double2* X) {
     const int n = p->hp.n, np = (n + 1) / 2;
-    hipLaunchKernelGGL((k_rows_fwd<L>), dim3(np), dim3(L / conv_e(L)), 0, p->stream, Y, n, n, n, X, n, p->tw);
-    hipLaunchKernelGGL((k_cols<L, 0>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, p->stream, X, n, n, n, p->spec,
-                       (double2*)nullptr, 0.0, p->tw);
-    hipLaunchKernelGGL((k_rows_inv<L>), dim3(np), dim3(L / conv_e(L)), 0, p->stream, X, n, n, out, p->tw);
+    constexpr int RE = rows_e(L), CE = cols_e(L);
+    hipLaunchKernelGGL((k_rows_fwd<L, RE>), dim3(np), dim3(L / RE), 0, p->stream, Y, n, n, n, X, n, p->tw);
+    hipLaunchKernelGGL((k_cols_apply<L, CE>), dim3(apply_col_blocks(L)), dim3(L / CE), 0, p->stream, X, n, p->spec, p->tw);
+    hipLaunchKernelGGL((k_rows_inv<L, RE>), dim3(np), dim3(L / RE), 0, p->stream, X, n, n, out, p->tw);
 }
 
 template <int L>
 void launch_spectrum(Plan* p, const double* G, double2* Xfull) {
+    constexpr int E = conv_e(L);
     const double scale = 1.0 / (double(L) * double(L));
-    hipLaunchKernelGGL((k_rows_fwd<L>), dim3(L / 2), dim3(L / conv_e(L)), 0, p->stream, G, L, L, L, Xfull, L, p->tw);
-    hipLaunchKernelGGL((k_cols<L, 1>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, p->stream, Xfull, L, L, L,
-                       (const double2*)nullptr, p->spec, scale, p->tw);
+    hipLaunchKernelGGL((k_rows_fwd<L, E>), dim3(L / 2), dim3(L / E), 0, p->stream, G, L, L, L, Xfull, L, p->tw);
+    hipLaunchKernelGGL((k_cols<L, 1>), dim3(L / 2 + 1), dim3(L / E), 0, p->stream, Xfull, L, L, L, p->spec, scale, p->tw);
 }
 
 template <int L>
 void launch_rows_fwd(Plan* p, const double* Y, hipStream_t s) {
+    constexpr int E = rows_e(L);
     const int n = p->hp.n;
-    hipLaunchKernelGGL((k_rows_fwd<L>), dim3((n + 1) / 2), dim3(L / conv_e(L)), 0, s, Y, n, n, n, p->X, n, p->tw);
+    hipLaunchKernelGGL((k_rows_fwd<L, E>), dim3((n + 1) / 2), dim3(L / E), 0, s, Y, n, n, n, p->X, n, p->tw);
 }
 
 // The axis-1 line-solve kernel for the launch's columns per block; bounds of
@@ -347,14 +348,15 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
     else
         hipLaunchKernelGGL(ks_adj_accum<3>, dim3(n, 1), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, Y, V, E, a->acc);
     if (p->jumps) {
+        constexpr int RE = rows_e(L);
         const int np = (n + 1) / 2;
         // the row transform of Y = V^{s+1} is the V transform of reverse step s + 1 when it had one;
         // those of lam (XA) and mu (XC) are in place already
         if (a->xb_is_v) std::swap(a->XB, a->XD);
-        else hipLaunchKernelGGL((k_rows_fwd<L>), dim3(np), dim3(L / conv_e(L)), 0, c.stream, Y, n, n, n, a->XB, n, p->tw);
+        else hipLaunchKernelGGL((k_rows_fwd<L, RE>), dim3(np), dim3(L / RE), 0, c.stream, Y, n, n, n, a->XB, n, p->tw);
         a->xb_is_v = false;
         if (c2 != 0.0) {
-            hipLaunchKernelGGL((k_rows_fwd<L>), dim3(np), dim3(L / conv_e(L)), 0, c.stream, V, n, n, n, a->XD, n, p->tw);
+            hipLaunchKernelGGL((k_rows_fwd<L, RE>), dim3(np), dim3(L / RE), 0, c.stream, V, n, n, n, a->XD, n, p->tw);
             a->xb_is_v = true;
         }
         hipLaunchKernelGGL((ks_adj_spec<L>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, c.stream, a->XA, a->XB, a->XC, a->XD, n,
@@ -371,9 +373,10 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
 template <int L>
 void launch_adj_kernel_grad(Plan* p, hipStream_t s) {
     Adjoint* a = p->adj;
-    hipLaunchKernelGGL((k_cols<L, 2>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, s, a->S, L, L, L, (const double2*)nullptr,
-                       (double2*)nullptr, 0.0, p->tw);
-    hipLaunchKernelGGL((k_rows_inv<L>), dim3(L / 2), dim3(L / conv_e(L)), 0, s, (const double2*)a->S, L, L, a->G, p->tw);
+    hipLaunchKernelGGL((k_cols<L, 2>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, s, a->S, L, L, L, (double2*)nullptr, 0.0,
+                       p->tw);
+    hipLaunchKernelGGL((k_rows_inv<L, rows_e(L)>), dim3(L / 2), dim3(L / rows_e(L)), 0, s, (const double2*)a->S, L, L, a->G,
+                       p->tw);
 }
 
 }  // namespace

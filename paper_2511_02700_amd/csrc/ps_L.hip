@@ -61,9 +61,9 @@ void PsL<L>::spectrum(hipStream_t s, const double* W, int W2, double2* Xf, doubl
                            (double2*)nullptr, PsOps{}, (const double2*)nullptr, spec, scale, tw, twM,
                            (const PsCtl*)nullptr, 0, 0.0);
     } else {
-        hipLaunchKernelGGL((k_rows_fwd<L>), dim3((W2 + 1) / 2), dim3(L / conv_e(L)), 0, s, W, W2, W2, W2, Xf, W2, tw);
-        hipLaunchKernelGGL((k_cols<L, 1>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, s, Xf, W2, W2, L,
-                           (const double2*)nullptr, spec, scale, tw);
+        hipLaunchKernelGGL((k_rows_fwd<L, conv_e(L)>), dim3((W2 + 1) / 2), dim3(L / conv_e(L)), 0, s, W, W2, W2, W2, Xf, W2, tw);
+        hipLaunchKernelGGL((k_cols<L, 1>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, s, Xf, W2, W2, L, spec,
+                           scale, tw);
     }
 }
 
