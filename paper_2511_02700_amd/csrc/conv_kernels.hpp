@@ -11,8 +11,9 @@
 // rows at L = 512: 3.6 against 3.9, but L = 768: 5.1 against 4.7).
 // In the same way the two real columns 0 and L/2 share one transform only where the
 // column pass is several waves of blocks (pair_cols): at L = 512 that block's longer
-// chain makes the pass 5.0 us against 4.2.  B v: 33.8 -> 33.1 us at n = 1001, 49.2 -> 43.4 at n = 1200 in L = 2048,
-// 118 -> 80 at n = 1400 in L = 3072, 139 -> 96 at n = 2000.
+// chain makes the pass 5.0 us against 4.2.  B v: 33.8 -> 33.1 us at n = 1001,
+// 49.2 -> 43.4 at n = 1200 in L = 2048, 118 -> 81 at n = 1400 in L = 3072, 139 -> 97
+// at n = 2000.
 // The plan-time spectrum keeps conv_e(L) elements: the mixed form's results
 // answer a change of its rounding at 1e-9.
 #pragma once

@@ -114,69 +114,25 @@ __device__ __forceinline__ void apply_D_parts(GP<double> U, int n, double h, int
     d12 = gi * gj * ((u11 - u10) - (u01 - u00));
 }
 
-// Column p of the one-dimensional first-difference matrix G used by the mixed
-// term (rows: central inside, forward at 0, backward at n-1): the (at most two)
-// rows r with G[r][p] != 0 and those entries.
-__device__ __forceinline__ int diff_T(int n, double h, int p, int* r, double* c) {
-    int m = 0;
-    const double i2h = 0.5 / h, ih = 1.0 / h;
-    if (p - 1 >= 1 && p - 1 <= n - 2) { r[m] = p - 1; c[m] = i2h; ++m; }    // G[p-1][p]
-    if (p + 1 >= 1 && p + 1 <= n - 2) { r[m] = p + 1; c[m] = -i2h; ++m; }   // G[p+1][p]
-    if (p == 0) { r[m] = 0; c[m] = -ih; ++m; }                               // row 0: (v1 - v0)/h
-    if (p == 1) { r[m] = 0; c[m] = ih; ++m; }
-    if (p == n - 2) { r[m] = n - 1; c[m] = -ih; ++m; }                       // row n-1: (v_{n-1} - v_{n-2})/h
-    if (p == n - 1) { r[m] = n - 1; c[m] = ih; ++m; }
-    return m;
-}
-
-// D^T applied to U at (i, j): the transposed log-grid stencil, boundary rows
-// included (the adjoint of apply_D).
-__device__ __forceinline__ double apply_DT(GP<double> U, const StencilArgs& s, int i, int j, double u) {
+// D^T u at (i, j), the transposed log-grid stencil with the boundary rows' terms:
+// arguments as D_of (neighbours clamped into the grid).  Every node takes the same
+// reads and arithmetic, the edges by their weights: row r of a second difference
+// exists for interior r only, and the rows of the first-difference matrix of the
+// mixed term are central inside, forward at 0 and backward at n - 1.
+__device__ __forceinline__ double DT_of(const StencilArgs& s, int i, int j, double u, double u1m, double u1p, double u2m,
+                                        double u2p, double u00, double u01, double u10, double u11) {
     const int n = s.n;
-    const double ih2 = 1.0 / (s.h * s.h), i2h = 0.5 / s.h;
-    // Away from the edges (every neighbour an interior node) the transposed
-    // stencil is the forward one with the first differences negated: the
-    // second differences and the product of two central differences are
-    // symmetric, a central difference is antisymmetric.
-    if (i >= 2 && i <= n - 3 && j >= 2 && j <= n - 3) {
-        const double u1m = U[(i - 1) * n + j], u1p = U[(i + 1) * n + j];
-        const double u2m = U[i * n + j - 1], u2p = U[i * n + j + 1];
-        double d = 0.5 * s.a11 * ((u1p - 2.0 * u + u1m) * ih2 + (u1p - u1m) * i2h) +
-                   0.5 * s.a22 * ((u2p - 2.0 * u + u2m) * ih2 + (u2p - u2m) * i2h);
-        if (s.a12 != 0.0) {
-            const int rm = (i - 1) * n, rp = (i + 1) * n;
-            d += s.a12 * i2h * i2h * ((U[rp + j + 1] - U[rp + j - 1]) - (U[rm + j + 1] - U[rm + j - 1]));
-        }
-        return d;
-    }
-    // second-difference parts: row r (interior) holds 1/2 [(v_{r+1} - 2 v_r + v_{r-1})/h^2 - (v_{r+1} - v_{r-1})/(2h)]
+    const double ih2 = 1.0 / (s.h * s.h), i2h = 0.5 / s.h, ih = 1.0 / s.h;
     const double cu = 0.5 * (ih2 - i2h);   // coefficient of v_{r+1} in row r
     const double cl = 0.5 * (ih2 + i2h);   // coefficient of v_{r-1} in row r
-    double d = 0.0;
-    {
-        double t = 0.0;
-        if (i > 0 && i < n - 1) t -= ih2 * u;
-        if (i - 1 >= 1 && i - 1 <= n - 2) t += cu * U[(i - 1) * n + j];
-        if (i + 1 >= 1 && i + 1 <= n - 2) t += cl * U[(i + 1) * n + j];
-        d += s.a11 * t;
-    }
-    {
-        double t = 0.0;
-        if (j > 0 && j < n - 1) t -= ih2 * u;
-        if (j - 1 >= 1 && j - 1 <= n - 2) t += cu * U[i * n + j - 1];
-        if (j + 1 >= 1 && j + 1 <= n - 2) t += cl * U[i * n + j + 1];
-        d += s.a22 * t;
-    }
-    if (s.a12 != 0.0) {
-        int ri[4], rj[4];
-        double ci[4], cj[4];
-        const int mi = diff_T(n, s.h, i, ri, ci), mj = diff_T(n, s.h, j, rj, cj);
-        double t = 0.0;
-        for (int a = 0; a < mi; ++a)
-            for (int b = 0; b < mj; ++b) t += ci[a] * cj[b] * U[ri[a] * n + rj[b]];
-        d += s.a12 * t;
-    }
-    return d;
+    auto second = [&](int p, double v, double vm, double vp) {
+        return (p >= 2 ? cu : 0.0) * vm + (p <= n - 3 ? cl : 0.0) * vp - (p > 0 && p < n - 1 ? ih2 : 0.0) * v;
+    };
+    // entries of column p in the rows max(p - 1, 0) and min(p + 1, n - 1)
+    auto lo = [&](int p) { return p == 0 ? -ih : (p == 1 ? ih : i2h); };
+    auto hi = [&](int p) { return p == n - 1 ? ih : (p == n - 2 ? -ih : -i2h); };
+    return s.a11 * second(i, u, u1m, u1p) + s.a22 * second(j, u, u2m, u2p) +
+           s.a12 * (lo(i) * (lo(j) * u00 + hi(j) * u01) + hi(i) * (lo(j) * u10 + hi(j) * u11));
 }
 
 }  // namespace lpide

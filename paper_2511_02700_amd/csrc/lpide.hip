@@ -956,6 +956,7 @@ void destroy_adjoint(Adjoint* a) {
     if (!a) return;
     for (void* x : a->allocs) (void)hipFree(x);
     if (a->ctl_h) (void)hipHostFree(a->ctl_h);
+    if (a->verdict) (void)hipEventDestroy(a->verdict);
     delete a;
 }
 
@@ -987,16 +988,15 @@ int adj_prepare(Plan* p, int C) {
         (rc = dalloc_into(al, nullptr, &a->incs, p->n_steps)) || (rc = dalloc_into(al, nullptr, &a->A, 1)))
         return rc;
     if (p->jumps) {
-        if ((rc = dalloc_into(al, nullptr, &a->XA, (size_t)hc * n)) ||
-            (rc = dalloc_into(al, nullptr, &a->XB, (size_t)hc * n)) ||
-            (rc = dalloc_into(al, nullptr, &a->XC, (size_t)hc * n)) ||
-            (rc = dalloc_into(al, nullptr, &a->XD, (size_t)hc * n)) ||
+        if ((rc = dalloc_into(al, nullptr, &a->XM, (size_t)hc * n)) ||
+            (rc = dalloc_into(al, nullptr, &a->XV, (size_t)hc * n)) ||
             (rc = dalloc_into(al, nullptr, &a->S, (size_t)hc * L)) ||
             (rc = dalloc_into(al, nullptr, &a->G, (size_t)L * L)))
             return rc;
     }
     if (hipHostMalloc((void**)&a->ctl_h, sizeof(Ctl), hipHostMallocDefault) != hipSuccess)
         return fail(LPIDE_E_OOM, "hipHostMalloc failed");
+    HIP_TRY(hipEventCreateWithFlags(&a->verdict, hipEventDisableTiming));
     a->counts_h.assign(p->n_steps, 0);
     // transposed step sets
     for (const StepDesc& fs : p->sets) {
@@ -1078,8 +1078,8 @@ int dispatch_adj_step(Plan* p, const Launch& c, int s, int* kpred, const double*
     return LPIDE_OK;
 }
 
-int dispatch_adj_kernel_grad(Plan* p, hipStream_t s) {
-#define CALL_KG(Lc) PerL<Lc>::adj_kernel_grad(p, s)
+int dispatch_adj_kernel_grad(Plan* p, const double* V, hipStream_t s) {
+#define CALL_KG(Lc) PerL<Lc>::adj_kernel_grad(p, V, s)
     LPIDE_SWITCH_L(p->L, CALL_KG)
 #undef CALL_KG
     HIP_TRY(hipGetLastError());
@@ -1220,7 +1220,7 @@ int adjoint(Plan* p, const double* v_bar, int C, std::vector<double>& native, lp
     int64_t iters = 0;
     int maxit = 0;
     a->have_corr = 0;
-    a->xb_is_v = false;
+    a->mu_c = 0.0;
     for (int q = (Ns - 1) / C; q >= 0; --q) {
         const int s0 = q * C, s1 = std::min(Ns, s0 + C);
         auto ta = now();
@@ -1256,7 +1256,7 @@ int adjoint(Plan* p, const double* v_bar, int C, std::vector<double>& native, lp
         native[q] = t;
     }
     if (p->jumps) {
-        if ((rc = dispatch_adj_kernel_grad(p, s))) return rc;
+        if ((rc = dispatch_adj_kernel_grad(p, a->seg, s))) return rc;    // seg[0]: V^0, of the segment reversed last
         const int L = p->L;
         std::vector<double> G((size_t)L * L);
         HIP_TRY(hipMemcpyAsync(G.data(), a->G, sizeof(double) * G.size(), hipMemcpyDeviceToHost, s));

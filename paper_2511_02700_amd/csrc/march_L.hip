@@ -278,12 +278,54 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
         hipLaunchKernelGGL((ks_adj_start<L, E>), gr, dim3(L / E), 0, c.stream, c.A, (const Ctl*)c.C, cp[0], cw[0], cp[1], cw[1], cp[2],
                            cw[2], cp[3], cw[3]);
     });
+    double* const corr_new = a->corr[3];
+    const double c1 = sd.dt * sd.theta, c2 = sd.dt * (1.0 - sd.theta);
+    // What follows the fixed point, in stream order behind its verdict: every kernel with a
+    // lasting effect leaves at once if the verdict was failure.  While lam's row transform
+    // is in X (the last iteration left it there), the spectral gradient term of V^{s+1};
+    // then mu = (T^SL)^T lam, the cotangent of V^s and the other gradient terms.
+    auto finish = [&] {
+        if (p->jumps) {
+            constexpr int RE = rows_e(L), CE = cols_e(L);
+            hipLaunchKernelGGL((k_rows_fwd<L, RE>), dim3((n + 1) / 2), dim3(L / RE), 0, c.stream, Y, n, n, n, a->XV, n, p->tw);
+            hipLaunchKernelGGL((ks_adj_spec<L, CE>), dim3(L / 2 + 1, 1), dim3(L / CE), 0, c.stream, c.A, (const Ctl*)c.C, a->XM,
+                               a->XV, c1, a->mu_c, a->S);
+        }
+        double2* x2 = (p->jumps && c2 != 0.0) ? a->XM : nullptr;
+        const bool narrow = sd.wt1 <= 8 && sd.wt2 <= 8;
+        with_E<L>(c.E_sl, [&](auto e) {
+            constexpr int E = decltype(e)::value;
+            if (narrow)
+                hipLaunchKernelGGL((ks_adj_sl<L, E, 8>), gr, dim3(L / E), 0, c.stream, c.A, (const Ctl*)c.C, x2, corr_new);
+            else
+                hipLaunchKernelGGL((ks_adj_sl<L, E, 0>), gr, dim3(L / E), 0, c.stream, c.A, (const Ctl*)c.C, x2, corr_new);
+        });
+        if (sd.theta < 1.0) {
+            with_E<L>(c.E_cols, [&](auto e) {
+                constexpr int E = decltype(e)::value;
+                hipLaunchKernelGGL((ks_cols<L, E, double2, true>), dim3(L / 2, 1), dim3(L / E), 0, c.stream, c.A, c.C, 0);
+            });
+            with_E<L>(c.E_rinv, [&](auto e) {
+                constexpr int E = decltype(e)::value;
+                hipLaunchKernelGGL((ks_rows_inv<L, E, 4>), gr, dim3(L / E), 0, c.stream, c.A, c.C, 0);
+            });
+        }
+        if (p->hp.sl_order == 1)
+            hipLaunchKernelGGL(ks_adj_accum<1>, dim3(n, 1), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, Y, V, E, a->acc);
+        else
+            hipLaunchKernelGGL(ks_adj_accum<3>, dim3(n, 1), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, Y, V, E, a->acc);
+    };
     int k = *kpred;
     for (int q = 1; q <= k; ++q) launch_adj_iteration<L>(c, q);
     hipLaunchKernelGGL(ks_adj_end, dim3(1), dim3(64), 0, c.stream, c.A, c.C, k);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(a->ctl_h, a->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, c.stream));
-    HIP_TRY(hipStreamSynchronize(c.stream));
+    HIP_TRY(hipEventRecord(a->verdict, c.stream));
+    finish();
+    HIP_TRY(hipGetLastError());
+    // the verdict is waited for with the rest of the step on its way (a wait for the whole
+    // stream left the device idle for a round trip in every reverse step)
+    HIP_TRY(hipEventSynchronize(a->verdict));
     while (a->ctl_h->fail) {
         const double ek = err_of(*a->ctl_h, k);
         if (!std::isfinite(ek)) return fail(LPIDE_E_NAN, "non-finite adjoint increment in step " + std::to_string(s));
@@ -300,83 +342,42 @@ int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipMemcpyAsync(a->ctl_h, a->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, c.stream));
         HIP_TRY(hipStreamSynchronize(c.stream));
+        if (!a->ctl_h->fail) finish();
     }
     int used = k;
     for (int q = 1; q <= k; ++q)
         if (err_of(*a->ctl_h, q) < p->opts.tol) { used = q; break; }
-    // the last iteration left the row transform of the converged lam in X:
-    // kept for the spectral gradient term (the transposed SL overwrites X)
-    const size_t xbytes = sizeof(double2) * (size_t)(L / 2 + 1) * n;
-    if (p->jumps) HIP_TRY(hipMemcpyAsync(a->XA, p->X, xbytes, hipMemcpyDeviceToDevice, c.stream));
     a->counts_h[s] = used;
     *kpred = std::max(1, std::min(p->opts.max_iter, used));
-    const int sb = int(std::min<size_t>(1024, (N + 255) / 256));
-    {
-        double* oldest = a->corr[3];
-        for (int q = 3; q > 0; --q) {
-            a->corr[q] = a->corr[q - 1];
-            a->corr_c[q] = a->corr_c[q - 1];
-        }
-        a->corr[0] = oldest;
+    for (int q = 3; q > 0; --q) {
+        a->corr[q] = a->corr[q - 1];
+        a->corr_c[q] = a->corr_c[q - 1];
     }
-    hipLaunchKernelGGL(ks_adj_corr, dim3(sb), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, a->corr[0]);
-    a->have_corr = std::min(4, a->have_corr + 1);
+    a->corr[0] = corr_new;
     a->corr_c[0] = cth;
-    // mu = (T^SL)^T lam (its row transform also into XC for the spectral
-    // gradient term when theta < 1), then the cotangent of V^s
-    const double c1 = sd.dt * sd.theta, c2 = sd.dt * (1.0 - sd.theta);
-    double2* x2 = (p->jumps && c2 != 0.0) ? a->XC : nullptr;
-    const bool narrow = sd.wt1 <= 8 && sd.wt2 <= 8;
-    with_E<L>(c.E_sl, [&](auto e) {
-        constexpr int E = decltype(e)::value;
-        if (narrow) hipLaunchKernelGGL((ks_adj_sl<L, E, 8>), gr, dim3(L / E), 0, c.stream, c.A, (const Ctl*)c.C, x2);
-        else hipLaunchKernelGGL((ks_adj_sl<L, E, 0>), gr, dim3(L / E), 0, c.stream, c.A, (const Ctl*)c.C, x2);
-    });
-    if (sd.theta < 1.0) {
-        with_E<L>(c.E_cols, [&](auto e) {
-            constexpr int E = decltype(e)::value;
-            hipLaunchKernelGGL((ks_cols<L, E, double2, true>), dim3(L / 2, 1), dim3(L / E), 0, c.stream, c.A, c.C, 0);
-        });
-        with_E<L>(c.E_rinv, [&](auto e) {
-            constexpr int E = decltype(e)::value;
-            hipLaunchKernelGGL((ks_rows_inv<L, E, 4>), gr, dim3(L / E), 0, c.stream, c.A, c.C, 0);
-        });
-    }
-    // gradient terms (they read lam and mu; the new cotangent is written last)
-    if (p->hp.sl_order == 1)
-        hipLaunchKernelGGL(ks_adj_accum<1>, dim3(n, 1), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, Y, V, E, a->acc);
-    else
-        hipLaunchKernelGGL(ks_adj_accum<3>, dim3(n, 1), dim3(256), 0, c.stream, c.A, (const Ctl*)c.C, Y, V, E, a->acc);
-    if (p->jumps) {
-        constexpr int RE = rows_e(L);
-        const int np = (n + 1) / 2;
-        // the row transform of Y = V^{s+1} is the V transform of reverse step s + 1 when it had one;
-        // those of lam (XA) and mu (XC) are in place already
-        if (a->xb_is_v) std::swap(a->XB, a->XD);
-        else hipLaunchKernelGGL((k_rows_fwd<L, RE>), dim3(np), dim3(L / RE), 0, c.stream, Y, n, n, n, a->XB, n, p->tw);
-        a->xb_is_v = false;
-        if (c2 != 0.0) {
-            hipLaunchKernelGGL((k_rows_fwd<L, RE>), dim3(np), dim3(L / RE), 0, c.stream, V, n, n, n, a->XD, n, p->tw);
-            a->xb_is_v = true;
-        }
-        hipLaunchKernelGGL((ks_adj_spec<L>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, c.stream, a->XA, a->XB, a->XC, a->XD, n,
-                           c1, c2, a->S, p->tw);
-    }
-    if (sd.theta >= 1.0)
-        hipLaunchKernelGGL(k_copy, dim3((N + 255) / 256), dim3(256), 0, c.stream, a->mu, a->ybar, N);
+    a->have_corr = std::min(4, a->have_corr + 1);
+    a->mu_c = c2;
     HIP_TRY(hipGetLastError());
     return LPIDE_OK;
 }
 
-// Inverse 2D transform of the spectral accumulator (column inverse FFTs in
-// place, then the row c2r): G[d1 mod L][d2 mod L] = L^2 x (kernel gradient).
+// The spectral term of V^0 with the last reverse step's mu, then the inverse 2D
+// transform of the accumulator (column inverse FFTs in place, then the row c2r):
+// G[d1 mod L][d2 mod L] = L^2 x (kernel gradient).
 template <int L>
-void launch_adj_kernel_grad(Plan* p, hipStream_t s) {
+void launch_adj_kernel_grad(Plan* p, const double* V, hipStream_t s) {
     Adjoint* a = p->adj;
+    constexpr int RE = rows_e(L), CE = cols_e(L);
+    const int n = p->hp.n;
+    if (a->mu_c != 0.0) {
+        hipLaunchKernelGGL((k_rows_fwd<L, RE>), dim3((n + 1) / 2), dim3(L / RE), 0, s, V, n, n, n, a->XV, n, p->tw);
+        hipLaunchKernelGGL((ks_adj_spec<L, CE>), dim3(L / 2 + 1, 1), dim3(L / CE), 0, s, a->A, (const Ctl*)a->ctl, a->XM, a->XV,
+                           0.0, a->mu_c, a->S);
+        a->mu_c = 0.0;
+    }
     hipLaunchKernelGGL((k_cols<L, 2>), dim3(L / 2 + 1), dim3(L / conv_e(L)), 0, s, a->S, L, L, L, (double2*)nullptr, 0.0,
                        p->tw);
-    hipLaunchKernelGGL((k_rows_inv<L, rows_e(L)>), dim3(L / 2), dim3(L / rows_e(L)), 0, s, (const double2*)a->S, L, L, a->G,
-                       p->tw);
+    hipLaunchKernelGGL((k_rows_inv<L, RE>), dim3(L / 2), dim3(L / RE), 0, s, (const double2*)a->S, L, L, a->G, p->tw);
 }
 
 }  // namespace
@@ -396,7 +397,7 @@ int PerL<L>::adj_step(Plan* p, const Launch& c, int s, int* kpred, const double*
     return ::lpide::detail::adj_step<L>(p, c, s, kpred, Y, V, E);
 }
 template <int L>
-void PerL<L>::adj_kernel_grad(Plan* p, hipStream_t s) { launch_adj_kernel_grad<L>(p, s); }
+void PerL<L>::adj_kernel_grad(Plan* p, const double* V, hipStream_t s) { launch_adj_kernel_grad<L>(p, V, s); }
 
 template struct PerL<LPIDE_L>;
 

@@ -186,8 +186,9 @@ struct Adjoint {
     double* corr[4] = {};            // lam - Ybar of the last reverse steps, newest first
     double corr_c[4] = {};           // dt theta of those steps
     int have_corr = 0;               // how many of corr[] are set
-    bool xb_is_v = false;            // XD holds the row transform of V^{s+1} from the previous reverse step
-    double2 *XA = nullptr, *XB = nullptr, *XC = nullptr, *XD = nullptr;
+    double2 *XM = nullptr, *XV = nullptr;   // row transforms of mu of the last reverse step and of V
+    double mu_c = 0.0;               // weight of that mu's spectral gradient term, still to be added (0: none)
+    hipEvent_t verdict = nullptr;    // behind the copy of a reverse step's control block to ctl_h
     double2* S = nullptr;           // (L/2+1) x L spectral accumulator
     double* G = nullptr;            // L x L inverse transform of S
     double* acc = nullptr;          // n x 8 per-row accumulators
@@ -249,7 +250,7 @@ struct PerL {
     static void rows_fwd(Plan* p, const double* Y, hipStream_t s);
     static int adj_step(Plan* p, const Launch& c, int s, int* kpred, const double* Y, const double* V,
                         const double* E);
-    static void adj_kernel_grad(Plan* p, hipStream_t s);
+    static void adj_kernel_grad(Plan* p, const double* V, hipStream_t s);
 };
 extern template struct PerL<64>;
 extern template struct PerL<128>;

@@ -452,13 +452,15 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
     const bool hasb = rb < n;
     const int tid = threadIdx.x;
     C reg[E];
-    if constexpr (MODE == 1) {
-        // everything but the B Y term first: its reads need no transform and are in
+    if constexpr (MODE == 1 || MODE >= 3) {
+        // everything but the correlation's term first: its reads need no transform and are in
         // flight with the gather's, and only stores follow the transform.  The two
         // rows share their stencils' reads (twelve nodes for both).  Per launch at
-        // 2048^2 56 -> 47 us, at 512^2 9.9 -> 8.5, at 64^2 8.0 -> 6.7.
-        const GP<double> U(c.now.Y), W(c.now.W), R(a.R), Bout(c.now.B);
-        const double cf = c.now.cth, r_omega = a.r_omega;
+        // 2048^2 56 -> 47 us, at 512^2 9.9 -> 8.5, at 64^2 8.0 -> 6.7; the adjoint's,
+        // with the edges as weights instead of a path of their own, at 512^2 13.1 -> 9.0.
+        const GP<double> U(MODE == 4 ? c.now.V : c.now.Y), W(MODE == 4 ? c.now.V : c.now.W),
+            R(MODE == 4 ? c.now.W : a.R), Bout(c.now.B);
+        const double cf = MODE == 4 ? c.now.cex : c.now.cth, r_omega = a.r_omega;
         const StencilArgs st = stencil(a);
         const int o0 = max(ra - 1, 0) * n, o1 = ra * n, o2 = min(rb, n - 1) * n, o3 = min(rb + 1, n - 1) * n;
         double g[E][2];
@@ -467,8 +469,15 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
             const int j = min(tid + e * T, n - 1), jm = max(j - 1, 0), jp = min(j + 1, n - 1);
             const double a0 = U[o0 + jm], a1 = U[o0 + j], a2 = U[o0 + jp], b0 = U[o1 + jm], b1 = U[o1 + j], b2 = U[o1 + jp];
             const double c0 = U[o2 + jm], c1 = U[o2 + j], c2 = U[o2 + jp], d0 = U[o3 + jm], d1 = U[o3 + j], d2 = U[o3 + jp];
-            g[e][0] = W[o1 + j] + cf * (D_of(st, ra, j, b1, a1, c1, b0, b2, a0, a2, c0, c2) - r_omega * b1) - b1;
-            g[e][1] = W[o2 + j] + cf * (D_of(st, rb, j, c1, b1, d1, c0, c2, b0, b2, d0, d2) - r_omega * c1) - c1;
+            if constexpr (MODE == 1) {
+                g[e][0] = W[o1 + j] + cf * (D_of(st, ra, j, b1, a1, c1, b0, b2, a0, a2, c0, c2) - r_omega * b1) - b1;
+                g[e][1] = W[o2 + j] + cf * (D_of(st, rb, j, c1, b1, d1, c0, c2, b0, b2, d0, d2) - r_omega * c1) - c1;
+            } else {
+                const double ga = cf * (DT_of(st, ra, j, b1, a1, c1, b0, b2, a0, a2, c0, c2) - r_omega * b1);
+                const double gb = cf * (DT_of(st, rb, j, c1, b1, d1, c0, c2, b0, b2, d0, d2) - r_omega * c1);
+                g[e][0] = MODE == 4 ? b1 + ga : W[o1 + j] + ga - b1;
+                g[e][1] = MODE == 4 ? c1 + gb : W[o2 + j] + gb - c1;
+            }
             if constexpr (L > 1024) asm volatile("" : "+v"(g[e][0]), "+v"(g[e][1])::"memory");
         }
         // formed here: left to the compiler, the arithmetic moves behind the transform
@@ -478,7 +487,7 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
         for (int e = 0; e < E; ++e) asm volatile("" : "+v"(g[e][0]), "+v"(g[e][1]));
         rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
         fft_block<L, E, true>(reg, lds, tw4);
-        const bool keepB = c.now.B != nullptr;       // B Y of the iterate, for the start of later steps
+        const bool keepB = MODE == 1 && c.now.B != nullptr;       // B Y of the iterate, for the start of later steps
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int j = tid + e * T;
@@ -494,9 +503,9 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
     }
     rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
     fft_block<L, E, true>(reg, lds, tw4);
-    constexpr bool EXPL = MODE == 0 || MODE == 4;
+    constexpr bool EXPL = MODE == 0;
     const GP<double> U(EXPL ? c.now.V : c.now.Y), P0(EXPL ? c.now.V : c.now.W);
-    const GP<double> out(MODE == 4 ? c.now.W : (MODE == 0 ? c.now.Wp : a.R));
+    const GP<double> out(MODE == 0 ? c.now.Wp : a.R);
     const double cf = EXPL ? c.now.cex : c.now.cth, c0 = EXPL ? 0.0 : -1.0;
     const bool want_r = MODE != 0 || c.now.expl != EXPL_NONE;
     const GP<double> base((MODE == 2 && k == 1 && c.now.anchor) ? a.BV : a.BY), BY(a.BY), BV(a.BV);
@@ -521,8 +530,7 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
             }
             if (want_r) {
                 const double u = U[o];
-                const double d = MODE >= 3 ? apply_DT(U, st, i, j, u) : apply_D(U, st, i, j, u);
-                out.put(o, P0[o] + cf * (d + bu - r_omega * u) + c0 * u);
+                out.put(o, P0[o] + cf * (apply_D(U, st, i, j, u) + bu - r_omega * u) + c0 * u);
             }
         }
     }
@@ -1178,19 +1186,6 @@ __global__ __launch_bounds__(L / E) void ks_adj_start(const MarchArgs* __restric
     rows_fwd_store<L, E>(reg, lds, tw4, xbuf<double2>(a), n, ra, hasb);
 }
 
-// corr = lam - Ybar after the adjoint fixed point converged (start of the next
-// reverse step).
-static __global__ void ks_adj_corr(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs,
-                                   double* __restrict__ corr) {
-    Args& a = plan_args(A);
-    CtlK& c = plan_ctl(Cs);
-    if (halted(a, c, 0)) return;
-    const size_t N = (size_t)a.n * a.n;
-    const GP<double> lam(c.now.Y), Yb(c.now.W);
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (size_t)gridDim.x * blockDim.x)
-        corr[i] = lam[i] - Yb[i];
-}
-
 // Verdict of the adjoint fixed point of the current reverse step: iteration
 // count (first k with err_k < tol) or the failure flag.
 static __global__ void ks_adj_end(const MarchArgs* __restrict__ A, Ctl* __restrict__ Cs, int kmax) {
@@ -1213,15 +1208,18 @@ static __global__ void ks_adj_end(const MarchArgs* __restrict__ A, Ctl* __restri
     }
 }
 
-// mu = (T_1^T (x) T_2^T) lam (the transposed semi-Lagrangian gather) into
-// pool[0]; when theta < 1 also its row transform for B^T mu, into X and, if
-// X2 is not null, into X2 as well (the spectral gradient term reads it).
-// WM > 0: the transposed tables are at most WM wide (the host checks), so
-// each thread holds its columns' sources and weights in registers and the
-// loops have fixed bounds; WM = 0: any width.
+// mu = (T_1^T (x) T_2^T) lam (the transposed semi-Lagrangian gather) into pool[0]
+// and corr = lam - Ybar (start of later reverse steps); when theta < 1 also mu's row
+// transform for B^T mu, into X and into X2 (the spectral gradient term of the next
+// reverse step reads it), otherwise mu is the cotangent of V^s and goes to Ybar as well.
+// One axis after the other: the rows' combination of axis 1 by coalesced reads into
+// LDS, the columns' of axis 2 from there (W1 + W2 terms per node; all W1 W2 of them
+// gathered from memory, and corr by a kernel of its own, took 18.3 + 4 us at 512^2; now 14.1).
+// WM > 0: the transposed tables are at most WM wide (the host checks): fixed bounds,
+// terms past the width are the last one's with weight 0; WM = 0: any width.
 template <int L, int E, int WM>
 __global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs,
-                                                  double2* __restrict__ X2) {
+                                                  double2* __restrict__ X2, double* __restrict__ corr) {
     Args& a = plan_args(A);
     CtlK& c = plan_ctl(Cs);
     if (halted(a, c, 0)) return;
@@ -1236,88 +1234,82 @@ __global__ __launch_bounds__(L / E) void ks_adj_sl(const MarchArgs* __restrict__
     if (fft) load_twiddles<L, E>(GP<double2>(a.tw), tw4);
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
-    const GP<double> lam(c.now.Y), mu(c.now.V), t1w(sd.t1w), t2w(sd.t2w);
+    const int rs = hasb ? rb : ra;
+    const GP<double> lam(c.now.Y), mu(c.now.V), Yb(c.now.W), t1w(sd.t1w), t2w(sd.t2w), cr(corr);
     const GP<int> t1i(sd.t1i), t2i(sd.t2i);
     const int W1 = sd.wt1, W2 = sd.wt2;
-    double outv[E][2];
     if constexpr (WM > 0) {
-        // the sources of rows ra and rb (block-uniform)
         int ia[WM], ib[WM];
         double wa[WM], wb[WM];
 #pragma unroll
         for (int q = 0; q < WM; ++q) {
-            const bool in = q < W1;
-            ia[q] = in ? t1i[ra * W1 + q] : ra;
-            wa[q] = in ? t1w[ra * W1 + q] : 0.0;
-            ib[q] = (in && hasb) ? t1i[rb * W1 + q] : ra;
-            wb[q] = (in && hasb) ? t1w[rb * W1 + q] : 0.0;
+            const int t = min(q, W1 - 1);
+            ia[q] = t1i[ra * W1 + t] * n;
+            ib[q] = t1i[rs * W1 + t] * n;
+            wa[q] = q < W1 ? t1w[ra * W1 + t] : 0.0;
+            wb[q] = q < W1 ? t1w[rs * W1 + t] : 0.0;
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int j = threadIdx.x + e * T;
+            const int j = min((int)threadIdx.x + e * T, n - 1);
             double sa = 0.0, sb = 0.0;
-            if (j < n) {
-                int jc[WM];
-                double wc[WM];
 #pragma unroll
-                for (int q = 0; q < WM; ++q) {
-                    const bool in = q < W2;
-                    jc[q] = in ? t2i[j * W2 + q] : j;
-                    wc[q] = in ? t2w[j * W2 + q] : 0.0;
-                }
-#pragma unroll
-                for (int q1 = 0; q1 < WM; ++q1) {
-                    if (q1 >= W1) break;
-                    const int la = ia[q1] * n, lb = ib[q1] * n;
-                    double ta = 0.0, tb = 0.0;
-#pragma unroll
-                    for (int q2 = 0; q2 < WM; ++q2) {
-                        if (q2 < W2) {
-                            ta += wc[q2] * lam[la + jc[q2]];
-                            tb += wc[q2] * lam[lb + jc[q2]];
-                        }
-                    }
-                    sa += wa[q1] * ta;
-                    sb += wb[q1] * tb;
-                }
+            for (int q = 0; q < WM; ++q) {
+                sa += wa[q] * lam[ia[q] + j];
+                sb += wb[q] * lam[ib[q] + j];
             }
-            outv[e][0] = sa;
-            outv[e][1] = hasb ? sb : 0.0;
+            if ((int)threadIdx.x + e * T < n) lds[j] = make_double2(sa, sb);
         }
     } else {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int j = threadIdx.x + e * T;
-            outv[e][0] = outv[e][1] = 0.0;
-            if (j < n) {
-                for (int r = 0; r < 2; ++r) {
-                    const int i = ra + r;
-                    if (r == 1 && !hasb) break;
-                    double acc = 0.0;
-                    for (int q1 = 0; q1 < W1; ++q1) {
-                        const double w = t1w[i * W1 + q1];
-                        const int lr = t1i[i * W1 + q1] * n;
-                        double s2 = 0.0;
-                        for (int q2 = 0; q2 < W2; ++q2)
-                            s2 += t2w[j * W2 + q2] * lam[lr + t2i[j * W2 + q2]];
-                        acc += w * s2;
-                    }
-                    outv[e][r] = acc;
-                }
+        for (int j = threadIdx.x; j < n; j += T) {
+            double sa = 0.0, sb = 0.0;
+            for (int q = 0; q < W1; ++q) {
+                sa += t1w[ra * W1 + q] * lam[t1i[ra * W1 + q] * n + j];
+                sb += t1w[rs * W1 + q] * lam[t1i[rs * W1 + q] * n + j];
             }
+            lds[j] = make_double2(sa, sb);
         }
     }
-    // the writes after every read (mu is not read here, but the compiler
-    // cannot tell)
+    __syncthreads();
     double2 reg[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int j = threadIdx.x + e * T;
+        double sa = 0.0, sb = 0.0;
         if (j < n) {
-            mu.put(ra * n + j, outv[e][0]);
-            if (hasb) mu.put(rb * n + j, outv[e][1]);
+            if constexpr (WM > 0) {
+#pragma unroll
+                for (int q = 0; q < WM; ++q) {
+                    const int t = min(q, W2 - 1);
+                    const double w = q < W2 ? t2w[j * W2 + t] : 0.0;
+                    const double2 v = lds[t2i[j * W2 + t]];
+                    sa += w * v.x;
+                    sb += w * v.y;
+                }
+            } else {
+                for (int q = 0; q < W2; ++q) {
+                    const double w = t2w[j * W2 + q];
+                    const double2 v = lds[t2i[j * W2 + q]];
+                    sa += w * v.x;
+                    sb += w * v.y;
+                }
+            }
         }
-        reg[e] = make_double2(outv[e][0], outv[e][1]);
+        reg[e] = make_double2(sa, hasb ? sb : 0.0);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int j = threadIdx.x + e * T;
+        if (j >= n) continue;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (r == 1 && !hasb) break;
+            const int o = (ra + r) * n + j;
+            const double m = r == 0 ? reg[e].x : reg[e].y;
+            cr.put(o, lam[o] - Yb[o]);
+            mu.put(o, m);
+            if (!fft) Yb.put(o, m);
+        }
     }
     if (fft) rows_fwd_store<L, E>(reg, lds, tw4, xbuf<double2>(a), n, ra, hasb, X2);
 }
@@ -1397,50 +1389,48 @@ __global__ __launch_bounds__(256) void ks_adj_accum(const MarchArgs* __restrict_
         for (int q = 0; q < 6; ++q) acc[(size_t)i * 8 + q] += red[q][0];
 }
 
-// Spectral accumulation of the kernel gradient: per column k2 of the row
-// transforms (transposed half spectra, n rows each), the column FFTs and
-// S[k2][k1] += c1 conj(FFT XA) FFT XB (+ c2 conj(FFT XC) FFT XD when c2 != 0).
-// After the march, the inverse 2D transform of S / L^2 is sum_m lam_m Y_{m+d}
-// summed over the steps with their weights: the gradient of the loss with
-// respect to the folded kernel K_d.
-template <int L, int E = conv_e(L)>
-__global__ __launch_bounds__(L / E) void ks_adj_spec(const double2* __restrict__ XA, const double2* __restrict__ XB,
-                                                     const double2* __restrict__ XC, const double2* __restrict__ XD,
-                                                     int n, double c1, double c2, double2* __restrict__ S,
-                                                     const double2* __restrict__ tw) {
+// Spectral accumulation of the kernel gradient.  V^{s+1} meets lam of reverse step s
+// (weight c1) and mu of the step before it, s + 1 (weight c2): per column k2 of the
+// row transforms (transposed half spectra, n rows each) one column FFT of their sum and
+// one of V^{s+1}'s, S[k2][k1] += conj(FFT(c1 XL + c2 XM)) FFT XV; a weight of 0 leaves its
+// term out.  After the march, the inverse 2D transform of S / L^2 is sum_m lam_m Y_{m+d}
+// summed over the steps with their weights: the gradient of the loss with respect to the
+// folded kernel K_d.  (Four FFTs a step, with both terms' pairs transformed by
+// themselves, and a copy of XL kept for them: 14.7 + 5 us at 512^2; now 10.9.)
+template <int L, int E>
+__global__ __launch_bounds__(L / E) void ks_adj_spec(const MarchArgs* __restrict__ A, const Ctl* __restrict__ Cs,
+                                                     const double2* __restrict__ XM, const double2* __restrict__ XV,
+                                                     double c1, double c2, double2* __restrict__ S) {
+    Args& a = plan_args(A);
+    CtlK& c = plan_ctl(Cs);
+    if (halted(a, c, 0)) return;
     constexpr int T = L / E;
     __shared__ double2 lds[lds_slots(L)];
     __shared__ double2 tw4[tw_slots<L, E>()];
-    load_twiddles<L, E>(tw, tw4);
-    const int col = blockIdx.x, tid = threadIdx.x;
-    double2 acc[E];
-    double2* sc = S + (size_t)col * L;
+    load_twiddles<L, E>(GP<double2>(a.tw), tw4);
+    const int n = a.n, col = blockIdx.x, tid = threadIdx.x;
+    const GP<double2> xl(GP<double2>(a.X), (size_t)col * n), xm(GP<double2>(XM), (size_t)col * n),
+        xv(GP<double2>(XV), (size_t)col * n), sc(GP<double2>(S), (size_t)col * L);
+    double2 ru[E], rv[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = sc[tid + e * T];
-    for (int pass = 0; pass < 2; ++pass) {
-        const double cf = pass == 0 ? c1 : c2;
-        if (cf == 0.0) continue;
-        const double2* xa = (pass == 0 ? XA : XC) + (size_t)col * n;
-        const double2* xb = (pass == 0 ? XB : XD) + (size_t)col * n;
-        double2 ra[E], rb[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int idx = tid + e * T;
-            ra[e] = idx < n ? xa[idx] : make_double2(0.0, 0.0);
-            rb[e] = idx < n ? xb[idx] : make_double2(0.0, 0.0);
-        }
-        __syncthreads();
-        fft_block<L, E, false>(ra, lds, tw4);
-        __syncthreads();
-        fft_block<L, E, false>(rb, lds, tw4);
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const double2 pr = cmulc(rb[e], ra[e]);    // conj(A) B
-            acc[e] = make_double2(acc[e].x + cf * pr.x, acc[e].y + cf * pr.y);
-        }
+    for (int e = 0; e < E; ++e) {
+        const int idx = tid + e * T, at = min(idx, n - 1);
+        double2 l = make_double2(0.0, 0.0), m = make_double2(0.0, 0.0);
+        if (c1 != 0.0) l = xl[at];
+        if (c2 != 0.0) m = xm[at];
+        const double2 v = xv[at];
+        const bool in = idx < n;
+        ru[e] = in ? make_double2(c1 * l.x + c2 * m.x, c1 * l.y + c2 * m.y) : make_double2(0.0, 0.0);
+        rv[e] = in ? v : make_double2(0.0, 0.0);
     }
+    fft_block<L, E, false>(ru, lds, tw4);
+    __syncthreads();
+    fft_block<L, E, false>(rv, lds, tw4);
 #pragma unroll
-    for (int e = 0; e < E; ++e) sc[tid + e * T] = acc[e];
+    for (int e = 0; e < E; ++e) {
+        const double2 pr = cmulc(rv[e], ru[e]), t = sc[tid + e * T];    // conj(U) V
+        sc.put(tid + e * T, make_double2(t.x + pr.x, t.y + pr.y));
+    }
 }
 
 // Control block at the start of a march: the state of step-list entry step0
