@@ -26,7 +26,7 @@ SIZES = [64, 128, 256, 512, 768, 1024, 1536, 2048, 3072, 4096]
 PS_SIZES = SIZES + [640, 896, 1152, 1280, 1792, 2304, 2560, 3584, 4608, 5120, 6144, 7168, 8192, 12288, 16384, 24576]
 # (source, object, extra flags)
 UNITS = ([("lpide.hip", "lpide.o", []), ("host_plan.cpp", "host_plan.o", []), ("ps.hip", "ps.o", []),
-          ("ps_host.cpp", "ps_host.o", [])] +
+          ("ps_host.cpp", "ps_host.o", []), ("model_grad.hip", "model_grad.o", [])] +
          [("march_L.hip", "march_L%d.o" % L, ["-DLPIDE_L=%d" % L]) for L in SIZES] +
          [("ps_L.hip", "ps_L%d.o" % L, ["-DLPIDE_L=%d" % L]) for L in PS_SIZES])
 

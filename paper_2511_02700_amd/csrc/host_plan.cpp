@@ -42,41 +42,6 @@ double log_bessel_k(double nu, double x) {
     return -x + 0.5 * std::log(kPi / (2.0 * x)) + std::log(sum);
 }
 
-// Gauss-Legendre nodes/weights on [-1, 1] (Newton iteration on P_n).
-void gauss_legendre(int m, std::vector<double>& x, std::vector<double>& w) {
-    x.assign(m, 0.0);
-    w.assign(m, 0.0);
-    for (int i = 0; i < (m + 1) / 2; ++i) {
-        double z = std::cos(kPi * (i + 0.75) / (m + 0.5));
-        double pp = 0;
-        for (int it = 0; it < 100; ++it) {
-            double p0 = 1.0, p1 = z;
-            for (int k = 2; k <= m; ++k) {
-                double p2 = ((2.0 * k - 1) * z * p1 - (k - 1.0) * p0) / k;
-                p0 = p1;
-                p1 = p2;
-            }
-            if (m == 1) { p1 = z; p0 = 1.0; }
-            pp = m * (z * p1 - p0) / (z * z - 1.0);
-            double dz = p1 / pp;
-            z -= dz;
-            if (std::fabs(dz) < 1e-16) break;
-        }
-        // recompute derivative at the converged node
-        double p0 = 1.0, p1 = z;
-        for (int k = 2; k <= m; ++k) {
-            double p2 = ((2.0 * k - 1) * z * p1 - (k - 1.0) * p0) / k;
-            p0 = p1;
-            p1 = p2;
-        }
-        pp = m * (z * p1 - p0) / (z * z - 1.0);
-        x[i] = -z;
-        x[m - 1 - i] = z;
-        w[i] = w[m - 1 - i] = 2.0 / ((1.0 - z * z) * pp * pp);
-    }
-    if (m % 2 == 1) x[m / 2] = 0.0;
-}
-
 // Run fn(b, e) over [0, count) on up to 16 host threads, handing out blocks of
 // `grain` items from a shared counter (the items may differ much in cost).
 void parallel_for(int64_t count, const std::function<void(int64_t, int64_t)>& fn, int64_t grain = 1) {
@@ -113,6 +78,41 @@ void lagrange(int s, int P, double x, double* w) {
 }
 
 }  // namespace
+
+// Gauss-Legendre nodes/weights on [-1, 1] (Newton iteration on P_n).
+void gauss_legendre(int m, std::vector<double>& x, std::vector<double>& w) {
+    x.assign(m, 0.0);
+    w.assign(m, 0.0);
+    for (int i = 0; i < (m + 1) / 2; ++i) {
+        double z = std::cos(kPi * (i + 0.75) / (m + 0.5));
+        double pp = 0;
+        for (int it = 0; it < 100; ++it) {
+            double p0 = 1.0, p1 = z;
+            for (int k = 2; k <= m; ++k) {
+                double p2 = ((2.0 * k - 1) * z * p1 - (k - 1.0) * p0) / k;
+                p0 = p1;
+                p1 = p2;
+            }
+            if (m == 1) { p1 = z; p0 = 1.0; }
+            pp = m * (z * p1 - p0) / (z * z - 1.0);
+            double dz = p1 / pp;
+            z -= dz;
+            if (std::fabs(dz) < 1e-16) break;
+        }
+        // recompute derivative at the converged node
+        double p0 = 1.0, p1 = z;
+        for (int k = 2; k <= m; ++k) {
+            double p2 = ((2.0 * k - 1) * z * p1 - (k - 1.0) * p0) / k;
+            p0 = p1;
+            p1 = p2;
+        }
+        pp = m * (z * p1 - p0) / (z * z - 1.0);
+        x[i] = -z;
+        x[m - 1 - i] = z;
+        w[i] = w[m - 1 - i] = 2.0 / ((1.0 - z * z) * pp * pp);
+    }
+    if (m % 2 == 1) x[m / 2] = 0.0;
+}
 
 bool make_nts(const lpide_levy& lv, Nts& p, std::string& err) {
     p = Nts();
@@ -201,15 +201,12 @@ double z_star(const Nts& p, double cut) {
     return std::max(best, std::max(f1, f2));
 }
 
-// Artificial diffusion S = int over [-M1 h, M1 h]^2 of z z^T l(z) dz (Sec. 3.1):
-// polar coordinates per octant, Gauss-Legendre in the angle, tanh-sinh in the
-// radius (the radial integrand r^3 l(r u) ~ r^(1 - 2 alpha) at the origin).
-void small_jump_cov(const Nts& p, double half, double S[3]) {
-    std::vector<double> gx, gw;
-    gauss_legendre(48, gx, gw);
-    // tanh-sinh nodes on [0, 1]: x = 1/(1 + e^{-pi sinh t}), dx = pi cosh t e^{-pi sinh t}/(1+e^{-pi sinh t})^2
+// Tanh-sinh nodes and weights on [0, 1]: x = 1/(1 + e^{-pi sinh t}),
+// dx = pi cosh t e^{-pi sinh t}/(1+e^{-pi sinh t})^2.
+void radial_nodes(std::vector<double>& tx, std::vector<double>& tw) {
     const double hts = 1.0 / 32.0;
-    std::vector<double> tx, tw;
+    tx.clear();
+    tw.clear();
     for (int k = -160; k <= 160; ++k) {
         double t = k * hts, s = kPi * std::sinh(t);
         double e = std::exp(-s);
@@ -219,6 +216,16 @@ void small_jump_cov(const Nts& p, double half, double S[3]) {
         tx.push_back(x);
         tw.push_back(w);
     }
+}
+
+// Artificial diffusion S = int over [-M1 h, M1 h]^2 of z z^T l(z) dz (Sec. 3.1):
+// polar coordinates per octant, Gauss-Legendre in the angle, tanh-sinh in the
+// radius (the radial integrand r^3 l(r u) ~ r^(1 - 2 alpha) at the origin).
+void small_jump_cov(const Nts& p, double half, double S[3]) {
+    std::vector<double> gx, gw;
+    gauss_legendre(48, gx, gw);
+    std::vector<double> tx, tw;
+    radial_nodes(tx, tw);
     // one radial integral per (octant, angle node), in parallel; summed in order
     const int na = int(gx.size());
     std::vector<double> Iv(size_t(8) * na), U1(Iv.size()), U2(Iv.size());

@@ -50,6 +50,9 @@ double log_density(const Nts& p, double z1, double z2);
 
 // z_max^III before rounding: largest |z|_inf on {l = cut} (Sec. 4 settings).
 double z_star(const Nts& p, double cut);
+// Gauss-Legendre nodes and weights on [-1, 1], and the radial rule of small_jump_cov on [0, 1].
+void gauss_legendre(int m, std::vector<double>& x, std::vector<double>& w);
+void radial_nodes(std::vector<double>& tx, std::vector<double>& tw);
 
 // Weights omega_l of the z-cells l in [-N_z, N_z)^2 of width h (Sec. 3.1): zero on
 // R_I (|l + 1/2|_inf <= M1), the ||z||^2-weighted cell integral over ||z_l||^2 on

@@ -388,17 +388,6 @@ int harvest_times(Plan* p) {
 }
 
 template <typename Tp>
-int dalloc_into(std::vector<void*>& allocs, int64_t* bytes, Tp** out, size_t count) {
-    void* d = nullptr;
-    hipError_t e = hipMalloc(&d, std::max<size_t>(1, count) * sizeof(Tp));
-    if (e != hipSuccess) return fail(LPIDE_E_OOM, std::string("hipMalloc: ") + hipGetErrorString(e));
-    allocs.push_back(d);
-    if (bytes) *bytes += int64_t(count * sizeof(Tp));
-    *out = static_cast<Tp*>(d);
-    return LPIDE_OK;
-}
-
-template <typename Tp>
 int dalloc(Plan* p, Tp** out, size_t count) { return dalloc_into(p->allocs, &p->bytes, out, count); }
 
 template <typename Tp>
@@ -990,6 +979,7 @@ int adj_prepare(Plan* p, int C) {
     if (p->jumps) {
         if ((rc = dalloc_into(al, nullptr, &a->XM, (size_t)hc * n)) ||
             (rc = dalloc_into(al, nullptr, &a->XV, (size_t)hc * n)) ||
+            (rc = dalloc_into(al, nullptr, &a->nat, (size_t)4 * p->hp.N_z * p->hp.N_z)) ||
             (rc = dalloc_into(al, nullptr, &a->S, (size_t)hc * L)) ||
             (rc = dalloc_into(al, nullptr, &a->G, (size_t)L * L)))
             return rc;
@@ -1083,74 +1073,6 @@ int dispatch_adj_kernel_grad(Plan* p, const double* V, hipStream_t s) {
     LPIDE_SWITCH_L(p->L, CALL_KG)
 #undef CALL_KG
     HIP_TRY(hipGetLastError());
-    return LPIDE_OK;
-}
-
-// Host model quantities that the march depends on continuously, at the
-// subordination parameters x (sigma1, sigma2, corr, theta1, theta2, kappa,
-// alpha, r), structure frozen at the plan's N_z: a11, a12, a22, r_omega,
-// kappa_omega^(1,2), then omega.
-int model_quantities(const Plan* p, const double* x, std::vector<double>& out) {
-    lpide_levy lv;
-    int rc = lpide_levy_from_std(x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7], &lv);
-    if (rc) return rc;
-    lpide_grid g;
-    lpide_grid_default(&g, p->hp.n, 0.0, 1.0);
-    g.y_lo[0] = p->hp.y_lo[0];
-    g.y_lo[1] = p->hp.y_lo[1];
-    g.y_hi[0] = p->hp.y_lo[0] + p->hp.h * (p->hp.n - 1);
-    g.y_hi[1] = p->hp.y_lo[1] + p->hp.h * (p->hp.n - 1);
-    g.sl_order = p->hp.sl_order;
-    g.in_order = p->hp.in_order;
-    g.m1 = p->hp.M1;
-    g.ell_cut = p->grid.ell_cut;
-    g.zmax2_frac = p->grid.zmax2_frac;
-    g.gl_nodes = p->grid.gl_nodes;
-    g.nz_fixed = p->hp.N_z;
-    HostPlan hp;
-    std::string err;
-    if (!build_host_plan(g, lv, hp, err)) return fail(LPIDE_E_PARAM, "model quantities: " + err);
-    if (hp.M2 != p->hp.M2 || hp.L_need > p->L) return fail(LPIDE_E_PARAM, "structure changed under the perturbation");
-    out.assign(6 + hp.omega.size(), 0.0);
-    out[0] = hp.a[0];
-    out[1] = hp.a[1];
-    out[2] = hp.a[2];
-    out[3] = hp.r_omega;
-    out[4] = hp.kappa[0];
-    out[5] = hp.kappa[1];
-    std::copy(hp.omega.begin(), hp.omega.end(), out.begin() + 6);
-    return LPIDE_OK;
-}
-
-// Central differences of model_quantities with steps 1e-4 max(|x_q|, 0.1)
-// for the seven Levy parameters; r enters only as kappa_omega = r - ... and
-// r_omega = r + sum omega, so its column is exact (0, 0, 0, 1, 1, 1, 0...).
-int model_jacobian(Plan* p, const double* x) {
-    Adjoint* a = p->adj;
-    if (a->jac_valid && std::equal(x, x + 8, a->jac_std)) return LPIDE_OK;
-    std::vector<double> fp, fm;
-    size_t m = 0;
-    for (int q = 0; q < 7; ++q) {
-        double xp[8], xm[8];
-        std::copy(x, x + 8, xp);
-        std::copy(x, x + 8, xm);
-        const double hq = 1e-4 * std::max(std::fabs(x[q]), 0.1);
-        xp[q] += hq;
-        xm[q] -= hq;
-        int rc = model_quantities(p, xp, fp);
-        if (!rc) rc = model_quantities(p, xm, fm);
-        if (rc) return rc;
-        if (q == 0) {
-            m = fp.size();
-            a->jac.assign(8 * m, 0.0);
-        }
-        for (size_t i = 0; i < m; ++i) a->jac[q * m + i] = (fp[i] - fm[i]) / (2.0 * hq);
-    }
-    a->jac[7 * m + 3] = 1.0;
-    a->jac[7 * m + 4] = 1.0;
-    a->jac[7 * m + 5] = 1.0;
-    std::copy(x, x + 8, a->jac_std);
-    a->jac_valid = true;
     return LPIDE_OK;
 }
 
@@ -1257,39 +1179,9 @@ int adjoint(Plan* p, const double* v_bar, int C, std::vector<double>& native, lp
     }
     if (p->jumps) {
         if ((rc = dispatch_adj_kernel_grad(p, a->seg, s))) return rc;    // seg[0]: V^0, of the segment reversed last
-        const int L = p->L;
-        std::vector<double> G((size_t)L * L);
-        HIP_TRY(hipMemcpyAsync(G.data(), a->G, sizeof(double) * G.size(), hipMemcpyDeviceToHost, s));
+        if ((rc = native_omega(p, a->G, a->nat, s))) return rc;
+        HIP_TRY(hipMemcpyAsync(native.data() + 6, a->nat, sizeof(double) * (size_t)W2 * W2, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
-        const double inv = 1.0 / (double(L) * double(L));
-        auto gk = [&](int d1, int d2) {
-            return G[(size_t)(((d1 % L) + L) % L) * L + (((d2 % L) + L) % L)] * inv;
-        };
-        // dJ/d omega_l = sum_j s_j1 s_j2 dJ/dK_{l + jlo + j}  (K = omega folded with the half-cell taps)
-        const int Pin = p->hp.in_order, jlo = -(Pin - 1) / 2;
-        double sw[4];
-        for (int i = 0; i <= Pin; ++i) {
-            double v = 1.0;
-            for (int j = 0; j <= Pin; ++j)
-                if (j != i) v *= (0.5 - (jlo + j)) / double(i - j);
-            sw[i] = v;
-        }
-        auto rows = [&](int r0, int r1) {
-            for (int l1 = r0 - Nz; l1 < r1 - Nz; ++l1)
-                for (int l2 = -Nz; l2 < Nz; ++l2) {
-                    double t = 0.0;
-                    for (int j1 = 0; j1 <= Pin; ++j1)
-                        for (int j2 = 0; j2 <= Pin; ++j2) t += sw[j1] * sw[j2] * gk(l1 + jlo + j1, l2 + jlo + j2);
-                    native[6 + (size_t)(l1 + Nz) * W2 + (l2 + Nz)] = t;
-                }
-        };
-        const int nth = int(std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
-        std::vector<std::thread> th;
-        for (int t = 0; t < nth; ++t) {
-            const int r0 = int((int64_t)W2 * t / nth), r1 = int((int64_t)W2 * (t + 1) / nth);
-            if (r0 < r1) th.emplace_back(rows, r0, r1);
-        }
-        for (auto& x : th) x.join();
     }
     if (info) {
         info->adj_iters = iters;
@@ -1721,14 +1613,7 @@ int lpide_adjoint(void* plan, const double* v_bar, int32_t checkpoint_every, con
             !close(lv.rho[1], q.rho[1]) || !close(lv.rho[2], q.rho[2]) || !close(lv.r, p->hp.r))
             return fail(LPIDE_E_PARAM, "std_params do not map to the plan's model");
         const auto t0 = std::chrono::steady_clock::now();
-        if ((rc = model_jacobian(p, std_params))) return rc;
-        const size_t m = nat.size();
-        for (int k = 0; k < 8; ++k) {
-            double t = 0.0;
-            const double* jr = p->adj->jac.data() + (size_t)k * m;
-            for (size_t i = 0; i < m; ++i) t += nat[i] * jr[i];
-            grad[k] = t;
-        }
+        if ((rc = model_gradient(p, std_params, nat.data(), grad))) return rc;
         if (info)
             info->jacobian_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     }

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <type_traits>
@@ -29,6 +30,18 @@ int fail(int code, const std::string& msg);
             return ::lpide::detail::fail(e_ == hipErrorOutOfMemory ? LPIDE_E_OOM : LPIDE_E_HIP, \
                                          std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
+
+// Device memory of `count` elements, kept in `allocs` and counted in `bytes` (if not null).
+template <typename Tp>
+int dalloc_into(std::vector<void*>& allocs, int64_t* bytes, Tp** out, size_t count) {
+    void* d = nullptr;
+    hipError_t e = hipMalloc(&d, std::max<size_t>(1, count) * sizeof(Tp));
+    if (e != hipSuccess) return fail(LPIDE_E_OOM, std::string("hipMalloc: ") + hipGetErrorString(e));
+    allocs.push_back(d);
+    if (bytes) *bytes += int64_t(count * sizeof(Tp));
+    *out = static_cast<Tp*>(d);
+    return LPIDE_OK;
+}
 
 struct Plan;
 
@@ -201,11 +214,9 @@ struct Adjoint {
     int* counts = nullptr;
     double* incs = nullptr;
     std::vector<int> counts_h;
-    // host Jacobian of (a11, a12, a22, r_omega, kappa1, kappa2, omega) with respect to the
-    // 8 subordination parameters, cached for the std point it was taken at
-    double jac_std[8] = {};
-    bool jac_valid = false;
-    std::vector<double> jac;        // 8 x (6 + (2 N_z)^2)
+    double* nat = nullptr;          // dJ/d omega of the last call, (2 N_z)^2
+    double* mg = nullptr;           // tables and partial sums of model_gradient
+    size_t mg_n = 0;
 };
 
 // Radix schedules instantiated per transform size: the E for which the
@@ -238,6 +249,13 @@ double bits_d(unsigned long long b);
 
 // Stopping-rule value after iteration k from a host copy of a control block.
 double err_of(const Ctl& c, int k);
+
+// model_grad.hip: dJ/d omega from the inverse transform G of the spectral accumulator,
+// and the gradient with respect to the eight subordination parameters x from the native
+// gradient `nat` (dJ/d(a11, a12, a22, r_omega, kappa1, kappa2) on the host, dJ/d omega in
+// adj->nat).
+int native_omega(Plan* p, const double* G, double* out, hipStream_t s);
+int model_gradient(Plan* p, const double* x, const double* nat, double* grad);
 
 // Work that depends on the transform size L, instantiated in one translation
 // unit per size (march_L.hip compiled with -DLPIDE_L=L).
