@@ -604,6 +604,8 @@ void destroy_group(Group* g) {
     for (auto& x : g->graphs) (void)hipGraphExecDestroy(x.exec);
     for (void* a : g->allocs) (void)hipFree(a);
     if (g->ctl_h) (void)hipHostFree(g->ctl_h);
+    for (hipEvent_t e : g->window)
+        if (e) (void)hipEventDestroy(e);
     delete g;
 }
 
@@ -654,11 +656,17 @@ int make_group(const std::vector<Plan*>& plans, hipStream_t stream, Group** out)
         destroy_group(g);
         return rc;
     }
-    if (hipHostMalloc((void**)&g->ctl_h, sizeof(Ctl) * np, hipHostMallocDefault) != hipSuccess) {
+    const int nctl = np + (np == 1 ? 2 : 0);
+    if (hipHostMalloc((void**)&g->ctl_h, sizeof(Ctl) * nctl, hipHostMallocDefault) != hipSuccess) {
         destroy_group(g);
         return fail(LPIDE_E_OOM, "hipHostMalloc failed");
     }
-    std::memset(g->ctl_h, 0, sizeof(Ctl) * np);
+    std::memset(g->ctl_h, 0, sizeof(Ctl) * nctl);
+    for (int q = 0; q < 2 && np == 1; ++q)
+        if (hipEventCreateWithFlags(&g->window[q], hipEventDisableTiming) != hipSuccess) {
+            destroy_group(g);
+            return fail(LPIDE_E_HIP, "hipEventCreateWithFlags failed");
+        }
     g->counts_h.assign((size_t)np * g->maxsteps, 0);
     g->incs_h.assign((size_t)np * g->maxsteps, 0.0);
     g->args_h.resize(np);
@@ -827,19 +835,11 @@ int march_begin(Group* g, MarchState& st, const int* nsteps, int step0, const do
     return LPIDE_OK;
 }
 
-int march_enqueue(Group* g, MarchState& st) {
-    int remaining = 0;
-    for (int i = 0; i < g->lc.np; ++i) remaining = std::max(remaining, st.nsteps[i] - st.at[i]);
-    if (remaining == 0) {
-        st.done = true;
-        return LPIDE_OK;
-    }
-    if (g->lc.timer) g->lc.timer->ev_mark = g->lc.timer->ev_recs.size();
-    int ns = std::min(g->slots, remaining);
-    // lean slots when every plan's steps in them are steady.  A window whose
-    // first steps are not steady (the start of a march, or of a recompute
-    // segment) ends where the steady run of every plan begins, so that the
-    // rest goes out lean in the next windows.
+// Slots of the next window, of at most ns: sets the launch to lean slots when every
+// plan's steps in them are steady.  A window whose first steps are not steady (the start
+// of a march, or of a recompute segment) ends where the steady run of every plan begins,
+// so that the rest goes out lean in the next windows.
+int window_slots(Group* g, const MarchState& st, int ns) {
     auto steady_from = [&](int k) {          // every plan steady on [at + k, at + ns)
         for (int i = 0; i < g->lc.np; ++i) {
             const Plan* p = g->plans[i];
@@ -857,6 +857,19 @@ int march_enqueue(Group* g, MarchState& st) {
             }
     }
     g->lc.lean = lean;
+    return ns;
+}
+
+int march_enqueue(Group* g, MarchState& st) {
+    int remaining = 0;
+    for (int i = 0; i < g->lc.np; ++i) remaining = std::max(remaining, st.nsteps[i] - st.at[i]);
+    if (remaining == 0) {
+        st.done = true;
+        return LPIDE_OK;
+    }
+    if (g->lc.timer) g->lc.timer->ev_mark = g->lc.timer->ev_recs.size();
+    int ns = std::min(g->slots, remaining);
+    ns = window_slots(g, st, ns);
     return enqueue_slots(g, st.at[0], ns, st.kpred);
 }
 
@@ -919,16 +932,70 @@ int march_end(Group* g, MarchState& st, double* const* v_out) {
     return LPIDE_OK;
 }
 
+// The steps of one plan alone, in windows of WINDOW slots of which the next is enqueued
+// before the last one's outcome is waited for, so that the device has work during the
+// host's round trip and the prediction follows the counts (they fall along a march: 7 to
+// 5 at 64^2, 7 to 4 at 512^2, 11 to 6 in the mixed form at 700^2, where a step above the
+// prediction also turns the rest of the slots behind it into no-ops).  An iteration past
+// convergence costs 8 to 10 us, a no-op slot six to nine of them.  Against windows of 32
+// slots with a wait after each: WINDOW_FIGURES.
+constexpr int WINDOW = 4;
+int march_windows(Group* g, MarchState& st) {
+    struct Win { int ns, k; size_t mark; };
+    Win win[2] = {};
+    Plan* tp = g->lc.timer;
+    hipStream_t s = g->lc.stream;
+    int head = 0, inflight = 0;                 // win[head] is the older one
+    const int end = st.nsteps[0];
+    int rc = LPIDE_OK;
+    while (st.at[0] < end || inflight > 0) {    // at: steps enqueued, as if every window met its tolerance
+        while (inflight < 2 && st.at[0] < end) {
+            const int q = (head + inflight) & 1;
+            const int ns = window_slots(g, st, std::min(WINDOW, end - st.at[0]));
+            win[q] = {ns, st.kpred, tp ? tp->ev_recs.size() : 0};
+            if ((rc = enqueue_slots(g, st.at[0], ns, st.kpred))) return rc;
+            HIP_TRY(hipMemcpyAsync(g->ctl_h + 1 + q, g->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+            HIP_TRY(hipEventRecord(g->window[q], s));
+            st.at[0] += ns;
+            ++inflight;
+        }
+        HIP_TRY(hipEventSynchronize(g->window[head]));
+        const Ctl* c = g->ctl_h + 1 + head;
+        const Win w = win[head];
+        head ^= 1;
+        --inflight;
+        int k = 0;
+        if (c->fail) {
+            // the slots behind the failed step, the next window's included, run as no-ops;
+            // its steps are enqueued again
+            if (tp)
+                for (size_t r = w.mark; r < tp->ev_recs.size(); ++r)
+                    if (tp->ev_recs[r].step > c->fail_step) tp->ev_recs[r].cls = -1;
+            g->ctl_h[0] = *c;
+            if ((rc = complete_step(g, 0, w.k, &k))) return rc;
+            c = g->ctl_h;
+            st.at[0] = c->step;
+            inflight = 0;
+        }
+        const int done = std::min(4, c->step - st.step0);
+        for (int q = 1; q <= done; ++q) k = std::max(k, c->recent[(c->step - q) & 3]);
+        if (k > 0) st.kpred = std::min(st.maxit, k);
+    }
+    return read_back(g);
+}
+
 // kpred0 > 0: the first prediction of iterations per step (else 8).
 int march_group(Group* g, const int* nsteps, int step0, const double* const* v_in, double* const* v_out,
                 int kpred0 = 0) {
     MarchState st;
     int rc = march_begin(g, st, nsteps, step0, v_in);
     if (!rc && kpred0 > 0) st.kpred = std::min(kpred0, st.maxit);
-    while (!rc && !st.done) {
-        rc = march_enqueue(g, st);
-        if (!rc) rc = march_check(g, st);
-    }
+    if (!rc && g->lc.np == 1 && !g->use_graph) rc = march_windows(g, st);
+    else
+        while (!rc && !st.done) {
+            rc = march_enqueue(g, st);
+            if (!rc) rc = march_check(g, st);
+        }
     if (!rc) rc = march_end(g, st, v_out);
     if (!rc) HIP_TRY(hipStreamSynchronize(g->lc.stream));
     return rc;

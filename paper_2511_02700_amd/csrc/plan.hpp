@@ -82,7 +82,8 @@ struct Group {
     std::vector<MarchArgs> args_h;
     MarchArgs* A = nullptr;
     Ctl* ctl = nullptr;
-    Ctl* ctl_h = nullptr;
+    Ctl* ctl_h = nullptr;           // np, and behind them one per window in flight (one plan alone)
+    hipEvent_t window[2] = {};      // behind the copy of the control block after a window (one plan alone)
     int* counts = nullptr;          // np x maxsteps
     double* incs = nullptr;
     std::vector<int> counts_h;

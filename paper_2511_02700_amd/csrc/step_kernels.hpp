@@ -95,6 +95,7 @@ struct Ctl {
     int bvalid;                       // bit b: bpool[b] holds B applied to pool[b] (this march)
     int w;                            // SL buffer of this step (the step before wrote the other one)
     int src[4];                       // pool indices of the start value's sources
+    int recent[4];                    // iteration counts of the last four steps, at step mod 4
     // stopping-rule value after iteration k: the maximum over x of err[x][k]
     // (bit patterns of non-negative doubles).  The row blocks of the line-solve
     // kernel reduce into the partial of their XCD, so the atomics of one launch
@@ -1046,6 +1047,7 @@ static __global__ void ks_step_end(const MarchArgs* __restrict__ A, Ctl* __restr
                 ok = 1;
                 a.counts[s] = kk;
                 a.incs[s] = ek[kk];
+                c->recent[s & 3] = kk;
                 const bool inner_sub = a.damping && s < a.n_sub - 1;
                 if (inner_sub) {
                     c->cur = c->y;                        // next damped sub-step starts here
@@ -1450,7 +1452,7 @@ static __global__ void ks_init(const MarchArgs* __restrict__ A, Ctl* __restrict_
         c->hc = 1;
         c->nsrc = 1;
         c->bvalid = 0;
-        for (int q = 0; q < 4; ++q) { c->hist[q] = 0; c->src[q] = 0; }
+        for (int q = 0; q < 4; ++q) { c->hist[q] = 0; c->src[q] = 0; c->recent[q] = 0; }
         c->now.coef[0] = 1.0;
         if (a.step0 < a.nsteps) {
             const int id = a.step_set[a.step0];
