@@ -49,7 +49,8 @@ void launch_rows_fwd(Plan* p, const double* Y, hipStream_t s) {
 template <int CPB, int MAXT, typename Go>
 void with_line_cols_mm(const Launch& c, Go&& go) {
     const int ch = (c.xcols * c.cpb + c.P_cols - 1) / c.P_cols;
-    if (ch <= 8) go(ks_line_cols<CPB, MAXT, 8>);
+    if (ch <= 4) go(ks_line_cols<CPB, MAXT, 4>);
+    else if (ch <= 8) go(ks_line_cols<CPB, MAXT, 8>);
     else if (ch <= 16) go(ks_line_cols<CPB, MAXT, 16>);
     else go(ks_line_cols<CPB, MAXT, LINE_MM>);
 }

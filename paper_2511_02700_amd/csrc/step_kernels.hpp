@@ -396,20 +396,35 @@ __global__ __launch_bounds__(L / E) void ks_rows_fwd(const MarchArgs* __restrict
 // pair reads the 32 contiguous bytes of one frequency once; the pair swaps its
 // values, the even lane forms z[k], the odd one z[L-k], and both go through LDS
 // to the canonical layout.
-template <int L, int E, typename C>
-__device__ __forceinline__ void rows_inv_gather(C (&reg)[E], C* lds, GP<C> X, int n, int ra, bool hasb) {
-    constexpr int T = L / E, NI = (L + 2 + T - 1) / T;
+constexpr int rows_inv_items(int L, int E) { return (L + 2 + L / E - 1) / (L / E); }
+
+// The gather's reads: item it of a thread.
+template <int L, int E, typename C, int NI>
+__device__ __forceinline__ void rows_inv_read(C (&v)[NI], GP<C> X, int n, int ra, bool hasb) {
+    constexpr int T = L / E;
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const int idx = threadIdx.x + it * T;
+        const int kk = idx >> 1, r = idx & 1;
+        const bool in = kk <= L / 2;
+        v[it] = (in && (r == 0 || hasb)) ? X[kk * n + ra + r] : CplxOps<C>::make(0, 0);
+    }
+}
+
+// The exchange of what rows_inv_read read.
+template <int L, int E, typename C, int NI>
+__device__ __forceinline__ void rows_inv_exchange(C (&reg)[E], C* lds, const C (&v)[NI]) {
+    constexpr int T = L / E;
     const int tid = threadIdx.x;
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
         const int idx = tid + it * T;
         const int kk = idx >> 1, r = idx & 1;
         const bool in = kk <= L / 2;
-        const C v = (in && (r == 0 || hasb)) ? X[kk * n + ra + r] : CplxOps<C>::make(0, 0);
         // every lane of the wave takes part in the swap (pairs never straddle the range end)
-        const C u = CplxOps<C>::make(__shfl_xor(v.x, 1), __shfl_xor(v.y, 1));
+        const C u = CplxOps<C>::make(__shfl_xor(v[it].x, 1), __shfl_xor(v[it].y, 1));
         const bool real_bin = kk == 0 || kk == L / 2;
-        const C ta = r == 0 ? v : u, tb = r == 0 ? u : v;
+        const C ta = r == 0 ? v[it] : u, tb = r == 0 ? u : v[it];
         const C ha = CplxOps<C>::make(ta.x, real_bin ? 0 : ta.y);
         const C hb = CplxOps<C>::make(tb.x, real_bin ? 0 : tb.y);
         if (in && r == 0) lds[lds_slot(kk)] = CplxOps<C>::make(ha.x - hb.y, ha.y + hb.x);
@@ -419,6 +434,13 @@ __device__ __forceinline__ void rows_inv_gather(C (&reg)[E], C* lds, GP<C> X, in
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < E; ++e) reg[e] = lds[lds_slot(tid + e * T)];
+}
+
+template <int L, int E, typename C>
+__device__ __forceinline__ void rows_inv_gather(C (&reg)[E], C* lds, GP<C> X, int n, int ra, bool hasb) {
+    C v[rows_inv_items(L, E)];
+    rows_inv_read<L, E>(v, X, n, ra, hasb);
+    rows_inv_exchange<L, E>(reg, lds, v);
 }
 
 // Row inverse FFT of the pairs (2p, 2p+1) with a fused epilogue.
@@ -464,6 +486,12 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
         const double cf = MODE == 4 ? c.now.cex : c.now.cth, r_omega = a.r_omega;
         const StencilArgs st = stencil(a);
         const int o0 = max(ra - 1, 0) * n, o1 = ra * n, o2 = min(rb, n - 1) * n, o3 = min(rb + 1, n - 1) * n;
+        // up to 1024 the gather's reads go first and are in flight with the stencil's (64^2
+        // 6.8 -> 6.0, 128^2 6.3 -> 4.9, 512^2 8.5 -> 7.6); above, their registers would cost
+        // blocks in flight
+        constexpr bool AHEAD = L <= 1024;
+        C xv[rows_inv_items(L, E)];
+        if constexpr (AHEAD) rows_inv_read<L, E>(xv, xbuf<C>(a), n, ra, hasb);
         double g[E][2];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -486,7 +514,8 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
         // to 1024 all elements' reads are in flight together, above one element's.
 #pragma unroll
         for (int e = 0; e < E; ++e) asm volatile("" : "+v"(g[e][0]), "+v"(g[e][1]));
-        rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
+        if constexpr (AHEAD) rows_inv_exchange<L, E>(reg, lds, xv);
+        else rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
         fft_block<L, E, true>(reg, lds, tw4);
         const bool keepB = MODE == 1 && c.now.B != nullptr;       // B Y of the iterate, for the start of later steps
 #pragma unroll
@@ -955,23 +984,30 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
             for (int q = 0; q < MM; ++q) x[q] = q < cnt ? Rr[o + q] : 0.0;
         }
     }
-    chunk_solve<MM>(x, s, cnt, r, ch, PR, 1, c.now.fl2, c.now.bu2, c.now.bc2, lds);
+    // the iterate, every element read before any write of the update (reads
+    // after those writes would wait element by element: the compiler cannot
+    // separate them): at E = 4 with the residual, its latency behind the line solve;
+    // above, and at L = 3072, after the solve, so that it is not held in registers across
+    // it (at E = 4 of L = 3072 82 registers leave one block per CU: 45.3 -> 61.7 us).
+    constexpr bool EARLY_Y = E <= 4 && L < 3072;
+    double yoa[E], yob[E];
+    auto read_iterate = [&] {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = tid + e * T;
+            yoa[e] = j < n ? Y[ra * n + j] : 0.0;
+            yob[e] = (j < n && hasb) ? Y[rb * n + j] : 0.0;
+        }
+    };
+    if constexpr (EARLY_Y) read_iterate();
+    chunk_solve<MM, (MM <= 4)>(x, s, cnt, r, ch, PR, 1, c.now.fl2, c.now.bu2, c.now.bc2, lds);
 #pragma unroll
     for (int q = 0; q < MM; ++q)
         if (q < cnt) rows[r * stride + s + q + ch] = x[q];
     __syncthreads();
-    // the iterate, every element read before any write of the update (reads
-    // after those writes would wait element by element: the compiler cannot
-    // separate them).  Read here rather than at the start, it is not held in
-    // registers across the line solve: 162 registers instead of 221 at
-    // L = 3072, E = 16 (55.7 -> 53.1 us alone).
-    double yoa[E], yob[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int j = tid + e * T;
-        yoa[e] = j < n ? Y[ra * n + j] : 0.0;
-        yob[e] = (j < n && hasb) ? Y[rb * n + j] : 0.0;
-    }
+    if constexpr (!EARLY_Y) read_iterate();
+    const unsigned inv_m = 0xFFFFFFFFu / (unsigned)m + 1;      // j / m = mulhi(j, inv_m) for j < 2^16, m > 1
+    auto chunk_of = [&](int j) { return m > 1 ? (int)__umulhi((unsigned)j, inv_m) : j; };
     double emax = 0.0;
     C reg[E];
 #pragma unroll
@@ -979,13 +1015,14 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
         const int j = tid + e * T;
         double ya = 0.0, yb = 0.0, da = 0.0, db = 0.0;
         if (j < n) {
-            da = rows[j + j / m];
+            const int at = j + chunk_of(j);
+            da = rows[at];
             ya = yoa[e] + da;
             Y.put(ra * n + j, ya);
             double ev = fabs(da) / fmax(1.0, fabs(ya));
             emax = (ev > emax || ev != ev) ? ev : emax;
             if (hasb) {
-                db = rows[stride + j + j / m];
+                db = rows[stride + at];
                 yb = yob[e] + db;
                 Y.put(rb * n + j, yb);
                 ev = fabs(db) / fmax(1.0, fabs(yb));
