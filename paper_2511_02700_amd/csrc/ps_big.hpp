@@ -164,7 +164,7 @@ __device__ __forceinline__ void big_windows(const double2 (&acc)[SO][M / BIG_T],
         __syncthreads();
         for (int q = tid; q < o.n; q += T) {
             const int sq = o.tout_s[q];
-            if (sq >= wlo && sq <= whi - 4) put(q, ps_interp(lds, o.tout_s, o.tout_w, q, wlo));
+            if (sq >= wlo && sq <= whi - 4) put(q, ps_interp(lds, ps_tap(o.tout_s, o.tout_w, q), wlo));
         }
         if (whi >= o.n_out) break;
         wlo = whi - 3;
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(BIG_T) void ps_big_cols(const double2* __restrict__
                 const int j = tid + e * T + s * M;
                 if (j < n_in) {
                     double2 z;
-                    if constexpr (MODE == 0) z = ps_interp(xc, o.tin_s, o.tin_w, j, 0);
+                    if constexpr (MODE == 0) z = ps_interp(xc, ps_tap(o.tin_s, o.tin_w, j), 0);
                     else z = xc[j];
                     const double2 v = cmul(z, w);
                     reg[e].x += v.x;

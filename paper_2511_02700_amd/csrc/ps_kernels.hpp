@@ -90,8 +90,10 @@ __device__ __forceinline__ double ps_bits(unsigned long long b) { return __longl
 
 __device__ __forceinline__ bool ps_halted(const PsCtl* c, int k, double tol) {
     if (c == nullptr) return false;
-    if (c->fail) return true;
-    return k > 1 && ps_bits(c->err[k - 1]) < tol;
+    KRef<PsCtl> r = kref(c);                       // one set of reads: neither waits for the other's test
+    const int fail = r.fail;
+    const unsigned long long e = r.err[k > 1 ? k - 1 : 0];
+    return (fail != 0) | (k > 1 && ps_bits(e) < tol);
 }
 
 // D Y at (i, j): a11 x_i^2 d2_i / 2 + a22 x_j^2 d2_j / 2 + a12 (x_i d1_i)(x_j d1_j).
@@ -119,15 +121,26 @@ __device__ __forceinline__ double ps_DY(const double* __restrict__ Y, const PsOp
     return d;
 }
 
-// sum_t w_t v[s + t] for row q of an interpolation table (start s, four weights).
-__device__ __forceinline__ double2 ps_interp(const double2* v, const int* __restrict__ st, const double* __restrict__ wt,
-                                             int q, int off) {
+// Row q of an interpolation table (start, four weights), read ahead of the values that
+// it is applied to: up to L = 4096 a pass's table reads are in flight with its data
+// instead of behind the barrier that publishes them.  At 8192 the registers that hold
+// them cost more (B v of NIG1 at N_x = 800 2.75 ms against 2.88).
+constexpr bool ps_ahead(int L) { return L <= 4096; }
+struct PsTap {
+    int s;
+    double2 a, b;
+};
+__device__ __forceinline__ PsTap ps_tap(const int* __restrict__ st, const double* __restrict__ wt, int q) {
     const double2* w2 = reinterpret_cast<const double2*>(wt) + 2 * (size_t)q;
-    const double2* r = v + (st[q] - off);
-    const double2 a = w2[0], b = w2[1];
+    return {st[q], w2[0], w2[1]};
+}
+
+// sum_t w_t v[s - off + t].
+__device__ __forceinline__ double2 ps_interp(const double2* v, const PsTap& p, int off) {
+    const double2* r = v + (p.s - off);
     const double2 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
-    return make_double2(a.x * r0.x + a.y * r1.x + b.x * r2.x + b.y * r3.x,
-                        a.x * r0.y + a.y * r1.y + b.x * r2.y + b.y * r3.y);
+    return make_double2(p.a.x * r0.x + p.a.y * r1.x + p.b.x * r2.x + p.b.y * r3.x,
+                        p.a.x * r0.y + p.a.y * r1.y + p.b.x * r2.y + p.b.y * r3.y);
 }
 
 // Grid rows (2p, 2p+1), tile blockIdx.y: the axis-2 interpolation from the rows
@@ -147,15 +160,21 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_rows_fwd(const double* __restr
     const int ra = 2 * p, rb = 2 * p + 1;
     const bool hasb = rb < n;
     const int tid = threadIdx.x;
+    const int i0 = blockIdx.y * o.vs;
+    PsTap in[KE];
+    if constexpr (ps_ahead(L)) {
+#pragma unroll
+        for (int e = 0; e < KE; ++e) in[e] = ps_tap(o.tin_s, o.tin_w, min(i0 + tid + e * T, o.n_nz - 1));
+    }
     for (int j = tid; j < n; j += T)
         lds[j] = make_double2(V[(size_t)ra * n + j], hasb ? V[(size_t)rb * n + j] : 0.0);
     __syncthreads();
-    const int i0 = blockIdx.y * o.vs;
     double2 reg[KE];
 #pragma unroll
     for (int e = 0; e < KE; ++e) {
         const int i = i0 + tid + e * T;
-        reg[e] = i < o.n_nz ? ps_interp(lds, o.tin_s, o.tin_w, i, 0) : make_double2(0.0, 0.0);
+        if constexpr (!ps_ahead(L)) in[e] = ps_tap(o.tin_s, o.tin_w, min(i, o.n_nz - 1));
+        reg[e] = i < o.n_nz ? ps_interp(lds, in[e], 0) : make_double2(0.0, 0.0);
     }
     fft_block<L, KE, false>(reg, lds, tw4);
     __syncthreads();
@@ -200,15 +219,21 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_cols(const double2* __restrict
     const size_t tile = (size_t)b2 * (L / 2 + 1);
     const double2* xc = X + (tile + col) * o.ldx;
     const double2* xn = X + (tile + L / 2) * o.ldx;
+    const int i0 = b1 * o.vs;
+    PsTap in[KE];
+    if constexpr (ps_ahead(L)) {
+#pragma unroll
+        for (int e = 0; e < KE; ++e) in[e] = ps_tap(o.tin_s, o.tin_w, min(i0 + tid + e * T, o.n_nz - 1));
+    }
     for (int j = tid; j < n; j += T) lds[j] = pair ? make_double2(xc[j].x, xn[j].x) : xc[j];
     __syncthreads();
-    const int i0 = b1 * o.vs;
     const double2* sc = spec + (size_t)col * L;
     double2 reg[KE];
 #pragma unroll
     for (int e = 0; e < KE; ++e) {
         const int i = i0 + tid + e * T;
-        reg[e] = i < o.n_nz ? ps_interp(lds, o.tin_s, o.tin_w, i, 0) : make_double2(0.0, 0.0);
+        if constexpr (!ps_ahead(L)) in[e] = ps_tap(o.tin_s, o.tin_w, min(i, o.n_nz - 1));
+        reg[e] = i < o.n_nz ? ps_interp(lds, in[e], 0) : make_double2(0.0, 0.0);
     }
     fft_block<L, KE, false>(reg, lds, tw4);
     if (pair) {
@@ -218,6 +243,8 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_cols(const double2* __restrict
         for (int e = 0; e < KE; ++e) reg[e] = cmul(reg[e], sc[tid + e * T]);
     }
     fft_block<L, KE, true>(reg, lds, tw4);
+    const int m0 = o.mlo[b1], m1 = o.mlo[b1 + 1];
+    PsTap out = ps_tap(o.tout_s, o.tout_w, min(m0 + tid, n - 1));
     __syncthreads();
     const int kept = min(o.v, o.n_out - i0);
 #pragma unroll
@@ -228,9 +255,9 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_cols(const double2* __restrict
     __syncthreads();
     double2* oc = Xo + (tile + col) * o.ldx;
     double2* on = Xo + (tile + L / 2) * o.ldx;
-    const int m1 = o.mlo[b1 + 1];
-    for (int q = o.mlo[b1] + tid; q < m1; q += T) {
-        const double2 y = ps_interp(lds, o.tout_s, o.tout_w, q, i0);
+    for (int q = m0 + tid; q < m1; q += T) {
+        const double2 y = ps_interp(lds, out, i0);
+        if (q + T < m1) out = ps_tap(o.tout_s, o.tout_w, q + T);
         if (pair) {
             oc[q] = make_double2(y.x, 0.0);
             on[q] = make_double2(y.y, 0.0);
@@ -284,6 +311,8 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_rows_inv(const double2* __rest
 #pragma unroll
     for (int e = 0; e < KE; ++e) reg[e] = lds[lds_slot(tid + e * T)];
     fft_block<L, KE, true>(reg, lds, tw4);
+    const int m0 = o.mlo[blockIdx.y], m1 = o.mlo[blockIdx.y + 1];
+    PsTap to = ps_tap(o.tout_s, o.tout_w, min(m0 + tid, n - 1));
     __syncthreads();
     const int i0 = blockIdx.y * o.vs, kept = min(o.v, o.n_out - i0);
 #pragma unroll
@@ -292,9 +321,9 @@ __global__ __launch_bounds__(L / ps_e(L)) void ps_rows_inv(const double2* __rest
         if (idx < kept) lds[idx] = reg[e];
     }
     __syncthreads();
-    const int m1 = o.mlo[blockIdx.y + 1];
-    for (int q = o.mlo[blockIdx.y] + tid; q < m1; q += T) {
-        const double2 y = ps_interp(lds, o.tout_s, o.tout_w, q, i0);
+    for (int q = m0 + tid; q < m1; q += T) {
+        const double2 y = ps_interp(lds, to, i0);
+        if (q + T < m1) to = ps_tap(o.tout_s, o.tout_w, q + T);
         BV[(size_t)ra * n + q] = y.x;
         if (hasb) BV[(size_t)rb * n + q] = y.y;
     }
@@ -319,16 +348,16 @@ __global__ __launch_bounds__(256) void ps_resid_rows(const double* __restrict__ 
     const int s = t * mlen;
     const int cnt = i < n ? max(0, min(mlen, n - s)) : 0;
     double x[MM];
+    // indices clamped into the grid, so that every read of the chunk is in flight at once
+    const int ic = min(i, n - 1);
 #pragma unroll
     for (int q = 0; q < MM; ++q) {
-        x[q] = 0.0;
-        if (q < cnt) {
-            const int j = s + q;
-            const size_t o_ = (size_t)i * n + j;
-            const double y = Y[o_];
-            const double by = BV ? BV[o_] : 0.0;
-            x[q] = W[o_] - y + sk.c * (ps_DY(Y, o, i, j) + by - o.r_omega * y);
-        }
+        const int j = min(s + q, n - 1);
+        const size_t o_ = (size_t)ic * n + j;
+        const double y = Y[o_];
+        const double by = BV ? BV[o_] : 0.0;
+        const double v = W[o_] - y + sk.c * (ps_DY(Y, o, ic, j) + by - o.r_omega * y);
+        x[q] = q < cnt ? v : 0.0;
     }
     chunk_solve<MM>(x, s, cnt, g, t, P, 1, sk.fl2, sk.bu2, sk.bc2, wtot);
 #pragma unroll
@@ -357,13 +386,19 @@ __global__ __launch_bounds__(1024) void ps_line_cols(double* __restrict__ Q, dou
     double x[MM];
 #pragma unroll
     for (int q = 0; q < MM; ++q) x[q] = q < cnt ? Q[(size_t)(s + q) * n + col] : 0.0;
+    constexpr bool EARLY = MM <= 8;                // the iterate read ahead of the solve, while registers allow
+    double yv[EARLY ? MM : 1];
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int q = 0; q < MM; ++q) yv[q] = q < cnt ? Y[(size_t)(s + q) * n + col] : 0.0;
+    }
     chunk_solve<MM>(x, s, cnt, c, t, P, 4, sk.fl1, sk.bu1, sk.bc1, wtot);
     double emax = 0.0;
 #pragma unroll
     for (int q = 0; q < MM; ++q) {
         if (q < cnt) {
             const size_t o_ = (size_t)(s + q) * n + col;
-            const double y = Y[o_] + x[q];
+            const double y = (EARLY ? yv[EARLY ? q : 0] : Y[o_]) + x[q];
             if (store_delta) Q[o_] = x[q];        // each thread rewrites the elements it read
             else Y[o_] = y;
             const double ev = fabs(x[q]) / fmax(1.0, fabs(y));
