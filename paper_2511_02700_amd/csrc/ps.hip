@@ -587,7 +587,7 @@ void enqueue_step(PsPlan* p, int s, int kmax, MState& m) {
     }
     hipLaunchKernelGGL(ps_sl, eb, dim3(256), 0, p->stream, p->ops, a, (const PsCtl*)p->ctl);
     for (int k = 1; k <= kmax; ++k) iteration(p, kd, a.Y, a.W, k);
-    hipLaunchKernelGGL(ps_step_end, dim3(1), dim3(1), 0, p->stream, p->ctl, p->counts_d, s, kmax, p->opts.tol);
+    hipLaunchKernelGGL(ps_step_end, dim3(1), dim3(PS_END_T), 0, p->stream, p->ctl, p->counts_d, s, kmax, p->opts.tol);
     m.y = y;
     m.w = wcur;
     m.cur = y;
@@ -672,7 +672,7 @@ int march(PsPlan* p, int nsteps, double* v_out) {
                 ++k;
                 hipLaunchKernelGGL(ps_ctl_reset, dim3(1), dim3(1), 0, p->stream, p->ctl, 0);
                 iteration(p, kd, p->pool[after.y], p->Wb[after.w], k);
-                hipLaunchKernelGGL(ps_step_end, dim3(1), dim3(1), 0, p->stream, p->ctl, p->counts_d, f, k, p->opts.tol);
+                hipLaunchKernelGGL(ps_step_end, dim3(1), dim3(PS_END_T), 0, p->stream, p->ctl, p->counts_d, f, k, p->opts.tol);
                 PS_TRY(hipGetLastError());
                 PS_TRY(hipMemcpyAsync(p->ctl_h, p->ctl, sizeof(PsCtl), hipMemcpyDeviceToHost, p->stream));
                 PS_TRY(hipStreamSynchronize(p->stream));

@@ -682,23 +682,40 @@ static __global__ __launch_bounds__(256) void ps_sl(PsOps o, PsSL a, const PsCtl
 // the step's count and err is cleared for the next step; without one the
 // failure flag is set (2 if an increment was not finite) and err is kept, so
 // that the host can add iterations.  One thread.
-static __global__ void ps_step_end(PsCtl* ctl, int* counts, int s, int kmax, double tol) {
-    if (ctl->fail) return;
+// One wave: the verdict is a ballot over the iterations' stopping values.
+constexpr int PS_END_T = 64;
+static __global__ __launch_bounds__(PS_END_T) void ps_step_end(PsCtl* ctl, int* counts, int s, int kmax, double tol) {
+    const int t = threadIdx.x;
+    KRef<PsCtl> r = kref(ctl);
+    if (r.fail) return;
     int kc = 0;
     bool nan = false;
-    for (int k = 1; k <= kmax; ++k) {
-        const double e = ps_bits(ctl->err[k]);
-        if (e != e) nan = true;
-        if (kc == 0 && e < tol) kc = k;
+    unsigned long long last = 0;
+    for (int k0 = 0; k0 <= kmax && kc == 0; k0 += PS_END_T) {
+        const int k = k0 + t;
+        const bool in = k >= 1 && k <= kmax;
+        const unsigned long long bits = in ? ctl->err[k] : 0ull;
+        const double e = ps_bits(bits);
+        nan = nan || __ballot(in && e != e) != 0;
+        const unsigned long long met = __ballot(in && e < tol);
+        if (met) {
+            const int lane = __ffsll(met) - 1;
+            kc = k0 + lane;
+            last = __shfl(bits, lane);
+        }
     }
     if (kc == 0) {
-        ctl->fail = nan ? 2 : 1;
-        counts[s] = 0;
+        if (t == 0) {
+            ctl->fail = nan ? 2 : 1;
+            counts[s] = 0;
+        }
         return;
     }
-    counts[s] = kc;
-    ctl->last = ctl->err[kc];
-    for (int k = 0; k < PS_MAXK + 2; ++k) ctl->err[k] = 0ull;
+    if (t == 0) {
+        counts[s] = kc;
+        ctl->last = last;
+    }
+    for (int k = t; k < PS_MAXK + 2; k += PS_END_T) ctl->err[k] = 0ull;
 }
 
 static __global__ void ps_ctl_reset(PsCtl* ctl, int clear_err) {

@@ -215,27 +215,36 @@ template <> __device__ __forceinline__ GP<float2> specbuf<float2>(Args& a) { ret
 // included).  In the others B V^{n-1} is carried from the previous step: its
 // last accumulated B Y, still in BY when the step's first iteration adds to it.
 
-// Fill c->now for step c->step (below nsteps) from the pool bookkeeping and the
+// The pool bookkeeping of a step, in registers of the kernel that starts it.
+struct Book {
+    int step, cur, y, w, nsrc, bvalid;
+    int src[4];
+    double coef[4];
+};
+
+// Fill c->now for step k.step (below nsteps) from the pool bookkeeping k and the
 // step's set sd (index id); cn: cn_rho of the step.  One thread.
-__device__ __forceinline__ void step_setup(Args& a, Ctl* c, const StepDesc& sd, int id, double cn) {
+template <typename SD>
+__device__ __forceinline__ void step_setup(Args& a, Ctl* c, const Book& k, SD& sd, int id, double cn) {
     StepNow& w = c->now;
-    const double rho = a.cn_rho && c->step > a.step0 ? cn : 0.0;
+    const double rho = a.cn_rho && k.step > a.step0 ? cn : 0.0, theta = sd.theta, dt = sd.dt;
     w.set = id;
-    w.cth = sd.dt * sd.theta;
-    w.cex = sd.dt * (1.0 - sd.theta);
+    w.cth = dt * theta;
+    w.cex = dt * (1.0 - theta);
     w.rho = rho;
-    w.expl = sd.theta >= 1.0 ? EXPL_NONE : (rho > 0.0 ? EXPL_IDENTITY : EXPL_CORR);
-    w.anchor = a.mixed && (c->step - a.step0) % a.anchor_every == 0;
-    w.V = a.pool[c->cur];
-    w.Y = a.pool[c->y];
-    w.W = a.Wb[c->w];
-    w.Wp = a.Wb[c->w ^ 1];
-    w.B = a.bpool[c->y];
+    w.expl = theta >= 1.0 ? EXPL_NONE : (rho > 0.0 ? EXPL_IDENTITY : EXPL_CORR);
+    w.anchor = a.mixed && (k.step - a.step0) % a.anchor_every == 0;
+    w.V = a.pool[k.cur];
+    w.Y = a.pool[k.y];
+    w.W = a.Wb[k.w];
+    w.Wp = a.Wb[k.w ^ 1];
+    w.B = a.bpool[k.y];
     bool lin = a.bpool[0] != nullptr;
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int b = c->src[q < c->nsrc ? q : 0];
-        if (q < c->nsrc) lin = lin && ((c->bvalid >> b) & 1);
-        else w.coef[q] = 0.0;
+        const int b = k.src[q < k.nsrc ? q : 0];
+        if (q < k.nsrc) lin = lin && ((k.bvalid >> b) & 1);
+        w.coef[q] = q < k.nsrc ? k.coef[q] : 0.0;
         w.H[q] = a.pool[b];
         w.Hb[q] = a.bpool[b];
     }
@@ -1055,75 +1064,96 @@ __global__ __launch_bounds__(L / E) void ks_line_rows(const MarchArgs* __restric
     if constexpr (FFT) rows_fwd_store<L, E>(reg, reinterpret_cast<C*>(lds), tw4, xbuf<C>(a), n, ra, hasb);
 }
 
+// Threads of ks_step_end: one wave, so that the verdict is a ballot.
+constexpr int END_T = 64;
+
 // End of a step: convergence verdict, history rotation, next starting value.
-// One block per plan.
-static __global__ void ks_step_end(const MarchArgs* __restrict__ A, Ctl* __restrict__ Cs, int kmax) {
+// One block per plan.  A chain of reads bounds it (control block, step list, set, pool
+// pointers): each is one set of scalar reads, the bookkeeping stays in registers and is
+// written once (reading and writing it in memory word by word: 5.0 us
+// behind a step of the 512^2 march, now 4.5).
+static __global__ __launch_bounds__(END_T) void ks_step_end(const MarchArgs* __restrict__ A, Ctl* __restrict__ Cs,
+                                                            int kmax) {
     Args& a = plan_args(A);
     Ctl* c = Cs + blockIdx.y;
-    if (c->hold || c->step >= a.nsteps) return;
-    __shared__ int ok;
-    __shared__ double ek[KSLOTS];
+    CtlK& r = plan_ctl(Cs);
+    int s = r.step, hold = r.hold, fail = r.fail, y = r.y, hc = r.hc, w = r.w, bv = r.bvalid;
+    int h0 = r.hist[0], h1 = r.hist[1], h2 = r.hist[2], h3 = r.hist[3];
+    // read here: none of these reads may move behind the writes below
+    asm volatile("" : "+s"(s), "+s"(y), "+s"(hc), "+s"(w), "+s"(bv), "+s"(h0), "+s"(h1), "+s"(h2), "+s"(h3)::"memory");
+    if (hold || s >= a.nsteps) return;
     // the next step's set, read ahead of the verdict
-    const int s2 = c->step + 1, sn = s2 < a.nsteps ? s2 : c->step;
-    const int id = a.step_set[sn];
-    const double cn = a.cn_rho ? a.cn_rho[sn] : 0.0;
-    const StepDesc sd = a.sets[id];
-    for (int q = threadIdx.x; q <= kmax; q += blockDim.x) ek[q] = err_max(*c, q);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ok = 0;
-        if (!c->fail) {
-            const int s = c->step;
-            int kk = 0;
-            for (int q = 1; q <= kmax; ++q)
-                if (ek[q] < a.tol) { kk = q; break; }
-            if (kk == 0) {
-                c->fail = 1;
-                c->fail_step = s;
-            } else {
-                ok = 1;
-                a.counts[s] = kk;
-                a.incs[s] = ek[kk];
-                c->recent[s & 3] = kk;
-                const bool inner_sub = a.damping && s < a.n_sub - 1;
-                if (inner_sub) {
-                    c->cur = c->y;                        // next damped sub-step starts here
-                } else {
-                    for (int q = 3; q > 0; --q) c->hist[q] = c->hist[q - 1];
-                    c->hist[0] = c->y;
-                    c->hc = c->hc < 4 ? c->hc + 1 : 4;
-                    c->cur = c->y;
-                }
-                c->bvalid |= 1 << c->cur;                 // its B Y was stored by the row kernel
-                int fr = -1;
-                for (int b = 0; b < POOL && fr < 0; ++b) {
-                    bool used = b == c->cur;
-                    for (int q = 0; q < c->hc; ++q) used = used || b == c->hist[q];
-                    if (!used) fr = b;
-                }
-                c->y = fr;
-                c->bvalid &= ~(1 << fr);                  // the free grid takes the next iterate
-                c->w ^= 1;
-                c->step = s2;
-                double* cf = c->now.coef;
-                for (int q = 0; q < 4; ++q) c->src[q] = c->hist[q];
-                if (a.damping && s2 < a.n_sub) {
-                    c->nsrc = 1;
-                    c->src[0] = c->cur;
-                    cf[0] = 1.0;
-                } else {
-                    c->nsrc = c->hc;
-                    if (c->hc == 1) { cf[0] = 1.0; }
-                    else if (c->hc == 2) { cf[0] = 2.0; cf[1] = -1.0; }
-                    else if (c->hc == 3) { cf[0] = 3.0; cf[1] = -3.0; cf[2] = 1.0; }
-                    else { cf[0] = 4.0; cf[1] = -6.0; cf[2] = 4.0; cf[3] = -1.0; }
-                }
-                if (s2 < a.nsteps) step_setup(a, c, sd, id, cn);
-            }
+    const int s2 = s + 1, sn = s2 < a.nsteps ? s2 : s;
+    const int id = kref(a.step_set + sn);
+    const double cn = a.cn_rho ? (double)kref(a.cn_rho + sn) : 0.0;
+    KRef<StepDesc> sd = kref(a.sets + id);
+    if (fail) return;
+    int kk = 0;
+    double inc = 0.0;
+    for (int q0 = 0; q0 <= kmax && kk == 0; q0 += END_T) {
+        const int q = q0 + (int)threadIdx.x;
+        const double e = q <= kmax ? err_max(r, q) : 0.0;
+        const unsigned long long met = __ballot(q >= 1 && q <= kmax && e < a.tol);
+        if (met) {
+            const int lane = __ffsll(met) - 1;
+            kk = q0 + lane;
+            inc = __shfl(e, lane);
         }
     }
-    __syncthreads();
-    if (ok) err_reset_upto(c, kmax);
+    if (kk == 0) {
+        if (threadIdx.x == 0) {
+            c->fail = 1;
+            c->fail_step = s;
+        }
+        return;
+    }
+    Book k;
+    const bool sub = a.damping && s < a.n_sub - 1;    // the next damped sub-step starts here
+    const int hist[4] = {sub ? h0 : y, sub ? h1 : h0, sub ? h2 : h1, sub ? h3 : h2};
+    const int hn = sub ? hc : (hc < 4 ? hc + 1 : 4);
+    k.cur = y;
+    int fr = -1;
+#pragma unroll
+    for (int b = POOL - 1; b >= 0; --b) {
+        bool used = b == k.cur;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) used = used || (q < hn && b == hist[q]);
+        if (!used) fr = b;
+    }
+    k.y = fr;
+    k.bvalid = (bv | (1 << k.cur)) & ~(1 << fr);      // B of the state was stored by the row kernel; the free
+                                                      // grid takes the next iterate
+    k.w = w ^ 1;
+    k.step = s2;
+    const bool damped = a.damping && s2 < a.n_sub;
+    k.nsrc = damped ? 1 : hn;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) k.src[q] = hist[q];
+    if (damped) k.src[0] = k.cur;
+    // extrapolation from nsrc states
+    k.coef[0] = k.nsrc;
+    k.coef[1] = k.nsrc == 2 ? -1.0 : (k.nsrc == 3 ? -3.0 : -6.0);
+    k.coef[2] = k.nsrc == 3 ? 1.0 : 4.0;
+    k.coef[3] = -1.0;
+    if (threadIdx.x == 0) {
+        a.counts[s] = kk;
+        a.incs[s] = inc;
+        c->recent[s & 3] = kk;
+        c->cur = k.cur;
+        c->y = k.y;
+        c->w = k.w;
+        c->hc = hn;
+        c->bvalid = k.bvalid;
+        c->nsrc = k.nsrc;
+        c->step = s2;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            c->hist[q] = hist[q];
+            c->src[q] = k.src[q];
+        }
+        if (s2 < a.nsteps) step_setup(a, c, k, sd, id, cn);
+    }
+    err_reset_upto(c, kmax);
 }
 
 // Recording for the adjoint march.  After sl (once per step): E_s, held in now.Wp
@@ -1176,7 +1206,8 @@ static __global__ void ks_adj_begin(const MarchArgs* __restrict__ A, Ctl* __rest
         c->nsrc = 0;
         c->bvalid = 0;
         for (int q = 0; q < 4; ++q) c->src[q] = 0;
-        step_setup(a, c, a.sets[id], id, 0.0);
+        const Book k = {s, 0, 1, 0, 0, 0, {0, 0, 0, 0}, {0.0, 0.0, 0.0, 0.0}};
+        step_setup(a, c, k, kref(a.sets + id), id, 0.0);
     }
 }
 
@@ -1490,10 +1521,10 @@ static __global__ void ks_init(const MarchArgs* __restrict__ A, Ctl* __restrict_
         c->nsrc = 1;
         c->bvalid = 0;
         for (int q = 0; q < 4; ++q) { c->hist[q] = 0; c->src[q] = 0; c->recent[q] = 0; }
-        c->now.coef[0] = 1.0;
+        const Book k = {a.step0, 0, 1, 0, 1, 0, {0, 0, 0, 0}, {1.0, 0.0, 0.0, 0.0}};
         if (a.step0 < a.nsteps) {
             const int id = a.step_set[a.step0];
-            step_setup(a, c, a.sets[id], id, a.cn_rho ? a.cn_rho[a.step0] : 0.0);
+            step_setup(a, c, k, kref(a.sets + id), id, a.cn_rho ? a.cn_rho[a.step0] : 0.0);
         }
     }
 }
