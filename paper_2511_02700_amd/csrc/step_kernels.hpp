@@ -540,6 +540,58 @@ __global__ __launch_bounds__(L / E) void ks_rows_inv(const MarchArgs* __restrict
         }
         return;
     }
+    if constexpr (MODE == 2 && L <= 1536) {
+        // the mixed form likewise: the epilogue's sums in the same order as below, from values
+        // held across the transform (march at 300^2 15.4 -> 14.4 ms, 512^2 29.4 -> 28.4,
+        // 1000^2 84.4 -> 82.4).  Up to 1024 the gather's reads go first; at 1536 that takes
+        // 131 registers and 47.9 ms at 700^2 against 44.8, above 1536 the held values alone
+        // cost blocks in flight.
+        const GP<double> U(c.now.Y), W(c.now.W), R(a.R), BY(a.BY), base((k == 1 && c.now.anchor) ? a.BV : a.BY);
+        const double cf = c.now.cth, r_omega = a.r_omega, c0 = -1.0;
+        const StencilArgs st = stencil(a);
+        const int o0 = max(ra - 1, 0) * n, o1 = ra * n, o2 = min(rb, n - 1) * n, o3 = min(rb + 1, n - 1) * n;
+        constexpr bool AHEAD = L <= 1024;
+        C xv[rows_inv_items(L, E)];
+        if constexpr (AHEAD) rows_inv_read<L, E>(xv, xbuf<C>(a), n, ra, hasb);
+        double d[E][2], u[E][2], w[E][2], b[E][2];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = min(tid + e * T, n - 1), jm = max(j - 1, 0), jp = min(j + 1, n - 1);
+            const double a0 = U[o0 + jm], a1 = U[o0 + j], a2 = U[o0 + jp], b0 = U[o1 + jm], b1 = U[o1 + j], b2 = U[o1 + jp];
+            const double c0_ = U[o2 + jm], c1 = U[o2 + j], c2 = U[o2 + jp], d0 = U[o3 + jm], d1 = U[o3 + j], d2 = U[o3 + jp];
+            d[e][0] = D_of(st, ra, j, b1, a1, c1, b0, b2, a0, a2, c0_, c2);
+            d[e][1] = D_of(st, rb, j, c1, b1, d1, c0_, c2, b0, b2, d0, d2);
+            u[e][0] = b1;
+            u[e][1] = c1;
+            w[e][0] = W[o1 + j];
+            w[e][1] = W[o2 + j];
+            b[e][0] = base[o1 + j];
+            b[e][1] = base[o2 + j];
+            if constexpr (!AHEAD) asm volatile("" : "+v"(d[e][0]), "+v"(d[e][1])::"memory");
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            asm volatile("" : "+v"(d[e][0]), "+v"(d[e][1]), "+v"(u[e][0]), "+v"(u[e][1]), "+v"(w[e][0]), "+v"(w[e][1]),
+                         "+v"(b[e][0]), "+v"(b[e][1]));
+        if constexpr (AHEAD) rows_inv_exchange<L, E>(reg, lds, xv);
+        else rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
+        fft_block<L, E, true>(reg, lds, tw4);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int j = tid + e * T;
+            if (j >= n) continue;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                if (r == 1 && !hasb) break;
+                const int o = (ra + r) * n + j;
+                double bu = r == 0 ? (double)reg[e].x : (double)reg[e].y;
+                bu += b[e][r];
+                BY.put(o, bu);
+                R.put(o, w[e][r] + cf * (d[e][r] + bu - r_omega * u[e][r]) + c0 * u[e][r]);
+            }
+        }
+        return;
+    }
     rows_inv_gather<L, E>(reg, lds, xbuf<C>(a), n, ra, hasb);
     fft_block<L, E, true>(reg, lds, tw4);
     constexpr bool EXPL = MODE == 0;
