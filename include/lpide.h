@@ -349,11 +349,11 @@ int lpide_plan_set_checkpoints(void* plan, int32_t every);
  * index 6 + (l1 + N_z) * 2 N_z + (l2 + N_z).  grad (host[8], may be NULL):
  * dJ/d(sigma1, sigma2, corr, theta1, theta2, kappa, alpha, r), the
  * subordination parameters std_params (host[8], same order) the plan's model
- * was made from by lpide_levy_from_std (checked); the host quantities are
+ * was made from by lpide_levy_from_std (checked); the model's quantities are
  * differentiated by central differences in the seven Levy parameters (step
- * 1e-4 max(|x|, 0.1), structure fixed) and exactly in r (it enters only
- * kappa_omega and r_omega, with unit slope); the Jacobian is cached per plan
- * and point.  Needs a plan with jumps.  The reverse march is FP64; on a
+ * 1e-4 max(|x|, 0.1), structure fixed), evaluated on the device, and exactly
+ * in r (it enters only kappa_omega and r_omega, with unit slope).
+ * Needs a plan with jumps.  The reverse march is FP64; on a
  * mixed-form plan the forward states it differentiates at (recomputed from
  * the checkpoints, with B V anchored at each checkpoint) carry the mixed
  * form's error.  Synchronises. */
