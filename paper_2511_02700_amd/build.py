@@ -13,6 +13,7 @@ links them into one shared library next to this file.
 import os
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -52,19 +53,19 @@ def build(verbose=False, jobs=None):
     # a failed build leaves no library behind, so nothing runs stale code
     if os.path.exists(LIB):
         os.remove(LIB)
-    objs = [os.path.join(CSRC, o) for _, o, _ in UNITS]
-    with ThreadPoolExecutor(max_workers=jobs) as ex:
-        futs = [ex.submit(_compile, src, obj, extra, verbose) for (src, _, extra), obj in zip(UNITS, objs)]
-        for f in futs:
-            f.result()
-    tmp = LIB + ".tmp"
-    cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp] + objs + ["-lpthread"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
-    os.replace(tmp, LIB)
-    for o in objs:
-        os.remove(o)
+    # objects outside the tree: a killed compiler leaves its temporaries beside them
+    with tempfile.TemporaryDirectory(prefix="lpide_build_") as d:
+        objs = [os.path.join(d, o) for _, o, _ in UNITS]
+        with ThreadPoolExecutor(max_workers=jobs) as ex:
+            futs = [ex.submit(_compile, src, obj, extra, verbose) for (src, _, extra), obj in zip(UNITS, objs)]
+            for f in futs:
+                f.result()
+        tmp = LIB + ".tmp"
+        cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp] + objs + ["-lpthread"]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+        os.replace(tmp, LIB)
     return LIB
 
 
