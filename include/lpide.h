@@ -516,6 +516,9 @@ typedef struct {
     double  last_increment;           /* last stopping-rule value of the last march */
     int64_t device_bytes;
     int32_t accel_depth;              /* Anderson depth in use (0: the paper's iteration) */
+    int16_t tile_L, tiles;            /* side of the transforms the correlation runs in, and how many
+                                         overlapping tiles of it cut each axis (L and 1: not tiled).  They
+                                         take the place of padding: the structure's size is unchanged */
 } lpide_ps_info;
 
 /* The paper's settings on N_x intervals over [0, x_max]: x_int = 5K/2,
@@ -525,7 +528,7 @@ void lpide_ps_grid_default(lpide_ps_grid* g, int32_t N_x, double x_max);
 
 /* Host-only discretization of the price-space plan (no device is touched):
  * fills info (sizes of the grids, c, h_z, z_star, sum_omega, kappa, r_omega,
- * S, a; L is the automatic transform side, 0 without jumps) and, where not
+ * S, a; L, tile_L and tiles are the automatic ones, 0 without jumps) and, where not
  * NULL, x (host, N_x + 1 nodes), v0 (host, (N_x+1)^2 pay-off grid) and omega
  * (host, (2 N_z)^2 weights, only if omega_len is at least that).  Errors as
  * lpide_ps_plan_create's validation. */

@@ -95,7 +95,7 @@ class PsInfo(C.Structure):
                 ("h_z", C.c_double), ("z_star", C.c_double), ("sum_omega", C.c_double),
                 ("kappa", C.c_double * 2), ("r_omega", C.c_double), ("S", C.c_double * 3), ("a", C.c_double * 3),
                 ("total_iters", C.c_int64), ("max_step_iters", C.c_int32), ("last_increment", C.c_double),
-                ("device_bytes", C.c_int64), ("accel_depth", C.c_int32)]
+                ("device_bytes", C.c_int64), ("accel_depth", C.c_int32), ("tile_L", C.c_int16), ("tiles", C.c_int16)]
 
     def to_dict(self):
         out = {}

@@ -753,6 +753,12 @@ int lpide_ps_discretize_host(const lpide_ps_grid* grid, const lpide_levy* levy, 
     info->n_out = hp.n_out;
     info->n_nz = hp.n_nz;
     info->L = hp.nts.jumps ? lpide::ps::ps_side_at_least(hp.n_in) : 0;
+    if (info->L > 0) {
+        int side = 0, nb = 0;
+        lpide::ps::choose_tiles(hp, info->L, &side, &nb);
+        info->tile_L = int16_t(side);
+        info->tiles = int16_t(nb);
+    }
     info->c = hp.c;
     info->x_int = hp.x_int;
     info->F = hp.F;
@@ -804,6 +810,8 @@ int lpide_ps_plan_info(void* plan, lpide_ps_info* info) {
     info->n_out = hp.n_out;
     info->n_nz = hp.n_nz;
     info->L = p->L;
+    info->tile_L = int16_t(p->Lc);
+    info->tiles = int16_t(p->jumps ? p->nb : 0);
     info->N_t = p->N_t;
     info->n_steps = int32_t(p->steps.size());
     info->c = hp.c;
