@@ -479,7 +479,7 @@ const char* lpide_last_error(void);
  * 1152, 1280, 1536, 1792, 2048, 2304, 2560, 3072, 3584, 4096, 4608, 5120,
  * 6144, 7168, 8192, 12288, 16384, 24576 (largest prime factor at most 7, as
  * Sec. 4 asks), whose correlation runs as overlapping tiles of a smaller side
- * where that is faster (always above 8192 unless 2 N_z comes near 8192);
+ * where that is measured to be faster (lpide_ps_info.tile_L, tiles);
  * otherwise one of these or 768, at least #in, as one transform; sides above
  * 8192 then run as (3, 4, 6) transforms of length 4096 per sequence) and
  * all_correlations (0: the explicit part of a step after one

@@ -67,7 +67,7 @@ int tiles_for(int M, int n_out, int N_z) {
     return std::max(1, (n_out - 3 + vs - 1) / vs);
 }
 
-// Time of the column pass of one tile pair of side M (us, n = 401; the row
+// Time of the column pass of one transform of side M alone (us, n = 401; the row
 // passes are a tenth of it); 0 below 1024, where nothing is gained by tiles.
 double tile_us(int M) {
     switch (M) {
@@ -91,22 +91,63 @@ double tile_us(int M) {
     }
 }
 
+// Time of B v per tile pair as they run (us, n = 201 to 1297), several to a grid: a
+// column's tile pairs share its spectrum column in L2, and small ones overlap.  Runs of
+// 4 to several hundred pairs lie within 10% of these.
+double pair_us(int M) {
+    switch (M) {
+        case 1024: return 2.9;
+        case 1152: return 6.3;
+        case 1280: return 6.0;
+        case 1536: return 7.4;
+        case 1792: return 11.5;
+        case 2048: return 13.0;
+        case 2304: return 31.0;
+        case 2560: return 30.0;
+        case 3072: return 43.0;
+        case 3584: return 53.0;
+        case 4096: return 58.0;
+        case 4608: return 119.0;
+        case 5120: return 144.0;
+        case 6144: return 185.0;
+        case 7168: return 268.0;
+        case 8192: return 305.0;
+        default: return 0.0;
+    }
+}
+
+// Time of B v by one two-level transform (us, n = 245 to 830; at 2000 a third more, as
+// the tiles' is), by the segments of length 4096 that hold its kept outputs.
+double two_level_us(int L, int n_out) {
+    const int so = std::min(6, (n_out + 4095) / 4096);
+    if (L == 12288) return so == 1 ? 1100.0 : (so == 2 ? 1300.0 : 1500.0);
+    if (L == 16384) return so <= 2 ? 2600.0 : (so == 3 ? 2800.0 : 3500.0);
+    return so <= 3 ? 7000.0 : (so == 4 ? 8000.0 : (so == 5 ? 13600.0 : 15600.0));
+}
+
 // Transforms of the correlation when no side is asked for: one of side L, or
 // nb x nb tiles of a side M <= 8192 (one workgroup per sequence) where that is
-// faster: above 4096 a CU holds one workgroup, so that four tiles of 4096 take
-// 277 us where one transform of 8192 takes 361 (NIG0 at N_x = 200, B v whole:
-// 256 us against 350 at 7168).  The two-level transforms take 7e-7 us L^2 log2 L
-// or more (B v whole 1.47 ms at 12288, 3.3 at 16384, 8.0 at 24576; by tiles of 4096
-// and 8192 on the same grids 0.83, 1.32 and 2.82).
+// faster.  Up to 8192 both by the column pass alone: above 4096 a CU holds one
+// workgroup, so that four tiles of 4096 take 277 us where one transform of 8192 takes
+// 361 (B v whole: 250 us against 381 for NIG0 at N_x = 224, 184 against 225 at 168).
+// Above 8192 both by B v whole, two-level transform against tiles: NIG0 at N_x = 400
+// 3.31 ms against 1.26 by four tiles of 8192, 448 3.57 against 2.32 by nine of 7168; NIG1
+// at 600 1.66 against 1.28, 760 3.64 against 2.73, 988 13.7 against 7.3; VG0 at 1500, whose
+// few outputs are one segment, 1.32 against 1.42, and VG1 at 1096 and 1800, whose weights
+// leave a tile few outputs, 1.63 against 2.81 and 9.6 against 65.
+// (Costed by 7e-7 us L^2 log2 L and by the column pass alone, 448, 600, 760 and 988 took
+// the two-level transform.)
 void choose_tiles(const PsHost& hp, int L, int* Lc, int* nb) {
     *Lc = L;
     *nb = 1;
-    double best = L > 8192 ? 7.0e-7 * double(L) * L * std::log2(double(L)) : tile_us(L);
+    const bool two = L > 8192;
+    double best = two ? two_level_us(L, hp.n_out) : tile_us(L);
     for (int M : kPsAutoSides) {
-        if (M >= L || tile_us(M) == 0.0) continue;
+        const double us = two ? pair_us(M) : tile_us(M);
+        if (M >= L || us == 0.0) continue;
         const int t = tiles_for(M, hp.n_out, hp.N_z);
         if (t < 1) continue;
-        const double c = double(t) * t * tile_us(M);
+        const double c = double(t) * t * us;
         if (c < best) {
             best = c;
             *Lc = M;

@@ -1,7 +1,8 @@
 // Two-level transforms of the price-space correlation for sides L = R M
 // beyond one workgroup's LDS (M = 4096; R = 3, 4, 6: L = 12288, 16384, 24576):
-// forced sides (lpide_opts.fft_size), and kernels so long (2 N_z near or above
-// 8192) that tiles of at most 8192 would keep too few outputs each.
+// forced sides (lpide_opts.fft_size), and grids where tiles of at most 8192 are
+// the slower form (choose_tiles): the weights leave a tile few outputs, or the
+// outputs are few.
 //
 // With w_N = exp(-2 pi i / N), a length-L transform splits by decimation in
 // frequency into R transforms of length M,
