@@ -79,12 +79,10 @@ def algorithmic_bytes(cls, n, L, mixed=False):
         "carry": 4 * 8 * n * n,
         # FP64 explicit part from the previous step's equation: read V and W, write E
         "expl_id": 3 * 8 * n * n,
-        # FP64 iteration 1 by linearity: read 4 stored products (3 in the steps just
-        # after the damping), W and Y; write R and the stored B Y^0
-        "rows_lin": 8 * 8 * n * n,
         # step begin without transforms (explicit part, SL, start value and iteration 1 in
-        # one): read the previous W, four history grids, four stored products; write W,
+        # one launch): read the previous W, four history grids, four stored products; write W,
         # Y^0, B Y^0 and R
+        "rows_lin": 13 * 8 * n * n,
         "sl_lin": 13 * 8 * n * n,
     }[cls]
 
@@ -97,10 +95,21 @@ def line_rows_capacity(n, L, el):
     return el if m <= el else (3 * el // 2 if m <= 3 * el // 2 else 2 * el)
 
 
+def step_begin_rows(n):
+    """Rows per tile of the step-begin kernel for one plan: 8 where such tiles (of at
+    most 252 columns, in whole cache lines where that fits) fill the chip with four
+    blocks per CU, else 2."""
+    c = -(-n // ((n + 251) // 252))
+    r = (c + 15) // 16 * 16
+    cols = r if r <= 252 else c
+    return 8 if -(-n // 8) * -(-n // cols) >= 1024 else 2
+
+
 def kernel_symbol(cls, L, mixed, sl_order, radix=(8, 8, 8, 8), n=None):
     """The kernel instantiation a timing class launches in the march (radix =
     elements per thread of the column pass, row c2r, line-row and SL kernels;
-    n: grid side, for the line-row kernel's chunk capacity)."""
+    n: grid side, for the line-row kernel's chunk capacity and the step-begin
+    kernel's tiles)."""
     tf = "true" if mixed else "false"
     c = "float" if mixed and cls == "cols" else "double"
     ec, er, el, es = radix
@@ -118,8 +127,8 @@ def kernel_symbol(cls, L, mixed, sl_order, radix=(8, 8, 8, 8), n=None):
         "rows_fwd": "lpide::ks_rows_fwd<%d, %d>" % (L, er),
         "carry": "lpide::ks_carry",
         "expl_id": "lpide::ks_expl_identity",
-        "rows_lin": "lpide::ks_begin_lin<%d" % sl_order,
-        "sl_lin": "lpide::ks_begin_lin<%d" % sl_order,
+        "rows_lin": "lpide::ks_begin_lin<%d, %d>" % (sl_order, step_begin_rows(n or L)),
+        "sl_lin": "lpide::ks_begin_lin<%d, %d>" % (sl_order, step_begin_rows(n or L)),
     }[cls]
 
 
