@@ -94,7 +94,6 @@ struct Ctl {
     int hist[4];                      // pool indices, newest first
     int bvalid;                       // bit b: bpool[b] holds B applied to pool[b] (this march)
     int w;                            // SL buffer of this step (the step before wrote the other one)
-    int src[4];                       // pool indices of the start value's sources
     int recent[4];                    // iteration counts of the last four steps, at step mod 4
     // stopping-rule value after iteration k: the maximum over x of err[x][k]
     // (bit patterns of non-negative doubles).  The row blocks of the line-solve
@@ -1199,10 +1198,7 @@ static __global__ __launch_bounds__(END_T) void ks_step_end(const MarchArgs* __r
         c->nsrc = k.nsrc;
         c->step = s2;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            c->hist[q] = hist[q];
-            c->src[q] = k.src[q];
-        }
+        for (int q = 0; q < 4; ++q) c->hist[q] = hist[q];
         if (s2 < a.nsteps) step_setup(a, c, k, sd, id, cn);
     }
     err_reset_upto(c, kmax);
@@ -1257,7 +1253,6 @@ static __global__ void ks_adj_begin(const MarchArgs* __restrict__ A, Ctl* __rest
         c->w = 0;
         c->nsrc = 0;
         c->bvalid = 0;
-        for (int q = 0; q < 4; ++q) c->src[q] = 0;
         const Book k = {s, 0, 1, 0, 0, 0, {0, 0, 0, 0}, {0.0, 0.0, 0.0, 0.0}};
         step_setup(a, c, k, kref(a.sets + id), id, 0.0);
     }
@@ -1572,7 +1567,7 @@ static __global__ void ks_init(const MarchArgs* __restrict__ A, Ctl* __restrict_
         c->hc = 1;
         c->nsrc = 1;
         c->bvalid = 0;
-        for (int q = 0; q < 4; ++q) { c->hist[q] = 0; c->src[q] = 0; c->recent[q] = 0; }
+        for (int q = 0; q < 4; ++q) { c->hist[q] = 0; c->recent[q] = 0; }
         const Book k = {a.step0, 0, 1, 0, 1, 0, {0, 0, 0, 0}, {1.0, 0.0, 0.0, 0.0}};
         if (a.step0 < a.nsteps) {
             const int id = a.step_set[a.step0];
