@@ -521,8 +521,8 @@ def price_space_check(lp):
 def adjoint_measure(lp, name="nts1024", C=32):
     """The adjoint form on its workload: forward solve time, and the adjoint's
     march part (segment recompute + reverse steps + gather, with the solve's
-    checkpoints reused) and host Jacobian, for J = a seeded combination of 64
-    spot-pair prices."""
+    checkpoints reused) and the model's gradient, for J = a seeded combination of
+    64 spot-pair prices."""
     import numpy as np
     import torch
     import workloads
@@ -539,7 +539,7 @@ def adjoint_measure(lp, name="nts1024", C=32):
     plan.set_checkpoints(C)
     V = plan.solve()
     vbar = plan.price_adjoint(spots, wts)
-    # one untimed call first, as for the forward solves (graph captures, Jacobian cache)
+    # one untimed call first, as for the forward solves (its buffers are allocated on first use)
     plan.adjoint(vbar, checkpoint_every=C, std_params=lp.std_params_of(w))
     t0 = time.perf_counter()
     grad, _, info = plan.adjoint(vbar, checkpoint_every=C, std_params=lp.std_params_of(w))
@@ -582,6 +582,7 @@ def adjoint_measure(lp, name="nts1024", C=32):
             "forward_all_correlations_ms": 1e3 * t_fwd_all,
             "ratio_to_forward_all_correlations": march / (1e3 * t_fwd_all),
             "keep_all_states": keep_all,
+            # the model's gradient (the key is older than its evaluation on the device)
             "host_jacobian_ms": info["jacobian_ms"], "adjoint_wall_ms": 1e3 * t_adj,
             "adjoint_iters_per_step": info["adj_iters"] / n_steps,
             "grad": [float(g) for g in grad]}

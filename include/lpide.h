@@ -566,7 +566,7 @@ int lpide_ps_apply_B(void* plan, const double* v, double* bv);
 /* The first `steps` entries of the step list (0 <= steps <= n_steps; the
  * whole march with steps = n_steps).  v_out: device, (N_x+1)^2.  Errors as
  * lpide_solve (LPIDE_E_NOCONV, LPIDE_E_NAN).  Synchronises the plan's
- * stream (the stopping rule is read back between batches of steps). */
+ * stream (the stopping rule is read back between windows of steps). */
 int lpide_ps_solve_steps(void* plan, int32_t steps, double* v_out);
 
 /* Delta and Gamma surfaces of a price-space grid at the nodes by the

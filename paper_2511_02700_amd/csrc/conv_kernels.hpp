@@ -14,8 +14,9 @@
 // chain makes the pass 5.0 us against 4.2.  B v: 33.8 -> 33.1 us at n = 1001,
 // 49.2 -> 43.4 at n = 1200 in L = 2048, 118 -> 81 at n = 1400 in L = 3072, 139 -> 97
 // at n = 2000.
-// The plan-time spectrum keeps conv_e(L) elements: the mixed form's results
-// answer a change of its rounding at 1e-9.
+// The plan-time spectrum keeps conv_e(L) elements so that the mixed form's results
+// stay bit for bit what they were; a change of its rounding would move them by 1e-9,
+// within their error of about 1e-8.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -6,10 +6,18 @@
 // for every LDS operation in flight.  GP states that the memory is global and
 // the base uniform, so that accesses are global instructions with a scalar base
 // and a 32-bit offset (arrays up to 4 GB; the largest grid and intermediate hold
-// 134 MB).  KRef reads structures that no kernel of a march changes while it
-// runs through the scalar cache, as one set of loads in flight.  Together (every
-// kernel of a march used to follow six to nine dependent flat loads before its
-// first work): 512^2 march 41.9 -> 38.1 ms, 2048^2 656 -> 572, 24 plans 195 -> 170.
+// 134 MB).  KRef reads the plan's arguments and its control block through the
+// scalar cache, as one set of loads in flight.  Together (every kernel of a march
+// used to follow six to nine dependent flat loads before its first work): 512^2
+// march 41.9 -> 38.1 ms, 2048^2 656 -> 572, 24 plans 195 -> 170.
+//
+// What KRef reads is constant to the compiler, and the scalar cache does not see
+// the vector stores of the kernel that reads it.  So a word read through KRef must
+// not be written by the same kernel until every use of the value is complete, or
+// the value is pinned in registers (an asm volatile with it as an operand).  The
+// control block's readers that also write it keep to that: the line-row kernel reads
+// the stopping values of the iteration before the one whose it raises, the kernels
+// that end a step have consumed or pinned what they read before they rewrite it.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -72,8 +72,9 @@ __device__ __forceinline__ double apply_D(GP<double> U, const StencilArgs& s, in
 // along axis 1, u2m, u2p along axis 2, u00 .. u11 the corners (first index axis
 // 1).  The interior tests select the arithmetic only (a zero a12 adds a zero
 // mixed term), so that none of a node's reads is conditional.  The row c2r
-// kernel, which unrolls many elements, keeps apply_D, whose branches throttle
-// the reads in flight.
+// kernel's forms whose stencil follows the transform (the explicit part, and the
+// mixed form above L = 1536) unroll many elements and keep apply_D, whose branches
+// throttle the reads in flight.
 __device__ __forceinline__ double D_of(const StencilArgs& s, int i, int j, double u, double u1m, double u1p, double u2m,
                                        double u2p, double u00, double u01, double u10, double u11) {
     const int n = s.n;

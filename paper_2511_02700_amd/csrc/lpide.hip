@@ -504,8 +504,10 @@ static int supported_e(int L, int E) {
 //   row c2r   2048 18.1 21.5 32.2 (n = 1024); 3072 54.5 95.0 95.9; 4096 79.1 73.7 106;
 //   line rows 1024 9.2 10.2 13.4; 2048 17.7 16.5 20.4; 3072 45.8 67.1 50.6 (n = 2048),
 //             31.2 42.9 39.6 (n = 1500); 4096 68.6 49.8 60.7.
-// The mixed form keeps the schedule it was tuned with: another radix rounds its
-// FP32 transforms differently, which its results show at 1e-9.
+// The mixed form keeps an earlier schedule, for reproducibility and not for time: its
+// results stay bit for bit what they were, while another radix would move them by 1e-9
+// (its error is about 1e-8, its bound 1e-6).  At 512^2 its FP32 column pass, E = 16,
+// takes 10.0 us where the FP64 one with E = 4 takes 8.8.
 Schedule default_schedule(int L, bool mixed) {
     Schedule s;
     if (!mixed) {

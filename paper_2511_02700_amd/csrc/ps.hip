@@ -67,8 +67,8 @@ int tiles_for(int M, int n_out, int N_z) {
     return std::max(1, (n_out - 3 + vs - 1) / vs);
 }
 
-// Time of the column pass of one transform of side M alone (us, n = 401; the row
-// passes are a tenth of it); 0 below 1024, where nothing is gained by tiles.
+// Time of the column pass of one transform of side M alone (us, n = 401, all taken in one
+// run; the row passes are a tenth of it); 0 below 1024, where nothing is gained by tiles.
 double tile_us(int M) {
     switch (M) {
         case 1024: return 10.4;

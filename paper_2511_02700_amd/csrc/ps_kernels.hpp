@@ -681,8 +681,8 @@ static __global__ __launch_bounds__(256) void ps_sl(PsOps o, PsSL a, const PsCtl
 // End of step s after kmax iterations: the first k with err_k < tol becomes
 // the step's count and err is cleared for the next step; without one the
 // failure flag is set (2 if an increment was not finite) and err is kept, so
-// that the host can add iterations.  One thread.
-// One wave: the verdict is a ballot over the iterations' stopping values.
+// that the host can add iterations.  One wave: the verdict is a ballot over the
+// iterations' stopping values.
 constexpr int PS_END_T = 64;
 static __global__ __launch_bounds__(PS_END_T) void ps_step_end(PsCtl* ctl, int* counts, int s, int kmax, double tol) {
     const int t = threadIdx.x;
